@@ -233,7 +233,9 @@ struct Accum {
   bool done = false;
   bool switched = false;   // opacity acceleration: leave the lines for the pyramid
   MergeLds mt;
-  __device__ Accum(const MergeLds& m) : mt(m) {
+  __device__ Accum(const MergeLds& m) : mt(m) {}
+  // empties the merge table (transparent lines only: opaque ones use none)
+  __device__ inline void open() {
 #pragma unroll
     for (int k = 0; k < kMergeSlots; ++k) {
       mt.tag[k * kWave] = 0xFFFFFFFFu;
@@ -290,8 +292,9 @@ struct Shade {
 // rendering"): the LUT opacity a holds for a chord of one tube diameter, so a
 // chord of length l has opacity 1 - (1 - a)^(l / 2r) (a tangent hit, l = 0,
 // has none).
+template <bool kOpaque>
 __device__ inline float fragment_alpha(const RenderArgs& R, float a, float chord) {
-  if (R.opaque) return 1.f;
+  if (kOpaque) return 1.f;
   if (!R.dist_alpha) return a;
   if (!(chord > 0.f)) return 0.f;
   if (a >= 1.f) return 1.f;
@@ -541,14 +544,14 @@ __device__ inline float4 lut_along(const float4* lut_lds, uint32_t en, const flo
                      l0.w + f * (l1.w - l0.w));
 }
 
-template <bool kVdi>
+template <bool kVdi, bool kOpaque>
 __device__ __attribute__((always_inline)) inline void composite(const RenderArgs& R, const float4* lut_lds, const Shade& S, Accum& acc, uint64_t rec,
                                  uint32_t k, const int32_t cell[3], const float p[3],
                                  const float a[3], const float b[3], float dt, Counts& cnt) {
   #pragma clang fp contract(fast)
   const int attr = (int)((rec >> 32) & 0xFF);
   const float4 lut = (kVdi && R.ends) ? lut_along(lut_lds, R.ends[k], p, a, b) : lut_lds[attr];
-  const float alpha = fragment_alpha(R, lut.w, dt * S.dlen);
+  const float alpha = fragment_alpha<kOpaque>(R, lut.w, dt * S.dlen);
   float col[3] = {lut.x, lut.y, lut.z};
   if (R.shading != 0) {
     float ba[3] = {b[0] - a[0], b[1] - a[1], b[2] - a[2]};
@@ -923,8 +926,82 @@ __device__ inline double shfl_f64(double v, int src) {
   return __hiloint2double(__shfl(__double2hiint(v), src, 64), __shfl(__double2loint(v), src, 64));
 }
 
-// Called by all 64 lanes together. Lane `mine` owns the voxel vcell entered
-// at vt0 with lines [lo, hi).
+// The first hit of an opaque ray, kept until the wave's walk has ended: the
+// line, the voxel that holds it and the entry point in that voxel's frame.
+struct FirstHit {
+  uint32_t k = 0xFFFFFFFFu;
+  int32_t cell[3];
+  float p[3];
+  __device__ inline bool any() const { return k != 0xFFFFFFFFu; }
+};
+
+// Opaque lines. Called by all 64 lanes together. Lane `mine` owns the voxel
+// vcell entered at vt0 with lines [lo, hi) and keeps the nearest hit in h.
+__device__ __attribute__((always_inline)) inline void voxels_opaque(
+    const RenderArgs& R, const Ray& ray, const int32_t vcell[3], double vt0, float dd,
+    float inv_dd, bool mine, uint32_t lo, uint32_t hi, Accum& acc, FirstHit& h, Counts& cnt) {
+  const int lane = wave_lane();
+  const uint32_t n = mine ? hi - lo : 0u;
+  if (__ballot(n != 0u) == 0ull) return;
+  float q[3] = {0.f, 0.f, 0.f};
+  if (mine) local_origin(ray, vt0, vcell, q);
+  uint32_t N;
+  const uint32_t P = wave_excl_scan(n, N);
+  float best = INFINITY;
+  uint32_t bi = 0xFFFFFFFFu;
+  for (uint32_t base = 0; base < N; base += 64) {
+    const uint32_t w = base + (uint32_t)lane;
+    const int r = pair_owner(P, w);
+    const float qr[3] = {__shfl(q[0], r, 64), __shfl(q[1], r, 64), __shfl(q[2], r, 64)};
+    const float dr[3] = {__shfl(ray.d[0], r, 64), __shfl(ray.d[1], r, 64),
+                         __shfl(ray.d[2], r, 64)};
+    const float ddr = __shfl(dd, r, 64), iddr = __shfl(inv_dd, r, 64);
+    const uint32_t lor = __shfl(lo, r, 64), Pr = __shfl(P, r, 64);
+    const double vt0r = shfl_f64(vt0, r);
+    bool hit = false;
+    float si = 0.f, so = 0.f;
+    uint32_t k = 0;
+    if (w < N) {
+      k = lor + (w - Pr);
+      const uint64_t rec = R.records[k];
+      float a[3], b[3];
+      decode_point((uint32_t)(rec & 0x7FFFu), R.inv_bins, a);
+      decode_point((uint32_t)((rec >> 15) & 0x7FFFu), R.inv_bins, b);
+      cnt.tested++;
+      hit = capsule(qr, dr, ddr, iddr, a, b, R.r2, si, so) && vt0r + (double)si >= 0.0;
+    }
+    unsigned long long m =
+        __ballot(hit) & bit_range(max((int)P - (int)base, 0), min((int)(P + n) - (int)base, 64));
+    while (__ballot(m != 0ull) != 0ull) {
+      const int src = m ? __builtin_ctzll(m) : 0;
+      const float ts = __shfl(si, src, 64);
+      const uint32_t ks = __shfl(k, src, 64);
+      if (m) {
+        cnt.hits++;
+        if (ts < best || (ts == best && ks < bi)) {
+          best = ts;
+          bi = ks;
+        }
+        m &= m - 1ull;
+      }
+    }
+  }
+  if (mine) {
+    cnt.list_bytes += 8u * n;
+    if (bi != 0xFFFFFFFFu) {
+      h.k = bi;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        h.cell[c] = vcell[c];
+        h.p[c] = q[c] + best * ray.d[c];
+      }
+      acc.done = true;
+    }
+  }
+}
+
+// Transparent lines. Called by all 64 lanes together. Lane `mine` owns the
+// voxel vcell entered at vt0 with lines [lo, hi).
 template <bool kVdi>
 __device__ __attribute__((always_inline)) inline void voxels_coop(
     const RenderArgs& R, const float4* lut_lds, const Ray& ray, const int32_t vcell[3],
@@ -935,63 +1012,6 @@ __device__ __attribute__((always_inline)) inline void voxels_coop(
   if (__ballot(n != 0u) == 0ull) return;
   float q[3] = {0.f, 0.f, 0.f};
   if (mine) local_origin(ray, vt0, vcell, q);
-  if (R.opaque) {
-    uint32_t N;
-    const uint32_t P = wave_excl_scan(n, N);
-    float best = INFINITY;
-    uint32_t bi = 0xFFFFFFFFu;
-    for (uint32_t base = 0; base < N; base += 64) {
-      const uint32_t w = base + (uint32_t)lane;
-      const int r = pair_owner(P, w);
-      const float qr[3] = {__shfl(q[0], r, 64), __shfl(q[1], r, 64), __shfl(q[2], r, 64)};
-      const float dr[3] = {__shfl(ray.d[0], r, 64), __shfl(ray.d[1], r, 64),
-                           __shfl(ray.d[2], r, 64)};
-      const float ddr = __shfl(dd, r, 64), iddr = __shfl(inv_dd, r, 64);
-      const uint32_t lor = __shfl(lo, r, 64), Pr = __shfl(P, r, 64);
-      const double vt0r = shfl_f64(vt0, r);
-      bool hit = false;
-      float si = 0.f, so = 0.f;
-      uint32_t k = 0;
-      if (w < N) {
-        k = lor + (w - Pr);
-        const uint64_t rec = R.records[k];
-        float a[3], b[3];
-        decode_point((uint32_t)(rec & 0x7FFFu), R.inv_bins, a);
-        decode_point((uint32_t)((rec >> 15) & 0x7FFFu), R.inv_bins, b);
-        cnt.tested++;
-        hit = capsule(qr, dr, ddr, iddr, a, b, R.r2, si, so) && vt0r + (double)si >= 0.0;
-      }
-      unsigned long long m =
-          __ballot(hit) & bit_range(max((int)P - (int)base, 0), min((int)(P + n) - (int)base, 64));
-      while (__ballot(m != 0ull) != 0ull) {
-        const int src = m ? __builtin_ctzll(m) : 0;
-        const float ts = __shfl(si, src, 64);
-        const uint32_t ks = __shfl(k, src, 64);
-        if (m) {
-          cnt.hits++;
-          if (ts < best || (ts == best && ks < bi)) {
-            best = ts;
-            bi = ks;
-          }
-          m &= m - 1ull;
-        }
-      }
-    }
-    if (mine) {
-      cnt.list_bytes += 8u * n;
-      if (bi != 0xFFFFFFFFu) {
-        const uint64_t rec = R.records[bi];
-        float a[3], b[3], p[3];
-        decode_point((uint32_t)(rec & 0x7FFFu), R.inv_bins, a);
-        decode_point((uint32_t)((rec >> 15) & 0x7FFFu), R.inv_bins, b);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) p[c] = q[c] + best * ray.d[c];
-        composite<kVdi>(R, lut_lds, S, acc, rec, bi, vcell, p, a, b, 0.f, cnt);
-        acc.done = true;
-      }
-    }
-    return;
-  }
   // transparent: passes of up to kCoopSlots hits per owner, in (t, index) order
   bool need = n != 0u;
   bool first = true;
@@ -1061,7 +1081,7 @@ __device__ __attribute__((always_inline)) inline void voxels_coop(
         decode_point((uint32_t)((rc >> 15) & 0x7FFFu), R.inv_bins, b);
 #pragma unroll
         for (int c = 0; c < 3; ++c) p[c] = q[c] + t_in * ray.d[c];
-        composite<kVdi>(R, lut_lds, S, acc, rc, ki, vcell, p, a, b, t_out - t_in, cnt);
+        composite<kVdi, false>(R, lut_lds, S, acc, rc, ki, vcell, p, a, b, t_out - t_in, cnt);
       }
       need = more && !acc.done;
       if (need) cnt.passes++;
@@ -1156,7 +1176,7 @@ __device__ inline bool capsule_abs(const Ray& ray, double tr, const float q[3], 
   return lo <= hi;
 }
 
-template <bool kVdi>
+template <bool kVdi, bool kOpaque>
 __device__ __attribute__((always_inline)) inline void voxel_exact(const RenderArgs& R, const float4* lut_lds, const Ray& ray, const Shade& S, float dd,
                                    float inv_dd, double idd, double t1, Accum& acc, Counts& cnt) {
   double last_t = -INFINITY;
@@ -1200,7 +1220,7 @@ __device__ __attribute__((always_inline)) inline void voxel_exact(const RenderAr
       const uint64_t rec = buf.rec[0];
       const uint32_t ki = buf.idx[0];
       buf.pop_front();
-      if (!R.opaque && R.merge) {
+      if (!kOpaque && R.merge) {
         const uint32_t tag = (uint32_t)(rec >> 40);
         if (merge_hit(acc, tag, t_in, t_in + (double)len, cnt)) continue;
       }
@@ -1214,8 +1234,8 @@ __device__ __attribute__((always_inline)) inline void voxel_exact(const RenderAr
       decode_point((uint32_t)((rec >> 15) & 0x7FFFu), R.inv_bins, b);
 #pragma unroll
       for (int c = 0; c < 3; ++c) p[c] = q[c] + s_in * ray.d[c];
-      composite<kVdi>(R, lut_lds, S, acc, rec, ki, w, p, a, b, len, cnt);
-      if (R.opaque) acc.done = true;
+      composite<kVdi, kOpaque>(R, lut_lds, S, acc, rec, ki, w, p, a, b, len, cnt);
+      if (kOpaque) acc.done = true;
     }
     if (acc.done || !more) break;
     first = false;
@@ -1248,7 +1268,7 @@ __device__ inline void flush_counts(RenderCounters* out, const Counts& c) {
   }
 }
 
-template <int kMode, bool kVdi>
+template <int kMode, bool kVdi, bool kOpaque>
 // All 64 lanes of the wave call this together (mode 0 tests lists
 // cooperatively); a lane whose pixel lies outside the image takes part
 // with a dead ray and writes nothing.
@@ -1259,6 +1279,8 @@ __device__ __attribute__((always_inline)) inline void render_pixel(const RenderA
   dda_init(R, ray);
   if (!valid) ray.alive = false;
   Accum acc(mt);
+  if (!kOpaque) acc.open();
+  FirstHit hit;
   const uint32_t live_ev0 = cnt.live_evictions;
   {
     const float dd = dot3(ray.d, ray.d);
@@ -1324,7 +1346,20 @@ __device__ __attribute__((always_inline)) inline void render_pixel(const RenderA
             ray.t0 = dda_step(R, ray);
           }
         }
-        voxels_coop<kVdi>(R, lut_lds, ray, vc, vt0, S, dd, inv_dd, mine, lo, hi, acc, cnt);
+        if (kOpaque)
+          voxels_opaque(R, ray, vc, vt0, dd, inv_dd, mine, lo, hi, acc, hit, cnt);
+        else
+          voxels_coop<kVdi>(R, lut_lds, ray, vc, vt0, S, dd, inv_dd, mine, lo, hi, acc, cnt);
+      }
+      // Opaque rays end at different steps of the wave's walk; shading each at
+      // its own step would run the shading code (and hemisphere AO's 16 rays)
+      // once per distinct step on a few lanes. It runs once here, on all.
+      if (kOpaque && hit.any()) {
+        const uint64_t rec = R.records[hit.k];
+        float a[3], b[3];
+        decode_point((uint32_t)(rec & 0x7FFFu), R.inv_bins, a);
+        decode_point((uint32_t)((rec >> 15) & 0x7FFFu), R.inv_bins, b);
+        composite<kVdi, true>(R, lut_lds, S, acc, rec, hit.k, hit.cell, hit.p, a, b, 0.f, cnt);
       }
     } else {
       for (int it = 0; it < max_steps && ray.alive && !acc.done; ++it) {
@@ -1332,7 +1367,7 @@ __device__ __attribute__((always_inline)) inline void render_pixel(const RenderA
         const int64_t vid =
             ray.cell[0] + (int64_t)R.g[0] * (ray.cell[1] + (int64_t)R.g[1] * ray.cell[2]);
         if (R.offsets[vid + 1] > R.offsets[vid]) cnt.nonempty++;
-        voxel_exact<kVdi>(R, lut_lds, ray, S, dd, inv_dd, idd, peek_t1(ray), acc, cnt);
+        voxel_exact<kVdi, kOpaque>(R, lut_lds, ray, S, dd, inv_dd, idd, peek_t1(ray), acc, cnt);
         ray.t0 = dda_step(R, ray);
       }
     }
@@ -1355,8 +1390,13 @@ __device__ inline void tile_pixel(const RenderArgs& R, int tile, int wave, int l
 template <bool kVdi>
 __device__ __attribute__((always_inline)) inline void render_any(const RenderArgs& R, const float4* lut_lds, const MergeLds& mt, int i, int j,
                        bool valid, Counts& cnt) {
-  if (R.mode == 0) render_pixel<0, kVdi>(R, lut_lds, mt, i, j, valid, cnt);
-  else render_pixel<1, kVdi>(R, lut_lds, mt, i, j, valid, cnt);
+  if (R.mode == 0) {
+    if (R.opaque) render_pixel<0, kVdi, true>(R, lut_lds, mt, i, j, valid, cnt);
+    else render_pixel<0, kVdi, false>(R, lut_lds, mt, i, j, valid, cnt);
+  } else {
+    if (R.opaque) render_pixel<1, kVdi, true>(R, lut_lds, mt, i, j, valid, cnt);
+    else render_pixel<1, kVdi, false>(R, lut_lds, mt, i, j, valid, cnt);
+  }
 }
 
 // Stages a view's transfer function (256 RGBA) in LDS.
@@ -1365,7 +1405,7 @@ __device__ inline void load_lut(const RenderArgs& R, float4* lut_lds) {
     lut_lds[k] = reinterpret_cast<const float4*>(R.lut)[k];
 }
 
-template <int kMode, bool kCount, bool kVdi>
+template <int kMode, bool kCount, bool kVdi, bool kOpaque>
 __global__ __launch_bounds__(kBlock) void k_render(RenderArgs R) {
   const unsigned long long t_start = R.times ? wall_clock64() : 0ull;
   int b = blockIdx.x;
@@ -1469,7 +1509,7 @@ __global__ __launch_bounds__(kBlock) void k_render(RenderArgs R) {
     } else {
       tile_pixel(R, tile, threadIdx.x >> 6, lane, i, j);
     }
-    render_pixel<kMode, kVdi>(R, lut_lds, merge_lds, i, j, valid && i < R.W && j < R.H, cnt);
+    render_pixel<kMode, kVdi, kOpaque>(R, lut_lds, merge_lds, i, j, valid && i < R.W && j < R.H, cnt);
   }
   if (kCount) flush_counts(R.counters, cnt);
   if (R.times && threadIdx.x == 0) {
@@ -1807,6 +1847,34 @@ int make_render_args(const ls_lineset* s, const ls_camera* cam, const ls_render_
   return LS_OK;
 }
 
+namespace {
+
+// The plain launch's kernel for a view. One instance per (mode, counters,
+// view-dependent illumination, opacity): the per-fragment illumination code,
+// the sort buffer and the merge table stay out of the instances that do not
+// use them.
+using RenderKernel = void (*)(RenderArgs);
+
+RenderKernel render_kernel(const RenderArgs& R) {
+  static const RenderKernel kernels[2][2][2][2] = {
+      {{{k_render<0, false, false, false>, k_render<0, false, false, true>},
+        {k_render<0, false, true, false>, k_render<0, false, true, true>}},
+       {{k_render<0, true, false, false>, k_render<0, true, false, true>},
+        {k_render<0, true, true, false>, k_render<0, true, true, true>}}},
+      {{{k_render<1, false, false, false>, k_render<1, false, false, true>},
+        {k_render<1, false, true, false>, k_render<1, false, true, true>}},
+       {{k_render<1, true, false, false>, k_render<1, true, false, true>},
+        {k_render<1, true, true, false>, k_render<1, true, true, true>}}}};
+  return kernels[R.mode != 0][R.counters != nullptr][view_dependent(R)][R.opaque != 0];
+}
+
+// Its dynamic LDS: the merge table, which opaque lines have no use for.
+size_t render_lds_bytes(const RenderArgs& R, unsigned threads) {
+  return R.opaque ? 0 : merge_lds_bytes(threads);
+}
+
+}  // namespace
+
 int launch_render(const RenderArgs& R, hipStream_t st) {
   const int tiles_y = R.n_tiles / R.tiles_x;
   const unsigned blocks =
@@ -1815,28 +1883,8 @@ int launch_render(const RenderArgs& R, hipStream_t st) {
                                      R.split_n * (R.split_s - 1))
                         : (unsigned)(kXcds * ((tiles_y + kXcds - 1) / kXcds) * R.tiles_x);
   const unsigned threads = (unsigned)(64 * R.wx * R.wy);
-  const size_t lds = merge_lds_bytes(threads);
   const dim3 grid(blocks), block(threads);
-  const bool vdi = view_dependent(R), cnt = R.counters != nullptr;
-  // one instance per (mode, counters, view-dependent illumination): the
-  // per-fragment illumination code stays out of the other instances
-  if (R.mode == 0) {
-    if (vdi) {
-      if (cnt) hipLaunchKernelGGL((k_render<0, true, true>), grid, block, lds, st, R);
-      else hipLaunchKernelGGL((k_render<0, false, true>), grid, block, lds, st, R);
-    } else {
-      if (cnt) hipLaunchKernelGGL((k_render<0, true, false>), grid, block, lds, st, R);
-      else hipLaunchKernelGGL((k_render<0, false, false>), grid, block, lds, st, R);
-    }
-  } else {
-    if (vdi) {
-      if (cnt) hipLaunchKernelGGL((k_render<1, true, true>), grid, block, lds, st, R);
-      else hipLaunchKernelGGL((k_render<1, false, true>), grid, block, lds, st, R);
-    } else {
-      if (cnt) hipLaunchKernelGGL((k_render<1, true, false>), grid, block, lds, st, R);
-      else hipLaunchKernelGGL((k_render<1, false, false>), grid, block, lds, st, R);
-    }
-  }
+  hipLaunchKernelGGL(render_kernel(R), grid, block, render_lds_bytes(R, threads), st, R);
   LS_HIP(hipGetLastError());
   return LS_OK;
 }
@@ -1922,22 +1970,23 @@ int grow(void** p, size_t* have, size_t bytes, hipStream_t st) {
   return pool_alloc(bytes, p, have);
 }
 
-// Workgroups the plain launch keeps resident on the device at once.
-int resident_blocks(int* out) {
+// Workgroups of the view's kernel that the device keeps resident at once.
+int resident_blocks(const RenderArgs& R, int* out) {
   static std::mutex mu;
-  static std::map<int, int> cache;
+  static std::map<std::pair<int, RenderKernel>, int> cache;
   int dev = 0;
   LS_HIP(hipGetDevice(&dev));
+  const RenderKernel k = render_kernel(R);
   std::lock_guard<std::mutex> lk(mu);
-  auto it = cache.find(dev);
+  auto it = cache.find({dev, k});
   if (it == cache.end()) {
     hipDeviceProp_t prop;
     LS_HIP(hipGetDeviceProperties(&prop, dev));
     int per_cu = 0;
     LS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &per_cu, reinterpret_cast<const void*>(k_render<0, false, false>), kWave,
-        merge_lds_bytes(kWave)));
-    it = cache.emplace(dev, prop.multiProcessorCount * (per_cu > 0 ? per_cu : 1)).first;
+        &per_cu, reinterpret_cast<const void*>(k), kWave, render_lds_bytes(R, kWave)));
+    it = cache.emplace(std::make_pair(dev, k),
+                       prop.multiProcessorCount * (per_cu > 0 ? per_cu : 1)).first;
   }
   *out = it->second;
   return LS_OK;
@@ -1950,7 +1999,7 @@ int resident_blocks(int* out) {
 int tile_order(const ls_lineset* s, const ls_camera* cam, const ls_render_params* p,
                RenderArgs& R, hipStream_t st) {
   int resident = 0, rc;
-  if ((rc = resident_blocks(&resident))) return rc;
+  if ((rc = resident_blocks(R, &resident))) return rc;
   if ((int64_t)R.n_tiles + (int64_t)R.split_n * (R.split_s - 1) <= resident) return LS_OK;
   OrderKey key;
   std::memset(&key, 0, sizeof(key));
