@@ -18,7 +18,7 @@ struct ls_batch {
   int n_views = 0;
   int total_tiles = 0;
   int32_t flags = 0;
-  bool vdi = false;          // some view uses per-fragment illumination
+  BatchKind kind;            // instance of the batched kernel its views need
   BatchPlan plan{2, 2, 0};
   BatchQueues queues{};
   std::vector<ls_view> views;
@@ -46,6 +46,11 @@ std::map<std::string, BatchPlan> g_plan_cache;
 bool view_dependent_params(const ls_view& v) {
   return (v.params.shading == 2 && (v.params.ao_mode != 0 || v.params.shadow_mode != 0)) ||
          (v.set && v.set->ends != nullptr) || (!v.params.opaque && v.params.accel_depth > 0.f);
+}
+
+void add_kind(BatchKind* kind, const ls_view& v) {
+  kind->vdi = kind->vdi || view_dependent_params(v);
+  kind->nb = kind->nb || v.params.mode != 0;
 }
 
 std::string signature(const std::vector<ls_view>& v) {
@@ -104,16 +109,16 @@ int launch(ls_batch* b, bool count, hipStream_t st) {
   int rc;
   if ((rc = fill_u32(b->d_queue, 0u, count ? kQueueWords : 8, st))) return rc;
   return launch_render_batch(b->d_args, b->d_tile_start, b->n_views, b->queues, b->d_queue,
-                             b->plan, count, b->vdi, st);
+                             b->plan, count, b->kind, st);
 }
 
-int plan_blocks(int wx, int wy, int mult, bool vdi, int* blocks) {
+int plan_blocks(int wx, int wy, int mult, const BatchKind& kind, int* blocks) {
   int dev = 0, per_cu = 1;
   LS_HIP(hipGetDevice(&dev));
   hipDeviceProp_t prop;
   LS_HIP(hipGetDeviceProperties(&prop, dev));
   int rc;
-  if ((rc = batch_blocks_per_cu(wx, wy, vdi, &per_cu))) return rc;
+  if ((rc = batch_blocks_per_cu(wx, wy, kind, &per_cu))) return rc;
   *blocks = prop.multiProcessorCount * per_cu * mult;
   return LS_OK;
 }
@@ -135,7 +140,7 @@ int autotune(ls_batch* b, hipStream_t st) {
   for (const auto& sh : shapes) {
     for (int mult : mults) {
       BatchPlan p{sh[0], sh[1], 0};
-      if ((rc = plan_blocks(p.wx, p.wy, mult, b->vdi, &p.blocks))) break;
+      if ((rc = plan_blocks(p.wx, p.wy, mult, b->kind, &p.blocks))) break;
       if ((rc = prepare(b, p, st))) break;
       if ((rc = launch(b, false, st))) break;  // warm
       LS_HIP(hipEventRecord(e0, st));
@@ -254,7 +259,7 @@ static int create_batch(const ls_view* views, int32_t n_views, int32_t flags, co
   b->n_views = n_views;
   b->flags = flags;
   b->views.assign(views, views + n_views);
-  for (const ls_view& x : b->views) b->vdi = b->vdi || view_dependent_params(x);
+  for (const ls_view& x : b->views) add_kind(&b->kind, x);
   (void)hipGetDevice(&b->device);
   auto fail = [&](int code) {
     (void)hipStreamSynchronize(st);
@@ -278,7 +283,7 @@ static int create_batch(const ls_view* views, int32_t n_views, int32_t flags, co
   }
   if (fixed) {
     BatchPlan p{fixed[0], fixed[1], 0};
-    rc = plan_blocks(p.wx, p.wy, fixed[2], b->vdi, &p.blocks);
+    rc = plan_blocks(p.wx, p.wy, fixed[2], b->kind, &p.blocks);
     if (!rc) rc = prepare(b, p, st);
   } else if (cached.blocks > 0) {
     rc = prepare(b, cached, st);
@@ -291,7 +296,7 @@ static int create_batch(const ls_view* views, int32_t n_views, int32_t flags, co
     }
   } else {
     BatchPlan p{2, 2, 0};
-    rc = plan_blocks(p.wx, p.wy, 1, b->vdi, &p.blocks);
+    rc = plan_blocks(p.wx, p.wy, 1, b->kind, &p.blocks);
     if (!rc) rc = prepare(b, p, st);
   }
   if (!rc && (flags & LS_BATCH_GRAPH)) rc = capture(b);
@@ -419,9 +424,9 @@ int lineset_render_batch_static(const ls_view* views, int32_t n_views, void* hip
   RenderArgs args[kStaticViews];
   int32_t tile_start[kStaticViews + 1];
   BatchPlan plan{2, 2, 0};
-  bool vdi = false;
-  for (int v = 0; v < n_views; ++v) vdi = vdi || view_dependent_params(views[v]);
-  if ((rc = plan_blocks(plan.wx, plan.wy, 1, vdi, &plan.blocks))) return rc;
+  BatchKind kind;
+  for (int v = 0; v < n_views; ++v) add_kind(&kind, views[v]);
+  if ((rc = plan_blocks(plan.wx, plan.wy, 1, kind, &plan.blocks))) return rc;
   int64_t total = 0;
   for (int v = 0; v < n_views; ++v) {
     const ls_view& x = views[v];
@@ -444,7 +449,7 @@ int lineset_render_batch_static(const ls_view* views, int32_t n_views, void* hip
   rc = fill_u32(d_queue, 0u, 8, st);
   if (!rc) {
     rc = launch_render_batch(d_args, d_tiles, n_views, make_queues((int)total), d_queue, plan,
-                             false, vdi, st);
+                             false, kind, st);
   }
   // Synchronise on every path from here: the copies read the stack arrays.
   if (hipStreamSynchronize(st) != hipSuccess && !rc) {

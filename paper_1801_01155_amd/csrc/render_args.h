@@ -9,6 +9,9 @@ struct RenderArgs {
   const uint32_t* offsets;
   const uint64_t* records;
   const unsigned long long* occ;  // per 4^3 macro cell: mask of non-empty voxels
+  // the same words grown by one voxel in every direction (neighbour mode; may be
+  // null: the kernel forms them)
+  const unsigned long long* grown;
   int32_t g[3];
   int32_t mg[3];                  // macro grid dims
   float inv_bins;
@@ -46,7 +49,7 @@ struct RenderArgs {
   // the waves over the densest part of the image hold fewer rays
   int32_t split_n, split_s;
   // ordered frames: the first top_n launch positions (the longest measured
-  // tiles) are split top_s ways (4 or 8), before the split_n ones above
+  // tiles) are split top_s ways (4, 8 or 16), before the split_n ones above
   int32_t top_n, top_s;
   // plain launch order by measured cost (tile_order): workgroup position p
   // renders tile order[p]; null: the ring order above. times (or null):
@@ -76,12 +79,16 @@ inline bool view_dependent(const RenderArgs& R) {
   return (R.shading == 2 && (R.ao_mode != 0 || R.shadow_mode != 0)) || R.ends != nullptr ||
          R.accel_A0 <= 1.f;
 }
+// What the views of a batch need of its kernel, which is compiled with and
+// without: the extended instance (view_dependent), the neighbour mode.
+struct BatchKind {
+  bool vdi = false, nb = false;
+};
 BatchQueues make_queues(int total_tiles);
 // dev_queue: 8 queue counters (zeroed before the launch), followed by a
 // RenderCounters block when `count` is set.
-// vdi: some view uses view-dependent illumination (view_dependent).
 int launch_render_batch(const RenderArgs* dev_views, const int32_t* dev_tile_start, int n_views,
                         const BatchQueues& q, unsigned* dev_queue, const BatchPlan& plan,
-                        bool count, bool vdi, hipStream_t st);
-int batch_blocks_per_cu(int wx, int wy, bool vdi, int* out);
+                        bool count, const BatchKind& kind, hipStream_t st);
+int batch_blocks_per_cu(int wx, int wy, const BatchKind& kind, int* out);
 int render_merge_slots();   // intervals in the per-ray curve-merge table
