@@ -910,34 +910,57 @@ __device__ inline void local_origin(const Ray& ray, double t, const int32_t cell
 // length; testing each lane's own list leaves most lanes idle while the
 // longest list is tested. Instead the (ray, line) pairs of the whole wave are
 // numbered by a prefix sum over the list lengths and dealt out 64 at a time:
-// pair w belongs to the last lane r with P_r <= w (a binary search over the
-// lanes' prefixes), and the tester reads r's ray frame by cross-lane reads.
+// pair w belongs to the last lane r with P_r <= w (chunk_owner), and the tester reads r's ray frame by cross-lane reads.
 // Hits go back to their owners through a ballot: owner r pulls the hits of
 // the testers in its pair range one by one, so every owner sees the same set
 // of hits (and the same sorted buffer) as if it had tested its list itself.
 __device__ inline int wave_lane() { return (int)(threadIdx.x & 63); }
 
+// Inclusive scans over the wave by DPP moves (row shifts, then the rows' last
+// lanes broadcast): six register-to-register steps. A cross-lane read through
+// the LDS pipe takes more than ten times as long, and the scans are serial
+// chains in every step of a ray.
+template <int kCtrl, int kRows>
+__device__ inline uint32_t dpp_or_0(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, kRows, 0xF, false);
+}
+
+__device__ inline uint32_t wave_incl_sum(uint32_t v) {
+  v += dpp_or_0<0x111, 0xF>(v);   // row_shr 1, 2, 4, 8
+  v += dpp_or_0<0x112, 0xF>(v);
+  v += dpp_or_0<0x114, 0xF>(v);
+  v += dpp_or_0<0x118, 0xF>(v);
+  v += dpp_or_0<0x142, 0xA>(v);   // row_bcast 15 into rows 1 and 3
+  v += dpp_or_0<0x143, 0xC>(v);   // row_bcast 31 into rows 2 and 3
+  return v;
+}
+
+__device__ inline uint32_t wave_incl_max(uint32_t v) {
+  v = max(v, dpp_or_0<0x111, 0xF>(v));
+  v = max(v, dpp_or_0<0x112, 0xF>(v));
+  v = max(v, dpp_or_0<0x114, 0xF>(v));
+  v = max(v, dpp_or_0<0x118, 0xF>(v));
+  v = max(v, dpp_or_0<0x142, 0xA>(v));
+  v = max(v, dpp_or_0<0x143, 0xC>(v));
+  return v;
+}
+
 __device__ inline uint32_t wave_excl_scan(uint32_t v, uint32_t& total) {
-  const int lane = wave_lane();
-  uint32_t inc = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t y = __shfl_up(inc, d, 64);
-    if (lane >= d) inc += y;
-  }
-  total = __shfl(inc, 63, 64);
+  const uint32_t inc = wave_incl_sum(v);
+  total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
   return inc - v;
 }
 
-// Last lane r with P_r <= w (P non-decreasing over the lanes).
-__device__ inline int pair_owner(uint32_t P, uint32_t w) {
-  int r = 0;
-#pragma unroll
-  for (int step = 32; step >= 1; step >>= 1) {
-    const uint32_t pc = __shfl(P, r + step, 64);
-    if (pc <= w) r += step;
-  }
-  return r;
+// Owner of pair base + lane among the wave's pairs (lane r owns [P_r, P_r +
+// n_r), in lane order): each owner marks its first pair of the chunk in the
+// wave's 64 words of LDS, and a running maximum spreads the marks.
+__device__ inline int chunk_owner(uint32_t* own, uint32_t P, uint32_t n, uint32_t base) {
+  const int lane = wave_lane();
+  own[lane] = 0u;
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  if (n != 0u && P < base + 64u && P + n > base) own[P > base ? P - base : 0u] = (uint32_t)lane;
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  return (int)wave_incl_max(own[lane]);
 }
 
 // Bits [a, b) of a 64-bit mask (0 <= a <= b <= 64).
@@ -964,7 +987,8 @@ struct FirstHit {
 // vcell entered at vt0 with lines [lo, hi) and keeps the nearest hit in h.
 __device__ __attribute__((always_inline)) inline void voxels_opaque(
     const RenderArgs& R, const Ray& ray, const int32_t vcell[3], double vt0, float dd,
-    float inv_dd, bool mine, uint32_t lo, uint32_t hi, Accum& acc, FirstHit& h, Counts& cnt) {
+    float inv_dd, bool mine, uint32_t lo, uint32_t hi, uint32_t* own, Accum& acc, FirstHit& h,
+    Counts& cnt) {
   const int lane = wave_lane();
   const uint32_t n = mine ? hi - lo : 0u;
   if (__ballot(n != 0u) == 0ull) return;
@@ -976,7 +1000,7 @@ __device__ __attribute__((always_inline)) inline void voxels_opaque(
   uint32_t bi = 0xFFFFFFFFu;
   for (uint32_t base = 0; base < N; base += 64) {
     const uint32_t w = base + (uint32_t)lane;
-    const int r = pair_owner(P, w);
+    const int r = chunk_owner(own, P, n, base);
     const float qr[3] = {__shfl(q[0], r, 64), __shfl(q[1], r, 64), __shfl(q[2], r, 64)};
     const float dr[3] = {__shfl(ray.d[0], r, 64), __shfl(ray.d[1], r, 64),
                          __shfl(ray.d[2], r, 64)};
@@ -1031,7 +1055,7 @@ template <bool kVdi>
 __device__ __attribute__((always_inline)) inline void voxels_coop(
     const RenderArgs& R, const float4* lut_lds, const Ray& ray, const int32_t vcell[3],
     double vt0, const Shade& S, float dd, float inv_dd, bool mine, uint32_t lo, uint32_t hi,
-    Accum& acc, Counts& cnt) {
+    uint32_t* own, Accum& acc, Counts& cnt) {
   const int lane = wave_lane();
   const uint32_t n = mine ? hi - lo : 0u;
   if (__ballot(n != 0u) == 0ull) return;
@@ -1049,7 +1073,7 @@ __device__ __attribute__((always_inline)) inline void voxels_coop(
     HitBuf<float, kCoopSlots> buf;
     for (uint32_t base = 0; base < N; base += 64) {
       const uint32_t w = base + (uint32_t)lane;
-      const int r = pair_owner(P, w);
+      const int r = chunk_owner(own, P, np, base);
       const float qr[3] = {__shfl(q[0], r, 64), __shfl(q[1], r, 64), __shfl(q[2], r, 64)};
       const float dr[3] = {__shfl(ray.d[0], r, 64), __shfl(ray.d[1], r, 64),
                            __shfl(ray.d[2], r, 64)};
@@ -1393,8 +1417,8 @@ struct NbBuf {
 // Called by all 64 lanes together.
 template <int K>
 __device__ __attribute__((always_inline)) inline void nb_sweep(
-    const RenderArgs& R, const Ray& ray, const NbLds& nl, bool need, int axis, double last_t,
-    uint32_t last_i, NbBuf<K>& buf, Counts& cnt) {
+    const RenderArgs& R, const Ray& ray, const NbLds& nl, uint32_t* own, bool need, int axis,
+    double last_t, uint32_t last_i, NbBuf<K>& buf, Counts& cnt) {
   const int lane = wave_lane();
   int32_t xa = max(ray.cell[0] - 1, 0), xb = min(ray.cell[0] + 1, R.g[0] - 1);
   if (axis == 0) {
@@ -1485,7 +1509,7 @@ __device__ __attribute__((always_inline)) inline void nb_sweep(
 
   for (uint32_t base = 0; base < N; base += 64) {
     const uint32_t w = base + (uint32_t)lane;
-    const int r = pair_owner(P, w);
+    const int r = chunk_owner(own, P, total, base);
     const uint32_t Pr = __shfl(P, r, 64), cr = __shfl(cellp, r, 64), sr = __shfl(span, r, 64);
     bool may = false;
     uint32_t k = 0, cw = 0;
@@ -1545,8 +1569,8 @@ __device__ __attribute__((always_inline)) inline void nb_sweep(
 // first hit in fh.
 template <bool kVdi, bool kOpaque>
 __device__ __attribute__((always_inline)) inline void walk_neighbours(
-    const RenderArgs& R, const float4* lut_lds, const NbLds& nl, Ray& ray, const Shade& S,
-    float dd, float inv_dd, double idd, int max_steps, Accum& acc, FirstHit& fh, Counts& cnt) {
+    const RenderArgs& R, const float4* lut_lds, const NbLds& nl, uint32_t* own, Ray& ray,
+    const Shade& S, float dd, float inv_dd, double idd, int max_steps, Accum& acc, FirstHit& fh, Counts& cnt) {
   constexpr int K = kOpaque ? 2 : kNbSlots;
   const int lane = wave_lane();
   nl.o[lane] = make_float4(ray.o[0], ray.o[1], ray.o[2], dd);
@@ -1609,7 +1633,7 @@ __device__ __attribute__((always_inline)) inline void walk_neighbours(
     bool need = act;
     int face = axis;
     while (__ballot(need) != 0ull) {
-      nb_sweep(R, ray, nl, need, face, last_t, last_i, buf, cnt);
+      nb_sweep(R, ray, nl, own, need, face, last_t, last_i, buf, cnt);
       if (need) {
         while (buf.n > 0 && !acc.done && buf.t[0] < t1) {
           const double t_in = buf.t[0];
@@ -1700,8 +1724,8 @@ template <int kMode, bool kVdi, bool kOpaque>
 // cooperatively); a lane whose pixel lies outside the image takes part
 // with a dead ray and writes nothing.
 __device__ __attribute__((always_inline)) inline void render_pixel(
-    const RenderArgs& R, const float4* lut_lds, const MergeLds& mt, double* nb_lds, int i, int j,
-    bool valid, Counts& cnt) {
+    const RenderArgs& R, const float4* lut_lds, const MergeLds& mt, double* nb_lds, uint32_t* own,
+    int i, int j, bool valid, Counts& cnt) {
   Ray ray;
   make_ray(R, valid ? i : 0, valid ? j : 0, ray.o, ray.d);
   dda_init(R, ray);
@@ -1792,12 +1816,12 @@ __device__ __attribute__((always_inline)) inline void render_pixel(
           }
         }
         if (kOpaque)
-          voxels_opaque(R, ray, vc, vt0, dd, inv_dd, mine, lo, hi, acc, hit, cnt);
+          voxels_opaque(R, ray, vc, vt0, dd, inv_dd, mine, lo, hi, own, acc, hit, cnt);
         else
-          voxels_coop<kVdi>(R, lut_lds, ray, vc, vt0, S, dd, inv_dd, mine, lo, hi, acc, cnt);
+          voxels_coop<kVdi>(R, lut_lds, ray, vc, vt0, S, dd, inv_dd, mine, lo, hi, own, acc, cnt);
       }
     } else {
-      walk_neighbours<kVdi, kOpaque>(R, lut_lds, nb_lds_view(nb_lds), ray, S, dd, inv_dd, idd,
+      walk_neighbours<kVdi, kOpaque>(R, lut_lds, nb_lds_view(nb_lds), own, ray, S, dd, inv_dd, idd,
                                      max_steps, acc, hit, cnt);
     }
     // Opaque rays end at different steps of the wave's walk; shading each at
@@ -1829,14 +1853,14 @@ __device__ inline void tile_pixel(const RenderArgs& R, int tile, int wave, int l
 // kNb: views of the neighbour mode may occur.
 template <bool kVdi, bool kNb>
 __device__ __attribute__((always_inline)) inline void render_any(
-    const RenderArgs& R, const float4* lut_lds, const MergeLds& mt, double* nb_lds, int i, int j,
-    bool valid, Counts& cnt) {
+    const RenderArgs& R, const float4* lut_lds, const MergeLds& mt, double* nb_lds, uint32_t* own,
+    int i, int j, bool valid, Counts& cnt) {
   if (!kNb || R.mode == 0) {
-    if (R.opaque) render_pixel<0, kVdi, true>(R, lut_lds, mt, nb_lds, i, j, valid, cnt);
-    else render_pixel<0, kVdi, false>(R, lut_lds, mt, nb_lds, i, j, valid, cnt);
+    if (R.opaque) render_pixel<0, kVdi, true>(R, lut_lds, mt, nb_lds, own, i, j, valid, cnt);
+    else render_pixel<0, kVdi, false>(R, lut_lds, mt, nb_lds, own, i, j, valid, cnt);
   } else if (kNb) {
-    if (R.opaque) render_pixel<1, kVdi, true>(R, lut_lds, mt, nb_lds, i, j, valid, cnt);
-    else render_pixel<1, kVdi, false>(R, lut_lds, mt, nb_lds, i, j, valid, cnt);
+    if (R.opaque) render_pixel<1, kVdi, true>(R, lut_lds, mt, nb_lds, own, i, j, valid, cnt);
+    else render_pixel<1, kVdi, false>(R, lut_lds, mt, nb_lds, own, i, j, valid, cnt);
   }
 }
 
@@ -1926,6 +1950,7 @@ __global__ __launch_bounds__(kBlock, kMode == 1 ? 2 : 1) void k_render(RenderArg
     tile = row * R.tiles_x + l % R.tiles_x;
     live = row * R.tiles_x < R.n_tiles;
   }
+  __shared__ uint32_t own_lds[kWave];   // one wave per workgroup
   __shared__ float4 lut_lds[256];
   extern __shared__ double dyn_lds[];
   const MergeLds merge_lds = merge_lds_view(dyn_lds);
@@ -1950,7 +1975,7 @@ __global__ __launch_bounds__(kBlock, kMode == 1 ? 2 : 1) void k_render(RenderArg
       tile_pixel(R, tile, threadIdx.x >> 6, lane, i, j);
     }
     double* nb_lds = dyn_lds + (kOpaque ? 0 : merge_lds_bytes(blockDim.x) / sizeof(double));
-    render_pixel<kMode, kVdi, kOpaque>(R, lut_lds, merge_lds, nb_lds, i, j, valid && i < R.W && j < R.H, cnt);
+    render_pixel<kMode, kVdi, kOpaque>(R, lut_lds, merge_lds, nb_lds, own_lds, i, j, valid && i < R.W && j < R.H, cnt);
   }
   if (kCount) flush_counts(R.counters, cnt);
   if (R.times && threadIdx.x == 0) {
@@ -1970,6 +1995,7 @@ __global__ __launch_bounds__(kBlock, kNb ? 2 : 1) void k_render_batch(const Rend
                                                          int32_t n_views, BatchQueues q,
                                                          unsigned* __restrict__ counters) {
   __shared__ int s_tile;
+  __shared__ uint32_t own_lds[kBlock];
   __shared__ float4 lut_lds[256];
   extern __shared__ double dyn_lds[];
   const MergeLds merge_lds = merge_lds_view(dyn_lds);
@@ -2019,7 +2045,8 @@ __global__ __launch_bounds__(kBlock, kNb ? 2 : 1) void k_render_batch(const Rend
     int i, j;
     tile_pixel(R, t - tile_start[v], threadIdx.x >> 6, threadIdx.x & 63, i, j);
     render_any<kVdi, kNb>(R, lut_lds, merge_lds,
-                          dyn_lds + merge_lds_bytes(blockDim.x) / sizeof(double), i, j, i < R.W && j < R.H, cnt);
+                          dyn_lds + merge_lds_bytes(blockDim.x) / sizeof(double),
+                          own_lds + (threadIdx.x & ~(kWave - 1)), i, j, i < R.W && j < R.H, cnt);
     __syncthreads();
   }
   if (kCount && counters) flush_counts(reinterpret_cast<RenderCounters*>(counters + kXcds), cnt);
