@@ -303,9 +303,10 @@ typedef struct {
  * slightly (eye within 2 % of the grid's diagonal, each camera vector within
  * 2 degrees and 1 % in length), its tiles start longest first by the times
  * of that earlier frame and the 32 longest are split four ways (eight ways
- * in frames that split no other tile). The library
+ * in frames that split no other tile, 16 ways in split mode 1 frames). The library
  * keeps, per (device, stream), the tile times of the stream's last 64 such
- * views (4 bytes per tile each) and one ordering buffer, until the process
+ * views (4 bytes per tile each), one ordering buffer and, after a mode 1
+ * frame, one buffer of 8 bytes per 4^3 voxels of its grid, until the process
  * ends; enlarging them synchronises the stream once. */
 int lineset_render(ls_lineset_t set, const ls_camera* cam, const ls_render_params* params,
                    float* rgba_out, void* hip_stream);

@@ -910,7 +910,8 @@ __device__ inline void local_origin(const Ray& ray, double t, const int32_t cell
 // length; testing each lane's own list leaves most lanes idle while the
 // longest list is tested. Instead the (ray, line) pairs of the whole wave are
 // numbered by a prefix sum over the list lengths and dealt out 64 at a time:
-// pair w belongs to the last lane r with P_r <= w (chunk_owner), and the tester reads r's ray frame by cross-lane reads.
+// pair w belongs to the last lane r with P_r <= w (chunk_owner), and the tester
+// reads r's ray frame by cross-lane reads.
 // Hits go back to their owners through a ballot: owner r pulls the hits of
 // the testers in its pair range one by one, so every owner sees the same set
 // of hits (and the same sorted buffer) as if it had tested its list itself.
@@ -2578,8 +2579,15 @@ int tile_order(const ls_lineset* s, const ls_camera* cam, const ls_render_params
 namespace {
 
 // Neighbour-mode frames: the grown occupancy of the set, formed anew for each
-// frame (the set may have changed) in the stream's buffer.
+// frame (the set may have changed) in the stream's buffer. Not under capture:
+// a graph may be replayed after the buffer was replaced, so there the kernel
+// forms the words itself.
 int grow_occupancy(RenderArgs& R, hipStream_t st) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return LS_OK;
+  }
   const int64_t nm = (int64_t)R.mg[0] * R.mg[1] * R.mg[2];
   int dev = 0, rc;
   LS_HIP(hipGetDevice(&dev));
