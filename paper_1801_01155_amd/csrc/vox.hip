@@ -20,9 +20,13 @@
 //   k_rank    thread per CSR slot: ranks the voxel's lines by emission order
 //             and gathers the record, so each list is in (curve, position
 //             along curve) order regardless of atomic order
+// Larger grids go by bricks of 8^3 voxels instead of by atomics and scattered
+// writes per line (see "Lists by bricks" below): a curve stays in a brick for
+// several lines, so what is counted, placed and read per brick are runs.
 // All arithmetic deciding a line's voxel, faces and bins is exact integer
 // arithmetic on the 1/256-voxel lattice.
 #include "ls_internal.h"
+#include "wave.h"
 
 #include <algorithm>
 #include <cmath>
@@ -361,14 +365,16 @@ __device__ inline uint32_t last_event(const int32_t P0[3], const int32_t P1[3],
   return cross;
 }
 
-// Brick-major index of voxel (x, y, z): bricks of 8^3 voxels, nbx bricks
-// along x and nbxy in a z layer of bricks; inside a brick x fastest. A curve's
-// consecutive voxels then share cache lines of a per-voxel array far more
-// often than in row-major order, where a step in z jumps a whole layer.
+// Brick index of voxel (x, y, z): brick << 9 | voxel in its brick (8^3 voxels, x
+// fastest). Bricks are numbered in blocks of 4 x 4 x 2 (x fastest), the blocks
+// row by row (nbx along x, nbxy in a layer): the bricks a curve visits in turn
+// then mostly share a 128-byte line of an array of words per brick, and
+// atomics of a wave that meet in one line travel as one request.
 __device__ inline uint32_t brick_index(uint32_t x, uint32_t y, uint32_t z, uint32_t nbx,
                                        uint32_t nbxy) {
-  return (((x >> 3) + nbx * (y >> 3) + nbxy * (z >> 3)) << 9) |
-         ((x & 7u) | (y & 7u) << 3 | (z & 7u) << 6);
+  return (((x >> 5) + nbx * (y >> 5) + nbxy * (z >> 4)) << 14) |
+         ((x & 7u) | (y & 7u) << 3 | (z & 7u) << 6 | (x >> 3 & 3u) << 9 | (y >> 3 & 3u) << 11 |
+          (z >> 3 & 1u) << 13);
 }
 
 // Segments with events wait in a per-wave ring in LDS until 64 of them
@@ -394,12 +400,14 @@ struct EmitRingAttr : EmitRing {
 // one event's entry point to the next event's exit point; it is dropped if
 // the two exact points or the two quantized endpoints coincide. The line
 // ending at an event goes to slot slot_off[c] + (plane crossings of the curve
-// before that event) - 1; slots no line takes keep the invalid mark written
-// before the launch. Each line takes its rank in its voxel with one atomic on
-// the histogram. With per-vertex attributes (kAttr) every event carries the
+// before that event) - 1; slots no line takes (dropped lines, and the extra
+// numbers of an event of several planes) get the invalid mark. kRank: each
+// line takes its rank in its voxel with one atomic on the histogram, and
+// vox_out is the row-major voxel; else vox_out is the voxel's brick index.
+// With per-vertex attributes (kAttr) every event carries the
 // attribute interpolated to it; a line writes its two endpoint attributes to
 // ends_out and their mean (rounded down) as its record's attribute byte.
-template <bool kFloatIn, bool kAttr>
+template <bool kFloatIn, bool kAttr, bool kRank>
 __global__ __launch_bounds__(kBlock, 4) void k_emit(const float* xyz, const int32_t* lat,
                                                  const int64_t* curve_off, const uint8_t* attr,
                                                  const uint8_t* vattr,
@@ -408,8 +416,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_emit(const float* xyz, const int3
                                                  GridArgs ga, const uint64_t* slot_off,
                                                  uint64_t* rec_out, uint16_t* ends_out,
                                                  uint32_t* vox_out, uint32_t* rank_out,
-                                                 uint32_t* hist, uint32_t hist_nbx,
-                                                 uint32_t hist_nbxy) {
+                                                 uint32_t* hist, uint32_t nbx,
+                                                 uint32_t nbxy) {
   using Ring = std::conditional_t<kAttr, EmitRingAttr, EmitRing>;
   __shared__ Ring rings[kWavesPerBlock];
   const int lane = threadIdx.x & 63;
@@ -444,8 +452,10 @@ __global__ __launch_bounds__(kBlock, 4) void k_emit(const float* xyz, const int3
     uint32_t prev_attr = va >> 16;
     for_each_event<true>(P0, P1, ga, [&](const Ev& ev, const int32_t* cell) {
       const uint32_t ea = kAttr ? event_attr(va & 0xFFu, (va >> 8) & 0xFFu, ev.nf, ev.den) : 0u;
+      const uint64_t w = w0 + (g - 1);
+      for (int k = 1; k < ev.planes; ++k)
+        if (w + k < w_end) vox_out[w + k] = LS_INVALID_VOXEL;
       if (has_prev) {
-        const uint64_t w = w0 + (g - 1);
         if (w < w_end) {
           // events of one segment have distinct parameters, so only its
           // first event can coincide with the event before it
@@ -458,18 +468,22 @@ __global__ __launch_bounds__(kBlock, 4) void k_emit(const float* xyz, const int3
             same = bx0 * ev.den == xn[0] * bden && bx1 * ev.den == xn[1] * bden &&
                    bx2 * ev.den == xn[2] * bden;
           }
-          if (!same && prev_entry != ev.exit_code) {
-            const uint32_t vid = (uint32_t)(cell[0] + gx * cell[1] + gxy * cell[2]);
+          if (same || prev_entry == ev.exit_code) {
+            vox_out[w] = LS_INVALID_VOXEL;
+          } else {
             uint64_t hb = hi_bits;
             if (kAttr) {
               hb = (hb & ~(0xFFull << 32)) | ((uint64_t)((prev_attr + ea) >> 1) << 32);
               ends_out[w] = (uint16_t)(prev_attr | (ea << 8));
             }
             rec_out[w] = (uint64_t)prev_entry | ((uint64_t)ev.exit_code << 15) | hb;
-            vox_out[w] = vid;
-            const uint32_t hv =
-                hist_nbx ? brick_index(cell[0], cell[1], cell[2], hist_nbx, hist_nbxy) : vid;
-            rank_out[w] = atomicAdd(hist + hv, 1u);
+            if (kRank) {
+              const uint32_t vid = (uint32_t)(cell[0] + gx * cell[1] + gxy * cell[2]);
+              vox_out[w] = vid;
+              rank_out[w] = atomicAdd(hist + vid, 1u);
+            } else {
+              vox_out[w] = brick_index(cell[0], cell[1], cell[2], nbx, nbxy);
+            }
           }
         }
       }
@@ -564,36 +578,6 @@ __global__ __launch_bounds__(kBlock) void k_scatter(const uint32_t* vox, const u
   uint32_t v = vox[e];
   if (v == LS_INVALID_VOXEL) return;
   idx[offsets[v] + rank[e]] = ((uint64_t)v << 32) | (uint32_t)e;
-}
-
-struct BrickGrid {
-  int32_t g[3];          // voxel grid (row-major ids)
-  uint32_t nbx, nbxy;    // brick grid (brick_index)
-};
-
-// Brick-major -> row-major copy of a per-voxel array. A workgroup moves 8
-// bricks consecutive along x (4096 words, one contiguous read) through LDS
-// and writes their 64 rows of up to 64 voxels (contiguous writes); grid
-// (ceil(nbx / 8), bricks along y, bricks along z).
-constexpr int kRunBricks = 8;
-
-__global__ __launch_bounds__(kBlock) void k_from_bricks(const uint32_t* brick, BrickGrid bg,
-                                                        uint32_t* rows) {
-  __shared__ uint32_t s_b[kRunBricks * 513];   // one padding word per brick: no bank conflicts
-  const uint32_t bx0 = blockIdx.x * kRunBricks, by = blockIdx.y, bz = blockIdx.z;
-  const uint32_t nb = bg.nbx - bx0 < (uint32_t)kRunBricks ? bg.nbx - bx0 : kRunBricks;
-  const uint32_t* src = brick + ((size_t)(bx0 + bg.nbx * by + bg.nbxy * bz) << 9);
-  for (uint32_t i = threadIdx.x; i < nb * 512; i += kBlock) s_b[(i >> 9) * 513 + (i & 511)] = src[i];
-  __syncthreads();
-  const int32_t x0 = 8 * (int32_t)bx0;
-#pragma unroll 4
-  for (int i = threadIdx.x; i < 64 * 64; i += kBlock) {
-    const int xx = i & 63, row = i >> 6;
-    const int32_t x = x0 + xx, y = 8 * (int32_t)by + (row & 7), z = 8 * (int32_t)bz + (row >> 3);
-    if (x < bg.g[0] && y < bg.g[1] && z < bg.g[2])
-      rows[x + (int64_t)bg.g[0] * (y + (int64_t)bg.g[1] * z)] =
-          s_b[(xx >> 3) * 513 + ((xx & 7) | (row & 7) << 3 | (row >> 3) << 6)];
-  }
 }
 
 // Each CSR slot p holds some emitted line e of voxel v; its final position is
@@ -712,6 +696,435 @@ __global__ __launch_bounds__(kBlock) void k_occupancy(const uint32_t* offsets, G
 }
 
 
+// ---------------------------------------------------------------------------
+// Lists by bricks. The emitted lines lie in slot order (curve by curve), and
+// consecutive slots of a curve mostly share a brick of 8^3 voxels. A run is a
+// maximal sequence of consecutive slots of one brick within 64 slots.
+//   k_runs<false>  counts runs per brick (one atomic per run), in kReps copies
+//                  of the counters: workgroup b counts in copy b mod kReps, so
+//                  a busy brick's counter is not one address for the chip
+//   scan           run offsets, copy by copy
+//   k_runs<true>   writes each run (first slot, length) to its brick's list,
+//                  one list per copy
+//   k_brick_count  workgroup per 4 bricks along x: voxel histogram in LDS,
+//                  written to the offsets array (counts), with the occupancy
+//                  words and list statistics of its macro cells; lists the
+//                  bricks too large for k_brick_fill as (brick, voxel range)
+//   scan           voxel offsets (CSR)
+//   k_brick_fill   workgroup per brick (k_brick_items: per listed range):
+//                  places the slots of its lines by voxel in LDS, ranks each
+//                  voxel's slots and gathers the records into the CSR, whose
+//                  rows of 8 voxels it fills by itself
+// One atomic and one scattered write per run (11 lines at 512^3) replace, per
+// line, the rank atomic, the scattered 8-byte pair, its reading back and the
+// scattered gather. The fills are bound by the latency of a brick's serial
+// stages (offsets, runs, slots, records), so each keeps kAhead loads per lane
+// in flight; the figures stand at kBrickMinVoxels.
+constexpr int kRunShift = 9;                 // see brick_index
+constexpr uint32_t kBrickVox = 1u << kRunShift;
+
+struct BrickGrid {
+  int32_t g[3];          // voxel grid (row-major ids)
+  int32_t m[3];          // macro-cell grid (4^3 voxels)
+  uint32_t nk[3];        // blocks of 4 x 4 x 2 bricks
+  uint32_t n;            // bricks, those of partial blocks included
+  // coordinates of brick b
+  __device__ inline void brick(uint32_t b, uint32_t c[3]) const {
+    const uint32_t k = b >> 5;
+    c[0] = 4 * (k % nk[0]) + (b & 3u);
+    c[1] = 4 * ((k / nk[0]) % nk[1]) + (b >> 2 & 3u);
+    c[2] = 2 * (k / (nk[0] * nk[1])) + (b >> 4 & 1u);
+  }
+};
+
+constexpr uint32_t kReps = 32;   // a power of two, at most 64
+
+template <bool kPlace>
+__global__ __launch_bounds__(kBlock) void k_runs(const uint32_t* __restrict__ vox, int64_t n_slots,
+                                                 uint32_t n_bricks, uint32_t* brick,
+                                                 uint32_t* cursor, unsigned long long* runs) {
+  const int lane = threadIdx.x & 63;
+  const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  const uint32_t v = e < n_slots ? vox[e] : LS_INVALID_VOXEL;
+  const bool ok = v != LS_INVALID_VOXEL;
+  const uint32_t b = ok ? v >> kRunShift : LS_INVALID_VOXEL;
+  const uint32_t p = __shfl_up(b, 1, 64);
+  const bool start = ok && (lane == 0 || p != b);
+  // a run ends before the next start or the next invalid slot
+  const unsigned long long stop = __ballot(start || !ok);
+  if (!start) return;
+  const unsigned long long rest = lane < 63 ? stop >> (lane + 1) : 0ull;
+  const uint32_t len = rest ? (uint32_t)__builtin_ctzll(rest) + 1u : 64u - (uint32_t)lane;
+  const size_t c = (size_t)(blockIdx.x % kReps) * n_bricks + b;
+  if (kPlace) {
+    const uint32_t pos = brick[c] + atomicAdd(cursor + c, 1u);
+    runs[pos] = (unsigned long long)len << 32 | (uint32_t)e;
+  } else {
+    atomicAdd(brick + c, 1u);
+  }
+}
+
+// Lines of a brick that k_brick_fill places in LDS (18 KB with the voxel
+// tables: 8 workgroups per CU), and that one listed range may hold.
+constexpr uint32_t kFillCap = 2048;
+constexpr uint32_t kItemCap = 8192;
+constexpr int kGroupBricks = 4;      // bricks per k_brick_count workgroup, along x
+constexpr int kCountThreads = 512;
+constexpr int kItemThreads = 1024;
+
+// A range [v0, v1) of the voxels of a brick.
+struct BrickItem {
+  uint32_t brick;
+  uint16_t v0, v1;
+};
+
+// The run lists of bricks [b, b + nb) (consecutive): one segment of
+// `runs` per copy of the counters.
+struct RunLists {
+  uint32_t pre[kReps + 1];   // runs before each segment
+  uint32_t at[kReps];        // the segment's first run
+};
+
+// Filled by the workgroup's first threads; a barrier follows in the caller.
+__device__ inline void run_lists(const uint32_t* __restrict__ brick, uint32_t n_bricks, uint32_t b,
+                                 uint32_t nb, RunLists& L) {
+  if (threadIdx.x < 64) {
+    const uint32_t k = threadIdx.x;
+    const uint32_t lo = k < kReps ? brick[(size_t)k * n_bricks + b] : 0u;
+    const uint32_t hi = k < kReps ? brick[(size_t)k * n_bricks + b + nb] : 0u;
+    const uint32_t inc = wave_incl_sum(hi - lo);
+    if (k < kReps) {
+      L.pre[k + 1] = inc;
+      L.at[k] = lo;
+    }
+    if (k == 0) L.pre[0] = 0u;
+  }
+}
+
+// Visits the lines of L's runs: f(slot, brick index of its voxel). A wave
+// takes up to 64 runs at a time, numbers their lines by a prefix sum and deals
+// them to its lanes, kAhead x 64 lines' loads in flight. own: 64 words of LDS
+// for this wave.
+constexpr int kAhead = 4;
+
+template <int kThreads, typename F>
+__device__ inline void for_each_line(const unsigned long long* __restrict__ runs,
+                                     const RunLists& L, const uint32_t* __restrict__ vox,
+                                     uint32_t* own, F&& f) {
+  constexpr uint32_t kWaves = kThreads / 64;
+  const uint32_t lane = (uint32_t)wave_lane();
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.pre[kReps]);
+  const uint32_t take = min(64u, (n + kWaves - 1) / kWaves);
+  for (uint32_t r0 = wave * take; r0 < n; r0 += kWaves * take) {
+    unsigned long long run = 0;
+    if (lane < take && r0 + lane < n) {
+      const uint32_t r = r0 + lane;
+      uint32_t k = 0;   // last segment with pre <= r
+#pragma unroll
+      for (uint32_t j = kReps / 2; j >= 1; j >>= 1)
+        if (L.pre[k + j] <= r) k += j;
+      run = runs[L.at[k] + (r - L.pre[k])];
+    }
+    const uint32_t len = (uint32_t)(run >> 32);
+    uint32_t total;
+    const uint32_t P = wave_excl_scan(len, total);
+    const uint32_t rel = (uint32_t)run - P;   // slot of line w: w + rel of its run
+    for (uint32_t base = 0; base < total; base += 64 * kAhead) {
+      uint32_t e[kAhead], v[kAhead];
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j) {
+        const uint32_t w0 = base + 64 * j;
+        e[j] = v[j] = LS_INVALID_VOXEL;
+        if (w0 < total) {   // wave-uniform
+          const int o = chunk_owner(own, P, len, w0);
+          const uint32_t s = w0 + lane + (uint32_t)__shfl((int)rel, o, 64);
+          if (w0 + lane < total) {
+            e[j] = s;
+            v[j] = vox[s];
+          }
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j)
+        if (v[j] != LS_INVALID_VOXEL) f(e[j], v[j]);
+    }
+  }
+}
+
+__global__ __launch_bounds__(kCountThreads) void k_brick_count(
+    const uint32_t* __restrict__ brick, const unsigned long long* __restrict__ runs,
+    const uint32_t* __restrict__ vox, BrickGrid bg, uint32_t* counts, unsigned long long* occ,
+    unsigned long long* part, uint32_t* n_items, BrickItem* items) {
+  __shared__ uint32_t hist[kGroupBricks * kBrickVox];
+  __shared__ uint32_t s_ne, s_mx, own[kCountThreads], s_lines[kGroupBricks];
+  __shared__ RunLists lists;
+  const uint32_t b0 = blockIdx.x * kGroupBricks;
+  constexpr uint32_t nb = kGroupBricks;
+  uint32_t bc[3];
+  bg.brick(b0, bc);
+  const uint32_t bx0 = bc[0], by = bc[1], bz = bc[2];
+  if (8 * bx0 >= (uint32_t)bg.g[0] || 8 * by >= (uint32_t)bg.g[1] || 8 * bz >= (uint32_t)bg.g[2]) {
+    if (threadIdx.x == 0) part[blockIdx.x] = 0ull;
+    return;   // a partial block's bricks outside the grid
+  }
+  for (uint32_t i = threadIdx.x; i < kGroupBricks * kBrickVox; i += kCountThreads) hist[i] = 0u;
+  if (threadIdx.x == 0) s_ne = s_mx = 0u;
+  if (threadIdx.x < kGroupBricks) s_lines[threadIdx.x] = 0u;
+  run_lists(brick, bg.n, b0, nb, lists);
+  __syncthreads();
+  const uint32_t base = b0 << kRunShift;
+  for_each_line<kCountThreads>(runs, lists, vox, own + (threadIdx.x & ~63u),
+                               [&](uint32_t, uint32_t v) { atomicAdd(hist + (v - base), 1u); });
+  __syncthreads();
+  // counts, in rows of up to 32 voxels
+  for (uint32_t i = threadIdx.x; i < kGroupBricks * kBrickVox; i += kCountThreads) {
+    const uint32_t xx = i & 31u, row = i >> 5, y = 8 * by + (row & 7u), z = 8 * bz + (row >> 3);
+    const uint32_t x = 8 * bx0 + xx;
+    if (x < (uint32_t)bg.g[0] && y < (uint32_t)bg.g[1] && z < (uint32_t)bg.g[2])
+      counts[x + (int64_t)bg.g[0] * (y + (int64_t)bg.g[1] * z)] =
+          hist[(xx >> 3) << kRunShift | (xx & 7u) | row << 3];
+  }
+  // a wave per macro cell: lane = voxel, the ballot is its occupancy word
+  const uint32_t lane = threadIdx.x & 63u;
+  uint32_t ne = 0, mx = 0;
+  for (uint32_t q = threadIdx.x >> 6; q < 8 * nb; q += kCountThreads / 64) {
+    const uint32_t lx = (lane & 3u) | (q & 1u) << 2, ly = (lane >> 2 & 3u) | (q & 2u) << 1,
+                   lz = (lane >> 4) | (q & 4u);
+    const uint32_t n = hist[(q >> 3) << kRunShift | lx | ly << 3 | lz << 6];
+    const unsigned long long w = __ballot(n != 0u);
+    const uint32_t cx = 2 * (bx0 + (q >> 3)) + (q & 1u), cy = 2 * by + (q >> 1 & 1u),
+                   cz = 2 * bz + (q >> 2 & 1u);
+    if (lane == 0 && cx < (uint32_t)bg.m[0] && cy < (uint32_t)bg.m[1] && cz < (uint32_t)bg.m[2])
+      occ[cx + (int64_t)bg.m[0] * (cy + (int64_t)bg.m[1] * cz)] = w;
+    ne += (uint32_t)__popcll(w);
+    mx = max(mx, n);
+    const uint32_t lines = wave_incl_sum(n);
+    if (lane == 63 && lines) atomicAdd(s_lines + (q >> 3), lines);
+  }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) mx = max(mx, (uint32_t)__shfl_xor(mx, d, 64));
+  if (lane == 0 && ne) {
+    atomicAdd(&s_ne, ne);
+    atomicMax(&s_mx, mx);
+  }
+  __syncthreads();
+  // bricks beyond k_brick_fill's room, cut into voxel ranges of at most
+  // kItemCap lines (or one voxel)
+  if (threadIdx.x < nb) {
+    const uint32_t b = b0 + threadIdx.x, n = s_lines[threadIdx.x];
+    if (n > kFillCap && n <= kItemCap) {
+      items[atomicAdd(n_items, 1u)] = BrickItem{b, 0, (uint16_t)kBrickVox};
+    } else if (n > kItemCap) {
+      const uint32_t* h = hist + threadIdx.x * kBrickVox;
+      uint32_t v0 = 0, sum = 0;
+      for (uint32_t v = 0; v <= kBrickVox; ++v) {
+        const uint32_t c = v < kBrickVox ? h[v] : 0u;
+        if (v == kBrickVox || (sum + c > kItemCap && v > v0)) {
+          if (sum > 0) items[atomicAdd(n_items, 1u)] = BrickItem{b, (uint16_t)v0, (uint16_t)v};
+          v0 = v;
+          sum = 0;
+        }
+        sum += c;
+      }
+    }
+  }
+  if (threadIdx.x == 0)
+    part[blockIdx.x] = (unsigned long long)s_mx << 32 | s_ne;
+}
+
+// What the host reads once the lists are counted.
+struct ListHeader {
+  unsigned long long nonempty, max_list;
+  uint32_t n_records, n_items;
+};
+
+// Sums k_brick_count's list statistics (non-empty voxels, longest list; the two
+// words after the occupancy words) and gathers the header.
+__global__ __launch_bounds__(1024) void k_list_stats(const unsigned long long* __restrict__ part,
+                                                     int64_t n, const uint32_t* n_records,
+                                                     const uint32_t* n_items,
+                                                     unsigned long long* stats, ListHeader* out) {
+  __shared__ unsigned long long s_ne;
+  __shared__ unsigned s_mx;
+  if (threadIdx.x == 0) {
+    s_ne = 0ull;
+    s_mx = 0u;
+  }
+  __syncthreads();
+  unsigned long long ne = 0;
+  unsigned mx = 0;
+  for (int64_t i = threadIdx.x; i < n; i += 1024) {
+    const unsigned long long p = part[i];
+    ne += (uint32_t)p;
+    mx = max(mx, (unsigned)(p >> 32));
+  }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) {
+    ne += __shfl_xor(ne, d, 64);
+    mx = max(mx, (unsigned)__shfl_xor(mx, d, 64));
+  }
+  if ((threadIdx.x & 63) == 0) {
+    atomicAdd(&s_ne, ne);
+    atomicMax(&s_mx, mx);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    stats[0] = s_ne;
+    stats[1] = s_mx;
+    *out = ListHeader{s_ne, s_mx, *n_records, *n_items};
+  }
+}
+
+// The lines of voxels [v0, v1) of brick b, at most kCap: slots placed by
+// voxel in LDS, ranked within the voxel by slot (= emission order), records
+// gathered into the CSR. lds: kCap slots, kCap voxels (16 bit).
+template <int kThreads, uint32_t kCap>
+__device__ inline void brick_fill(const unsigned long long* __restrict__ runs,
+                                  const uint32_t* __restrict__ vox,
+                                  const uint64_t* __restrict__ rec,
+                                  const uint16_t* __restrict__ ends_in, const BrickGrid& bg,
+                                  const uint32_t* __restrict__ offsets, uint32_t b, uint32_t v0,
+                                  uint32_t v1, uint32_t* s_e, uint16_t* s_v, uint32_t* s_off,
+                                  uint32_t* s_lo, uint32_t* s_cur, uint32_t* own,
+                                  RunLists& lists, uint64_t* __restrict__ records,
+                                  uint16_t* __restrict__ ends) {
+  static_assert(kThreads >= 64 && kBrickVox % 64 == 0, "scan by one wave");
+  uint32_t bc[3];
+  bg.brick(b, bc);
+  for (uint32_t i = threadIdx.x; i < kBrickVox; i += kThreads) {
+    const uint32_t x = 8 * bc[0] + (i & 7u), y = 8 * bc[1] + (i >> 3 & 7u), z = 8 * bc[2] + (i >> 6);
+    uint32_t lo = 0, n = 0;
+    if (i >= v0 && i < v1 && x < (uint32_t)bg.g[0] && y < (uint32_t)bg.g[1] &&
+        z < (uint32_t)bg.g[2]) {
+      const int64_t v = x + (int64_t)bg.g[0] * (y + (int64_t)bg.g[1] * z);
+      lo = offsets[v];
+      n = offsets[v + 1] - lo;
+    }
+    s_off[i] = lo;
+    s_lo[i] = n;
+    s_cur[i] = 0u;
+  }
+  __syncthreads();
+  // exclusive scan of the counts: the first wave, 8 voxels per lane
+  if (threadIdx.x < 64) {
+    constexpr int kPer = kBrickVox / 64;
+    uint32_t c[kPer], sum = 0, total;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      c[k] = s_lo[threadIdx.x * kPer + k];
+      sum += c[k];
+    }
+    uint32_t pre = wave_excl_scan(sum, total);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      s_lo[threadIdx.x * kPer + k] = pre;
+      pre += c[k];
+    }
+    if (threadIdx.x == 0) s_lo[kBrickVox] = total;
+  }
+  __syncthreads();
+  const uint32_t n = s_lo[kBrickVox];
+  if (n > kCap) return;   // a listed brick
+  for_each_line<kThreads>(runs, lists, vox, own, [&](uint32_t e, uint32_t bv) {
+    const uint32_t v = bv & (kBrickVox - 1);
+    if (v < v0 || v >= v1) return;
+    const uint32_t p = s_lo[v] + atomicAdd(s_cur + v, 1u);
+    s_e[p] = e;
+    s_v[p] = (uint16_t)v;
+  });
+  __syncthreads();
+  // kAhead lines per thread: their ranks, then their loads, then their writes
+  for (uint32_t p0 = threadIdx.x; p0 < n; p0 += kAhead * kThreads) {
+    uint32_t e[kAhead], w[kAhead];
+    uint64_t r[kAhead];
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      const uint32_t p = p0 + j * kThreads;
+      if (p < n) {
+        const uint32_t v = s_v[p], hi = s_lo[v + 1];
+        e[j] = s_e[p];
+        w[j] = s_off[v];
+        r[j] = rec[e[j]];
+        for (uint32_t q = s_lo[v]; q < hi; ++q) w[j] += s_e[q] < e[j];
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      if (p0 + j * kThreads < n) {
+        records[w[j]] = r[j];
+        if (ends) ends[w[j]] = ends_in[e[j]];
+      }
+    }
+  }
+}
+
+// Bricks of up to kFillCap lines, a workgroup each; XCD x (= block mod 8) takes
+// a contiguous run of bricks, so the rows that neighbouring bricks fill meet in
+// one L2.
+__global__ __launch_bounds__(kBlock) void k_brick_fill(
+    const uint32_t* __restrict__ brick, const unsigned long long* __restrict__ runs,
+    const uint32_t* __restrict__ vox, const uint64_t* __restrict__ rec,
+    const uint16_t* __restrict__ ends_in, BrickGrid bg, const uint32_t* __restrict__ offsets,
+    uint64_t* records, uint16_t* ends) {
+  __shared__ uint32_t s_e[kFillCap], s_off[kBrickVox], s_lo[kBrickVox + 1], s_cur[kBrickVox];
+  __shared__ uint16_t s_v[kFillCap];
+  __shared__ uint32_t own[kBlock];
+  __shared__ RunLists lists;
+  const uint32_t per = (bg.n + 7u) / 8u, b = (blockIdx.x & 7u) * per + (blockIdx.x >> 3);
+  if ((blockIdx.x >> 3) >= per || b >= bg.n) return;
+  run_lists(brick, bg.n, b, 1u, lists);
+  __syncthreads();
+  if (lists.pre[kReps] == 0u) return;
+  brick_fill<kBlock, kFillCap>(runs, vox, rec, ends_in, bg, offsets, b, 0u, kBrickVox, s_e, s_v,
+                               s_off, s_lo, s_cur, own + (threadIdx.x & ~63u), lists, records,
+                               ends);
+}
+
+// The listed voxel ranges of larger bricks, dealt over the grid. (A voxel of
+// more than kItemCap lines is not reached: vox_build takes the other path.)
+constexpr size_t kItemLds = kItemCap * (sizeof(uint32_t) + sizeof(uint16_t));
+
+__global__ __launch_bounds__(kItemThreads) void k_brick_items(
+    const uint32_t* __restrict__ brick, const unsigned long long* __restrict__ runs,
+    const uint32_t* __restrict__ vox, const uint64_t* __restrict__ rec,
+    const uint16_t* __restrict__ ends_in, BrickGrid bg, const uint32_t* __restrict__ offsets,
+    const uint32_t* __restrict__ n_items, const BrickItem* __restrict__ items, uint64_t* records,
+    uint16_t* ends) {
+  extern __shared__ uint32_t item_lds[];
+  __shared__ uint32_t s_off[kBrickVox], s_lo[kBrickVox + 1], s_cur[kBrickVox];
+  __shared__ uint32_t own[kItemThreads];
+  __shared__ RunLists lists;
+  uint16_t* s_v = reinterpret_cast<uint16_t*>(item_lds + kItemCap);
+  const uint32_t n = *n_items;
+  for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
+    const BrickItem it = items[i];
+    run_lists(brick, bg.n, it.brick, 1u, lists);
+    brick_fill<kItemThreads, kItemCap>(runs, vox, rec, ends_in, bg, offsets, it.brick, it.v0,
+                                       it.v1, item_lds, s_v, s_off, s_lo, s_cur,
+                                       own + (threadIdx.x & ~63u), lists, records, ends);
+    __syncthreads();
+  }
+}
+
+// Slots given by brick index turned into row-major voxels, with a rank from a
+// per-voxel counter (what k_emit<kRank> writes): the way back to k_scatter and
+// k_rank for sets with a voxel of more than kItemCap lines.
+__global__ __launch_bounds__(kBlock) void k_unbrick(uint32_t* vox, int64_t n_slots, BrickGrid bg,
+                                                    uint32_t* count, uint32_t* rank) {
+  const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (e >= n_slots) return;
+  const uint32_t bv = vox[e];
+  if (bv == LS_INVALID_VOXEL) return;
+  const uint32_t i = bv & (kBrickVox - 1);
+  uint32_t bc[3];
+  bg.brick(bv >> kRunShift, bc);
+  const uint32_t x = 8 * bc[0] + (i & 7u), y = 8 * bc[1] + (i >> 3 & 7u), z = 8 * bc[2] + (i >> 6);
+  const uint32_t v = (uint32_t)(x + (int64_t)bg.g[0] * (y + (int64_t)bg.g[1] * z));
+  vox[e] = v;
+  rank[e] = atomicAdd(count + v, 1u);
+}
+
 // Per-block bounds of the vertices (min and max are exact in fp32; widened
 // to fp64 for the set-up). kVec: xyz 16-byte aligned, read as three float4
 // per 4 vertices.
@@ -819,10 +1232,21 @@ __global__ __launch_bounds__(kBlock) void k_snap(const float* xyz, int64_t nv, S
 
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
-// Grids from this many voxels count lines in brick-major order: their 4-byte
-// per-voxel array (128 MiB and up) no longer sits comfortably in the 256 MB
-// last-level cache, so the emit's row-major atomics would go to HBM at random.
-constexpr int64_t kBrickMinVoxels = int64_t(1) << 25;
+// Lists are formed by bricks from this many voxels and line slots on, and up to
+// this many slots per brick on average; else by one rank atomic per line in
+// k_emit, k_scatter and k_rank. Below 2^22 lines the atomics cost less than the
+// brick passes' launches (201x97x130, 70k lines: 128 us of kernels against
+// 165); small grids of long lists have too few bricks for the chip. Measured at
+// 256^3, 9.5M lines (100k x 200 curves): 1169 -> 1080 us for the whole call; at
+// 512^3, 140.6M lines (1M x 100): 14.63 -> 8.23 ms, of it the emission 4.66 ->
+// 2.77 ms without the rank atomics, and scatter + rank + occupancy + histogram
+// copy 7.96 -> 3.45 ms as runs (0.50 + 0.75), counts 0.55, fills 0.51 + 1.16.
+// Run atomics are bound by requests per 128-byte line: one copy of the counters
+// in plain brick order took 1.0 + 1.2 ms at 512^3 and 0.13 + 0.15 ms at 256^3,
+// 4 x 4 x 2 blocks and 32 copies take 0.50 + 0.75 and 0.04 + 0.04.
+constexpr int64_t kBrickMinVoxels = int64_t(1) << 20;
+constexpr int64_t kBrickMinSlots = int64_t(1) << 22;
+constexpr int64_t kBrickMaxMean = 2048;
 inline unsigned curve_blocks(int64_t n) {
   return (unsigned)((n + kWavesPerBlock - 1) / kWavesPerBlock);
 }
@@ -897,6 +1321,13 @@ int vox_snap(const float* xyz, int64_t nv, SnapArgs sa, int32_t* lat, hipStream_
   hipLaunchKernelGGL(k_snap, dim3(blocks_for(3 * nv)), dim3(kBlock), 0, st, xyz, nv, sa, lat);
   LS_HIP(hipGetLastError());
   return LS_OK;
+}
+
+// The macro grid and its occupancy words (with the two statistics words).
+static int occupancy_alloc(ls_lineset* s) {
+  for (int a = 0; a < 3; ++a) s->macro[a] = (s->grid[a] + 3) / 4;
+  const int64_t nm = (int64_t)s->macro[0] * s->macro[1] * s->macro[2];
+  return ls_alloc(s, (void**)&s->occupancy, sizeof(uint64_t) * (nm + 2));
 }
 
 int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t* curve_off,
@@ -987,96 +1418,160 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
   }
   s->n_slots = (int64_t)n_slots;
 
-  // 2. offsets array (owned by the set) doubles as the histogram; on grids
-  // whose per-voxel array outgrows the last-level cache the lines are counted
-  // in a brick-major array instead (the emit's atomics then follow a curve
-  // through nearby cache lines), copied to row-major order before the scan
+  // 2. offsets array (owned by the set) and the way its lists are formed
   if ((rc = ls_alloc(s, (void**)&s->offsets, sizeof(uint32_t) * (s->nvox + 1)))) return rc;
-  const bool bricks = s->nvox >= kBrickMinVoxels;
   BrickGrid bg{};
-  for (int a = 0; a < 3; ++a) bg.g[a] = s->grid[a];
-  DeviceBuf hist_b(st);
-  if (bricks) {
-    bg.nbx = (uint32_t)(s->grid[0] + 7) / 8;
-    bg.nbxy = bg.nbx * (uint32_t)((s->grid[1] + 7) / 8);
-    const int64_t nb = (int64_t)bg.nbxy * ((s->grid[2] + 7) / 8) * 512;
-    if ((rc = hist_b.alloc(sizeof(uint32_t) * nb))) return rc;
-    if ((rc = fill_u32(hist_b.as<uint32_t>(), 0u, nb, st))) return rc;
-  } else if ((rc = fill_u32(s->offsets, 0u, s->nvox + 1, st))) {
-    return rc;
+  for (int a = 0; a < 3; ++a) {
+    bg.g[a] = s->grid[a];
+    bg.m[a] = (s->grid[a] + 3) / 4;
+    bg.nk[a] = (uint32_t)(s->grid[a] + (a < 2 ? 31 : 15)) / (a < 2 ? 32 : 16);
   }
-  uint32_t* hist = bricks ? hist_b.as<uint32_t>() : s->offsets;
+  bg.n = 32 * bg.nk[0] * bg.nk[1] * bg.nk[2];
+  const bool bricks = s->nvox >= kBrickMinVoxels && (int64_t)n_slots >= kBrickMinSlots &&
+                      (int64_t)n_slots <= kBrickMaxMean * bg.n;
 
   // 3. emit
   DeviceBuf rec(st), vox(st), rank(st), sums32(st), ends_slots(st);
   if ((rc = rec.alloc(sizeof(uint64_t) * n_slots)) || (rc = vox.alloc(sizeof(uint32_t) * n_slots)) ||
-      (rc = rank.alloc(sizeof(uint32_t) * n_slots)) ||
       (rc = sums32.alloc(sizeof(uint32_t) * scan_block_sums_len(s->nvox))))
     return rc;
+  if (!bricks) {
+    // the offsets array doubles as the histogram
+    if ((rc = rank.alloc(sizeof(uint32_t) * n_slots)) ||
+        (rc = fill_u32(s->offsets, 0u, s->nvox + 1, st)))
+      return rc;
+  }
   if (vattr && (rc = ends_slots.alloc(sizeof(uint16_t) * (n_slots ? n_slots : 1)))) return rc;
-  if ((rc = fill_u32(vox.as<uint32_t>(), LS_INVALID_VOXEL, (int64_t)n_slots, st))) return rc;
+  uint16_t* eo = vattr ? ends_slots.as<uint16_t>() : nullptr;
   if (C > 0) {
-    const dim3 grid(curve_blocks(C)), block(kBlock);
-    uint16_t* eo = vattr ? ends_slots.as<uint16_t>() : nullptr;
-    if (float_in && vattr)
-      hipLaunchKernelGGL((k_emit<true, true>), grid, block, 0, st, xyz, lat, curve_off, attr,
-                         vattr, C, s->curve_base, sad, ga, slots.as<uint64_t>(),
-                         rec.as<uint64_t>(), eo, vox.as<uint32_t>(), rank.as<uint32_t>(),
-                         hist, bg.nbx, bg.nbxy);
-    else if (float_in)
-      hipLaunchKernelGGL((k_emit<true, false>), grid, block, 0, st, xyz, lat, curve_off, attr,
-                         vattr, C, s->curve_base, sad, ga, slots.as<uint64_t>(),
-                         rec.as<uint64_t>(), eo, vox.as<uint32_t>(), rank.as<uint32_t>(),
-                         hist, bg.nbx, bg.nbxy);
-    else if (vattr)
-      hipLaunchKernelGGL((k_emit<false, true>), grid, block, 0, st, xyz, lat, curve_off, attr,
-                         vattr, C, s->curve_base, sad, ga, slots.as<uint64_t>(),
-                         rec.as<uint64_t>(), eo, vox.as<uint32_t>(), rank.as<uint32_t>(),
-                         hist, bg.nbx, bg.nbxy);
-    else
-      hipLaunchKernelGGL((k_emit<false, false>), grid, block, 0, st, xyz, lat, curve_off, attr,
-                         vattr, C, s->curve_base, sad, ga, slots.as<uint64_t>(),
-                         rec.as<uint64_t>(), eo, vox.as<uint32_t>(), rank.as<uint32_t>(),
-                         hist, bg.nbx, bg.nbxy);
+    using Emit = decltype(&k_emit<true, true, true>);
+    static const Emit kernels[2][2][2] = {
+        {{k_emit<false, false, false>, k_emit<false, false, true>},
+         {k_emit<false, true, false>, k_emit<false, true, true>}},
+        {{k_emit<true, false, false>, k_emit<true, false, true>},
+         {k_emit<true, true, false>, k_emit<true, true, true>}}};
+    hipLaunchKernelGGL(kernels[float_in][vattr != nullptr][!bricks], dim3(curve_blocks(C)),
+                       dim3(kBlock), 0, st, xyz, lat, curve_off, attr, vattr, C, s->curve_base, sad,
+                       ga, slots.as<uint64_t>(), rec.as<uint64_t>(), eo, vox.as<uint32_t>(),
+                       rank.as<uint32_t>(), s->offsets, bg.nk[0], bg.nk[0] * bg.nk[1]);
     LS_HIP(hipGetLastError());
   }
 
   // 4. counts -> offsets (in place)
+  DeviceBuf brick(st), runs(st), items(st), part(st), sums_b(st);
+  int64_t n_groups = 0;
+  const size_t item_max = 3 * (size_t)(n_slots / kFillCap) + 1;
+  uint32_t* n_items = nullptr;
+  uint32_t* cursor = nullptr;
   if (bricks) {
-    const dim3 grid((bg.nbx + kRunBricks - 1) / kRunBricks, (s->grid[1] + 7) / 8,
-                    (s->grid[2] + 7) / 8);
-    hipLaunchKernelGGL(k_from_bricks, grid, dim3(kBlock), 0, st, hist_b.as<uint32_t>(), bg,
-                       s->offsets);
+    // run counts (kReps copies, one past the last), run cursors, item count
+    n_groups = bg.n / kGroupBricks;
+    const int64_t nc = (int64_t)kReps * bg.n;
+    const size_t words = 2 * (size_t)nc + 2;
+    if ((rc = brick.alloc(sizeof(uint32_t) * words)) ||
+        (rc = sums_b.alloc(sizeof(uint32_t) * scan_block_sums_len(nc))) ||
+        (rc = runs.alloc(sizeof(uint64_t) * (n_slots ? n_slots : 1))) ||
+        (rc = items.alloc(sizeof(BrickItem) * item_max)) ||
+        (rc = part.alloc(sizeof(ListHeader) + sizeof(uint64_t) * n_groups)) ||
+        (rc = occupancy_alloc(s)))
+      return rc;
+    uint32_t* bc = brick.as<uint32_t>();
+    cursor = bc + nc + 1;
+    n_items = cursor + nc;
+    if ((rc = fill_u32(bc, 0u, (int64_t)words, st))) return rc;
+    if (n_slots > 0) {
+      hipLaunchKernelGGL(k_runs<false>, dim3(blocks_for((int64_t)n_slots)), dim3(kBlock), 0, st,
+                         vox.as<uint32_t>(), (int64_t)n_slots, bg.n, bc, cursor,
+                         runs.as<unsigned long long>());
+      LS_HIP(hipGetLastError());
+    }
+    if ((rc = exclusive_scan_u32(bc, bc, nc, sums_b.as<uint32_t>(), st))) return rc;
+    if (n_slots > 0) {
+      hipLaunchKernelGGL(k_runs<true>, dim3(blocks_for((int64_t)n_slots)), dim3(kBlock), 0, st,
+                         vox.as<uint32_t>(), (int64_t)n_slots, bg.n, bc, cursor,
+                         runs.as<unsigned long long>());
+      LS_HIP(hipGetLastError());
+    }
+    hipLaunchKernelGGL(k_brick_count, dim3((unsigned)n_groups), dim3(kCountThreads), 0, st, bc,
+                       runs.as<unsigned long long>(), vox.as<uint32_t>(), bg, s->offsets,
+                       reinterpret_cast<unsigned long long*>(s->occupancy),
+                       reinterpret_cast<unsigned long long*>(part.as<ListHeader>() + 1), n_items,
+                       items.as<BrickItem>());
     LS_HIP(hipGetLastError());
   }
   if ((rc = exclusive_scan_u32(s->offsets, s->offsets, s->nvox, sums32.as<uint32_t>(), st)))
     return rc;
-  uint32_t n_rec = 0;
-  LS_HIP(hipMemcpyAsync(&n_rec, s->offsets + s->nvox, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+  ListHeader lh{};
+  if (bricks) {
+    const int64_t nm = (int64_t)s->macro[0] * s->macro[1] * s->macro[2];
+    ListHeader* d_lh = part.as<ListHeader>();
+    hipLaunchKernelGGL(k_list_stats, dim3(1), dim3(1024), 0, st,
+                       reinterpret_cast<unsigned long long*>(d_lh + 1), n_groups,
+                       s->offsets + s->nvox, n_items,
+                       reinterpret_cast<unsigned long long*>(s->occupancy + nm), d_lh);
+    LS_HIP(hipGetLastError());
+    LS_HIP(hipMemcpyAsync(&lh, d_lh, sizeof(lh), hipMemcpyDeviceToHost, st));
+  } else {
+    LS_HIP(hipMemcpyAsync(&lh.n_records, s->offsets + s->nvox, sizeof(uint32_t),
+                          hipMemcpyDeviceToHost, st));
+  }
   LS_HIP(hipStreamSynchronize(st));
+  const uint32_t n_rec = lh.n_records, h_items = lh.n_items;
   s->n_records = n_rec;
+  if (bricks) {
+    s->nonempty = (int64_t)lh.nonempty;
+    s->max_list = (int64_t)lh.max_list;
+    s->stats_pending = false;
+  }
+  // a voxel too long for one workgroup's LDS: scatter and rank through memory
+  const bool long_list = bricks && s->max_list > (int64_t)kItemCap;
 
-  // 5. scatter + rank/gather into the set's record array
+  // 5. the records, list by list
   if ((rc = ls_alloc(s, (void**)&s->records, sizeof(uint64_t) * (n_rec ? n_rec : 1)))) return rc;
   if (vattr && (rc = ls_alloc(s, (void**)&s->ends, sizeof(uint16_t) * (n_rec ? n_rec : 1))))
     return rc;
-  DeviceBuf idx(st);
-  if ((rc = idx.alloc(sizeof(uint64_t) * (n_rec ? n_rec : 1)))) return rc;
-  if (n_slots > 0) {
-    hipLaunchKernelGGL(k_scatter, dim3(blocks_for((int64_t)n_slots)), dim3(kBlock), 0, st,
-                       vox.as<uint32_t>(), rank.as<uint32_t>(), (int64_t)n_slots, s->offsets,
-                       idx.as<uint64_t>());
-    LS_HIP(hipGetLastError());
-  }
-  if (n_rec > 0) {
-    hipLaunchKernelGGL(k_rank, dim3(blocks_for(n_rec)), dim3(kBlock), 0, st, idx.as<uint64_t>(),
-                       rec.as<uint64_t>(), vattr ? ends_slots.as<uint16_t>() : nullptr,
-                       (int64_t)n_rec, s->offsets, s->records, vattr ? s->ends : nullptr);
-    LS_HIP(hipGetLastError());
+  uint16_t* ends = vattr ? s->ends : nullptr;
+  DeviceBuf idx(st), count(st);
+  if (bricks && !long_list) {
+    if (n_rec > 0) {
+      hipLaunchKernelGGL(k_brick_fill, dim3(8 * ((bg.n + 7) / 8)), dim3(kBlock), 0, st,
+                         brick.as<uint32_t>(), runs.as<unsigned long long>(),
+                         vox.as<uint32_t>(), rec.as<uint64_t>(), eo, bg, s->offsets, s->records,
+                         ends);
+      if (h_items > 0)
+        hipLaunchKernelGGL(k_brick_items, dim3(h_items), dim3(kItemThreads), kItemLds, st,
+                           brick.as<uint32_t>(), runs.as<unsigned long long>(),
+                           vox.as<uint32_t>(), rec.as<uint64_t>(), eo, bg, s->offsets, n_items,
+                           items.as<BrickItem>(), s->records, ends);
+      LS_HIP(hipGetLastError());
+    }
+  } else {
+    if ((rc = idx.alloc(sizeof(uint64_t) * (n_rec ? n_rec : 1)))) return rc;
+    if (long_list) {
+      if ((rc = rank.alloc(sizeof(uint32_t) * n_slots)) ||
+          (rc = count.alloc(sizeof(uint32_t) * s->nvox)) ||
+          (rc = fill_u32(count.as<uint32_t>(), 0u, s->nvox, st)))
+        return rc;
+      hipLaunchKernelGGL(k_unbrick, dim3(blocks_for((int64_t)n_slots)), dim3(kBlock), 0, st,
+                         vox.as<uint32_t>(), (int64_t)n_slots, bg, count.as<uint32_t>(),
+                         rank.as<uint32_t>());
+      LS_HIP(hipGetLastError());
+    }
+    if (n_slots > 0) {
+      hipLaunchKernelGGL(k_scatter, dim3(blocks_for((int64_t)n_slots)), dim3(kBlock), 0, st,
+                         vox.as<uint32_t>(), rank.as<uint32_t>(), (int64_t)n_slots, s->offsets,
+                         idx.as<uint64_t>());
+      LS_HIP(hipGetLastError());
+    }
+    if (n_rec > 0) {
+      hipLaunchKernelGGL(k_rank, dim3(blocks_for(n_rec)), dim3(kBlock), 0, st, idx.as<uint64_t>(),
+                         rec.as<uint64_t>(), eo, (int64_t)n_rec, s->offsets, s->records, ends);
+      LS_HIP(hipGetLastError());
+    }
   }
 
-  // 6. macro-cell occupancy and list statistics
-  if ((rc = vox_occupancy(s, st))) return rc;
+  // 6. macro-cell occupancy and list statistics (k_brick_count's by now)
+  if (!bricks && (rc = vox_occupancy(s, st))) return rc;
   LS_HIP(hipStreamSynchronize(st));
   return LS_OK;
 }
@@ -1089,10 +1584,9 @@ int vox_occupancy(ls_lineset* s, hipStream_t st) {
   for (int a = 0; a < 3; ++a) ga.g[a] = s->grid[a];
   ga.bins = s->bins;
   ga.bin_shift = 0;
-  for (int a = 0; a < 3; ++a) s->macro[a] = (s->grid[a] + 3) / 4;
-  int64_t nm = (int64_t)s->macro[0] * s->macro[1] * s->macro[2];
   int rc;
-  if ((rc = ls_alloc(s, (void**)&s->occupancy, sizeof(uint64_t) * (nm + 2)))) return rc;
+  if ((rc = occupancy_alloc(s))) return rc;
+  const int64_t nm = (int64_t)s->macro[0] * s->macro[1] * s->macro[2];
   char* stats = reinterpret_cast<char*>(s->occupancy + nm);
   LS_HIP(hipMemsetAsync(stats, 0, 16, st));
   hipLaunchKernelGGL(k_occupancy, dim3(blocks_for(nm)), dim3(kBlock), 0, st, s->offsets, ga,
