@@ -95,8 +95,9 @@ double vox_scale(const double lo[3], const double hi[3], const int32_t grid[3]);
 int vox_snap(const float* xyz, int64_t nv, SnapArgs sa, int32_t* lat, hipStream_t st);
 // Builds the set's CSR. Float input (xyz): the grid set-up runs on the
 // device and s->lo_scale is set; lattice input (lat): used as given.
+// lists_only: the occupancy words and list statistics may be left out.
 int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t* curve_off,
-              const uint8_t* attr, const uint8_t* vattr, hipStream_t st);
+              const uint8_t* attr, const uint8_t* vattr, hipStream_t st, bool lists_only = false);
 // Occupancy words and list statistics of s->offsets (allocates s->occupancy).
 int vox_occupancy(ls_lineset* s, hipStream_t st);
 

@@ -916,13 +916,6 @@ __device__ inline void local_origin(const Ray& ray, double t, const int32_t cell
 // Hits go back to their owners through a ballot: owner r pulls the hits of
 // the testers in its pair range one by one, so every owner sees the same set
 // of hits (and the same sorted buffer) as if it had tested its list itself.
-// Bits [a, b) of a 64-bit mask (0 <= a <= b <= 64).
-__device__ inline unsigned long long bit_range(int a, int b) {
-  if (a >= b) return 0ull;
-  const unsigned long long hi = b >= 64 ? ~0ull : ((1ull << b) - 1ull);
-  return hi & ~((1ull << a) - 1ull);
-}
-
 __device__ inline double shfl_f64(double v, int src) {
   return __hiloint2double(__shfl(__double2hiint(v), src, 64), __shfl(__double2loint(v), src, 64));
 }
@@ -973,7 +966,7 @@ __device__ __attribute__((always_inline)) inline void voxels_opaque(
       hit = capsule(qr, dr, ddr, iddr, a, b, R.r2, si, so) && vt0r + (double)si >= 0.0;
     }
     unsigned long long m =
-        __ballot(hit) & bit_range(max((int)P - (int)base, 0), min((int)(P + n) - (int)base, 64));
+        __ballot(hit) & lane_range(max((int)P - (int)base, 0), min((int)(P + n) - (int)base, 64));
     while (__ballot(m != 0ull) != 0ull) {
       const int src = m ? __builtin_ctzll(m) : 0;
       const float ts = __shfl(si, src, 64);
@@ -1051,7 +1044,7 @@ __device__ __attribute__((always_inline)) inline void voxels_coop(
               (firstr || HitBuf<float, kCoopSlots>::less(ltr, lir, si, k));
       }
       unsigned long long m =
-          __ballot(hit) & bit_range(max((int)P - (int)base, 0), min((int)(P + np) - (int)base, 64));
+          __ballot(hit) & lane_range(max((int)P - (int)base, 0), min((int)(P + np) - (int)base, 64));
       while (__ballot(m != 0ull) != 0ull) {
         const int src = m ? __builtin_ctzll(m) : 0;
         const float ts = __shfl(si, src, 64), os = __shfl(so, src, 64);
@@ -1444,7 +1437,7 @@ __device__ __attribute__((always_inline)) inline void nb_sweep(
       hit = capsule_abs(q, tr, ql, v, ro.w, rd.w, idd, a, b, R.r2, ti, to);
     }
     unsigned long long m = __ballot(hit) &
-                           bit_range(min(max((int)(mb - qh), 0), 64), min(max((int)(mt - qh), 0), 64));
+                           lane_range(min(max((int)(mb - qh), 0), 64), min(max((int)(mt - qh), 0), 64));
     const float len = (float)(to - ti);
     while (__ballot(m != 0ull) != 0ull) {
       const int src = m ? __builtin_ctzll(m) : 0;
@@ -1508,9 +1501,9 @@ __device__ __attribute__((always_inline)) inline void nb_sweep(
     // this lane's lines of the chunk are contiguous, and so are their places
     const int c0 = max((int)P - (int)base, 0), c1 = min((int)(P + total) - (int)base, 64);
     if (c0 < c1) {
-      const uint32_t before = (uint32_t)__popcll(am & bit_range(0, c0));
+      const uint32_t before = (uint32_t)__popcll(am & lane_range(0, c0));
       if (P >= base) mb = qt + before;   // the lane's first lines
-      mt = qt + before + (uint32_t)__popcll(am & bit_range(c0, c1));
+      mt = qt + before + (uint32_t)__popcll(am & lane_range(c0, c1));
     }
     qt += (uint32_t)__popcll(am);
     if (qt - qh >= 64) test(64);

@@ -12,9 +12,9 @@
 // removed curves' followed by the added curves' records:
 //   1. the added curves are voxelized on their own (same kernels, curve tags
 //      offset by the old curve count), mapped with the set's grid set-up;
-//   2. k_merge_count: thread per voxel, kept old records + added records;
+//   2. k_merge_count: wave per 64 voxels, kept old records + added records;
 //   3. exclusive scan -> new offsets;
-//   4. k_merge_scatter: thread per voxel, copies the kept records, then the
+//   4. k_merge_scatter: wave per 64 voxels, copies the kept records, then the
 //      added ones, into the new record array;
 //   5. occupancy words and list statistics of the new lists.
 // Curve ids live in the records' 24-bit curve tag, so updates need at most
@@ -26,6 +26,7 @@
 #include <vector>
 
 #include "ls_internal.h"
+#include "wave.h"
 
 namespace {
 
@@ -53,39 +54,74 @@ __global__ __launch_bounds__(kBlock) void k_mark_removed(const int64_t* ids, int
   atomicOr(mask + (id >> 5), 1u << (id & 31));
 }
 
+// Both merge passes read the old lists as a wave: the records of 64 consecutive
+// voxels are one contiguous run, taken 64 at a time (coalesced); each voxel owns
+// a range of the chunk's lanes. They are bound by memory traffic (counts: old
+// and added offsets and the records read, counts written; scatter: three offset
+// arrays and the records read, the records written). A thread per voxel walking
+// its list took 128 us to count and 202 us to scatter at 256^3 with 9.5M records
+// (1 % of the curves removed, as many added).
+
 // counts[v] = kept records of v + added records of v
-__global__ __launch_bounds__(kBlock) void k_merge_count(const uint32_t* off, const uint64_t* rec,
-                                                        const uint32_t* mask,
-                                                        const uint32_t* add_off, int64_t nvox,
-                                                        uint32_t* counts) {
+__global__ __launch_bounds__(kBlock) void k_merge_count(const uint32_t* __restrict__ off,
+                                                        const uint64_t* __restrict__ rec,
+                                                        const uint32_t* __restrict__ mask,
+                                                        const uint32_t* __restrict__ add_off,
+                                                        int64_t nvox,
+                                                        uint32_t* __restrict__ counts) {
   const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (v >= nvox) return;
-  const uint32_t lo = off[v], hi = off[v + 1];
-  uint32_t n = 0;
-  if (mask) {
-    for (uint32_t k = lo; k < hi; ++k) n += removed(mask, rec[k]) ? 0u : 1u;
-  } else {
-    n = hi - lo;
+  const bool in = v < nvox;
+  const uint32_t lo = in ? off[v] : 0u, n = in ? off[v + 1] - lo : 0u;
+  uint32_t kept = n;
+  if (in && add_off) kept += add_off[v + 1] - add_off[v];
+  if (mask) {   // wave-uniform
+    uint32_t N;
+    const uint32_t P = wave_excl_scan(n, N);
+    const uint32_t lo0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
+    for (uint32_t base = 0; base < N; base += 64) {
+      const uint32_t w = base + (uint32_t)wave_lane();
+      const bool gone = w < N && removed(mask, rec[lo0 + w]);
+      const unsigned long long gm = __ballot(gone);
+      if (gm == 0ull) continue;
+      // this voxel's lanes of the chunk
+      const int c0 = max((int)P - (int)base, 0), c1 = min((int)(P + n) - (int)base, 64);
+      if (c0 < c1) kept -= (uint32_t)__popcll(gm & lane_range(c0, c1));
+    }
   }
-  if (add_off) n += add_off[v + 1] - add_off[v];
-  counts[v] = n;
+  if (in) counts[v] = kept;
 }
 
-__global__ __launch_bounds__(kBlock) void k_merge_scatter(const uint32_t* off, const uint64_t* rec,
-                                                          const uint32_t* mask,
-                                                          const uint32_t* add_off,
-                                                          const uint64_t* add_rec, int64_t nvox,
-                                                          const uint32_t* new_off,
-                                                          uint64_t* out) {
+__global__ __launch_bounds__(kBlock) void k_merge_scatter(
+    const uint32_t* __restrict__ off, const uint64_t* __restrict__ rec,
+    const uint32_t* __restrict__ mask, const uint32_t* __restrict__ add_off,
+    const uint64_t* __restrict__ add_rec, int64_t nvox, const uint32_t* __restrict__ new_off,
+    uint64_t* __restrict__ out) {
+  __shared__ uint32_t marks[kBlock];
+  uint32_t* own = marks + (threadIdx.x & ~63u);
   const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (v >= nvox) return;
-  uint32_t w = new_off[v];
-  for (uint32_t k = off[v]; k < off[v + 1]; ++k) {
-    const uint64_t r = rec[k];
-    if (!removed(mask, r)) out[w++] = r;
+  const bool in = v < nvox;
+  const uint32_t lo = in ? off[v] : 0u, n = in ? off[v + 1] - lo : 0u;
+  uint32_t next = in ? new_off[v] : 0u;   // this voxel's next free slot
+  uint32_t N;
+  const uint32_t P = wave_excl_scan(n, N);
+  const uint32_t lo0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
+  const int lane = wave_lane();
+  for (uint32_t base = 0; base < N; base += 64) {
+    const uint32_t w = base + (uint32_t)lane;
+    const uint64_t r = w < N ? rec[lo0 + w] : 0ull;
+    const bool keep = w < N && !removed(mask, r);
+    const unsigned long long km = __ballot(keep);
+    const int o = chunk_owner(own, P, n, base);
+    const uint32_t Po = (uint32_t)__shfl((int)P, o, 64);
+    const uint32_t at = (uint32_t)__shfl((int)next, o, 64);
+    // kept records of the same voxel before this one in the chunk
+    const int s0 = Po > base ? (int)(Po - base) : 0;
+    if (keep) out[at + (uint32_t)__popcll(km & lane_range(s0, lane))] = r;
+    const int c0 = max((int)P - (int)base, 0), c1 = min((int)(P + n) - (int)base, 64);
+    if (c0 < c1) next += (uint32_t)__popcll(km & lane_range(c0, c1));
   }
-  if (add_off)
-    for (uint32_t k = add_off[v]; k < add_off[v + 1]; ++k) out[w++] = add_rec[k];
+  if (in && add_off)
+    for (uint32_t k = add_off[v], e = add_off[v + 1]; k < e; ++k) out[next++] = add_rec[k];
 }
 
 // Pool blocks released after the stream has drained.
@@ -222,7 +258,7 @@ extern "C" int lineset_update(ls_lineset_t s, const ls_update_desc* d, void* hip
     add->device = s->device;
     // lattice input: vox_build checks the range (a vertex outside the grid
     // is an error, and the set stays as it was)
-    if ((rc = vox_build(add, nullptr, lat, off, attr, nullptr, st))) return rc;
+    if ((rc = vox_build(add, nullptr, lat, off, attr, nullptr, st, true))) return rc;
   }
 
   // 2. removal mask over the old curve ids

@@ -1331,7 +1331,7 @@ static int occupancy_alloc(ls_lineset* s) {
 }
 
 int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t* curve_off,
-              const uint8_t* attr, const uint8_t* vattr, hipStream_t st) {
+              const uint8_t* attr, const uint8_t* vattr, hipStream_t st, bool lists_only) {
   GridArgs ga;
   for (int a = 0; a < 3; ++a) ga.g[a] = s->grid[a];
   ga.bins = s->bins;
@@ -1571,7 +1571,7 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
   }
 
   // 6. macro-cell occupancy and list statistics (k_brick_count's by now)
-  if (!bricks && (rc = vox_occupancy(s, st))) return rc;
+  if (!bricks && !lists_only && (rc = vox_occupancy(s, st))) return rc;
   LS_HIP(hipStreamSynchronize(st));
   return LS_OK;
 }

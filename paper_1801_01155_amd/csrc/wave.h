@@ -56,4 +56,11 @@ __device__ inline int chunk_owner(uint32_t* own, uint32_t P, uint32_t n, uint32_
   return (int)wave_incl_max(own[lane]);
 }
 
+// Bits [a, b) of a 64-bit mask (0 <= a, b <= 64; none if a >= b).
+__device__ inline unsigned long long lane_range(int a, int b) {
+  if (a >= b) return 0ull;
+  const unsigned long long hi = b >= 64 ? ~0ull : ((1ull << b) - 1ull);
+  return hi & ~((1ull << a) - 1ull);
+}
+
 }  // namespace
