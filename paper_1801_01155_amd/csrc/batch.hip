@@ -19,14 +19,14 @@ struct ls_batch {
   int total_tiles = 0;
   int32_t flags = 0;
   BatchKind kind;            // instance of the batched kernel its views need
-  BatchPlan plan{2, 2, 0};
+  BatchPlan plan = kDefaultPlan;
   BatchQueues queues{};
   std::vector<ls_view> views;
   std::vector<RenderArgs> args;
   std::vector<int32_t> tile_start;
   RenderArgs* d_args = nullptr;
   int32_t* d_tile_start = nullptr;
-  unsigned* d_queue = nullptr;  // 8 queue counters + RenderCounters
+  unsigned* d_queue = nullptr;  // queue counters + RenderCounters
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -37,7 +37,7 @@ struct ls_batch {
 
 namespace {
 
-constexpr int kQueueWords = 8 + (int)(sizeof(RenderCounters) / sizeof(unsigned));
+constexpr int kCountedWords = kQueueWords + (int)(sizeof(RenderCounters) / sizeof(unsigned));
 
 std::mutex g_cache_mu;
 std::map<std::string, BatchPlan> g_plan_cache;
@@ -107,7 +107,7 @@ int prepare(ls_batch* b, const BatchPlan& plan, hipStream_t st) {
 
 int launch(ls_batch* b, bool count, hipStream_t st) {
   int rc;
-  if ((rc = fill_u32(b->d_queue, 0u, count ? kQueueWords : 8, st))) return rc;
+  if ((rc = fill_u32(b->d_queue, 0u, count ? kCountedWords : kQueueWords, st))) return rc;
   return launch_render_batch(b->d_args, b->d_tile_start, b->n_views, b->queues, b->d_queue,
                              b->plan, count, b->kind, st);
 }
@@ -191,11 +191,10 @@ int capture(ls_batch* b) {
 // array per GPU instead of hipMalloc'd buffers.
 constexpr int kStaticViews = 256;
 constexpr size_t kStaticQueueOff = 0;
-constexpr size_t kStaticTileOff = 256;  // after the queue words
+constexpr size_t kStaticTileOff = sizeof(unsigned) * kQueueWords;
 constexpr size_t kStaticArgsOff =
     (kStaticTileOff + sizeof(int32_t) * (kStaticViews + 1) + 255) / 256 * 256;
 constexpr size_t kStaticBytes = kStaticArgsOff + sizeof(RenderArgs) * kStaticViews;
-static_assert(sizeof(unsigned) * 8 <= kStaticTileOff, "queue words overlap the tile starts");
 
 constexpr int kStaticDevices = 64;
 std::mutex g_static_mu;
@@ -269,7 +268,7 @@ static int create_batch(const ls_view* views, int32_t n_views, int32_t flags, co
   };
   if (hipMalloc(&b->d_args, sizeof(RenderArgs) * n_views) != hipSuccess ||
       hipMalloc(&b->d_tile_start, sizeof(int32_t) * (n_views + 1)) != hipSuccess ||
-      hipMalloc(&b->d_queue, sizeof(unsigned) * kQueueWords) != hipSuccess) {
+      hipMalloc(&b->d_queue, sizeof(unsigned) * kCountedWords) != hipSuccess) {
     (void)hipGetLastError();
     ls_set_error("device allocation failed");
     return fail(LS_ENOMEM);
@@ -295,7 +294,7 @@ static int create_batch(const ls_view* views, int32_t n_views, int32_t flags, co
       g_plan_cache[key] = b->plan;
     }
   } else {
-    BatchPlan p{2, 2, 0};
+    BatchPlan p = kDefaultPlan;
     rc = plan_blocks(p.wx, p.wy, 1, b->kind, &p.blocks);
     if (!rc) rc = prepare(b, p, st);
   }
@@ -372,7 +371,7 @@ int lineset_batch_render_counted(ls_batch_t b, ls_render_counters* c, void* hip_
   int rc;
   if ((rc = launch(b, true, st))) return rc;
   RenderCounters h{};
-  LS_HIP(hipMemcpyAsync(&h, b->d_queue + 8, sizeof(h), hipMemcpyDeviceToHost, st));
+  LS_HIP(hipMemcpyAsync(&h, b->d_queue + kQueueWords, sizeof(h), hipMemcpyDeviceToHost, st));
   LS_HIP(hipStreamSynchronize(st));
   export_counters(h, c);
   return LS_OK;
@@ -423,7 +422,7 @@ int lineset_render_batch_static(const ls_view* views, int32_t n_views, void* hip
   // stream synchronisation at the end returns.
   RenderArgs args[kStaticViews];
   int32_t tile_start[kStaticViews + 1];
-  BatchPlan plan{2, 2, 0};
+  BatchPlan plan = kDefaultPlan;
   BatchKind kind;
   for (int v = 0; v < n_views; ++v) add_kind(&kind, views[v]);
   if ((rc = plan_blocks(plan.wx, plan.wy, 1, kind, &plan.blocks))) return rc;
@@ -446,7 +445,7 @@ int lineset_render_batch_static(const ls_view* views, int32_t n_views, void* hip
   LS_HIP(hipMemcpyAsync(d_args, args, sizeof(RenderArgs) * n_views, hipMemcpyHostToDevice, st));
   LS_HIP(hipMemcpyAsync(d_tiles, tile_start, sizeof(int32_t) * (n_views + 1),
                         hipMemcpyHostToDevice, st));
-  rc = fill_u32(d_queue, 0u, 8, st);
+  rc = fill_u32(d_queue, 0u, kQueueWords, st);
   if (!rc) {
     rc = launch_render_batch(d_args, d_tiles, n_views, make_queues((int)total), d_queue, plan,
                              false, kind, st);

@@ -1935,6 +1935,8 @@ __global__ __launch_bounds__(kBlock, kMode == 1 ? 2 : 1) void k_render(RenderArg
 // views' tile counts) is cut into 8 contiguous queues, one per XCD; a
 // workgroup pops tiles from its own XCD's queue and then steals from the
 // others. Every workgroup reaches the exit once all queues are drained.
+// A pop is an atomic on one address for the whole chip: the queues' counters
+// stand in cache lines of their own.
 template <bool kCount, bool kVdi, bool kNb>
 __global__ __launch_bounds__(kBlock, kNb ? 2 : 1) void k_render_batch(const RenderArgs* __restrict__ views,
                                                          const int32_t* __restrict__ tile_start,
@@ -1961,7 +1963,7 @@ __global__ __launch_bounds__(kBlock, kNb ? 2 : 1) void k_render_batch(const Rend
             qb = q.begin[x];
             ql = q.len[x];
           }
-        const unsigned k = atomicAdd(counters + qq, 1u);
+        const unsigned k = atomicAdd(counters + qq * kQueueStride, 1u);
         if (k < (unsigned)ql) {
           t = qb + (int)k;
           break;
@@ -1995,7 +1997,8 @@ __global__ __launch_bounds__(kBlock, kNb ? 2 : 1) void k_render_batch(const Rend
                           own_lds + (threadIdx.x & ~(kWave - 1)), i, j, i < R.W && j < R.H, cnt);
     __syncthreads();
   }
-  if (kCount && counters) flush_counts(reinterpret_cast<RenderCounters*>(counters + kXcds), cnt);
+  if (kCount && counters)
+    flush_counts(reinterpret_cast<RenderCounters*>(counters + kQueueWords), cnt);
 }
 
 // ---------------------------------------------------------------------------

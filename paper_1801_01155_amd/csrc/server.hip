@@ -51,7 +51,6 @@ struct Request {
   hipEvent_t ready = nullptr;  // recorded on the caller's stream at submission
 };
 
-constexpr int kQueueWords = 8 + (int)(sizeof(RenderCounters) / sizeof(unsigned));
 
 struct Slot {
   hipStream_t stream = nullptr;
@@ -71,7 +70,7 @@ struct Slot {
 struct ls_server {
   ls_server_config cfg{};
   int device = 0;
-  BatchPlan plan{2, 2, 0};
+  BatchPlan plan = kDefaultPlan;
   std::vector<ls_lineset_t> sets;
   size_t resident = 0;      // bytes of the sets at the last admission pass
   std::vector<hipEvent_t> free_events;  // submission events, reused
@@ -175,7 +174,7 @@ int launch_slot(ls_server* S, Slot& sl) {
   LS_HIP(hipMemcpyAsync(sl.d_tile_start, sl.h_tile_start, sizeof(int32_t) * (n + 1),
                         hipMemcpyHostToDevice, sl.stream));
   int rc;
-  if ((rc = fill_u32(sl.d_queue, 0u, 8, sl.stream))) return rc;
+  if ((rc = fill_u32(sl.d_queue, 0u, kQueueWords, sl.stream))) return rc;
   if ((rc = launch_render_batch(sl.d_args, sl.d_tile_start, n, q, sl.d_queue, S->plan, false,
                                 kind, sl.stream)))
     return rc;
@@ -320,12 +319,13 @@ int ls_server_create(const ls_server_config* cfg, ls_server_t* out) {
   int per_cu = 1;
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, S->device) != hipSuccess ||
-      batch_blocks_per_cu(2, 2, BatchKind{}, &per_cu) != LS_OK) {
+      batch_blocks_per_cu(kDefaultPlan.wx, kDefaultPlan.wy, BatchKind{}, &per_cu) != LS_OK) {
     delete S;
     ls_set_error("ls_server_create: device query failed");
     return LS_EDEVICE;
   }
-  S->plan = BatchPlan{2, 2, prop.multiProcessorCount * per_cu};
+  S->plan = kDefaultPlan;
+  S->plan.blocks = prop.multiProcessorCount * per_cu;
   S->slots.resize(cfg->n_slots);
   const int nv = cfg->max_batch_views;
   for (Slot& sl : S->slots) {
