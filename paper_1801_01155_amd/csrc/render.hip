@@ -2021,6 +2021,7 @@ constexpr int kCostBuckets = 256;
 // frame: 2.0 -> 1.46 ms (four ways), 1.22 ms (eight ways; 64 tiles the same);
 // opaque frames (unsplit), batch-workload sets 12-18 % faster (four ways).
 constexpr int kTopTiles = 32;
+constexpr int kSmallSplit = 4;   // see split_small
 // In the neighbour mode a wave deals the lines of all its rays over 64 lanes, so
 // a few rays fill it where the set is dense, and split frames split those
 // tiles 16 ways (4 pixels per workgroup): 963x541, 20k x 150 lines in 160^3
@@ -2421,6 +2422,29 @@ int resident_blocks(const RenderArgs& R, int* out) {
   return LS_OK;
 }
 
+// Small frames leave the device idle and last as long as their slowest wave, a
+// serial chain over the steps of its slowest ray. Fewer rays per wave shorten
+// it (fewer lanes wait for the slowest, and each step tests fewer lists), so
+// all tiles are split, up to one ray per workgroup, as long as the workgroups
+// stay below a few times what the device holds; at least four ways, else the
+// measured order pays more. Measured, whole -> split: opaque (limit 4 x
+// resident) 256x256 over 64^3 132 -> 71 us (16 ways; 32: 87, 64: 146), over
+// 192^3 188 -> 107, 128x128 131 -> 62 (64 ways; 16: 71), 400x300 192 -> 119,
+// with hemisphere AO 344 -> 286, neighbour mode 408 -> 286; transparent (limit
+// 8 x resident, against ordered frames split four ways) 256x256 232 -> 159 and
+// 543 -> 327 (limit 4: 182, 428), 100x100 440 -> 204 (64 ways). Transparent
+// neighbour-mode frames stay ordered (256x256: 1.05 ms, 1.12 split 8 ways).
+bool split_small(RenderArgs& R, int resident) {
+  if (R.mode != 0 && !R.opaque) return false;
+  const int64_t most = (int64_t)resident * (R.opaque ? 4 : 8);
+  int s = 1;
+  while (s < 64 && 2 * s * (int64_t)R.n_tiles <= most) s *= 2;
+  if (s < kSmallSplit || s <= R.split_s) return false;
+  R.split_s = s;
+  R.split_n = (2 * R.spiral_r + 1) * (2 * R.spiral_r + 1);
+  return true;
+}
+
 // Plain frames with more workgroups than the device holds at once: tile
 // times are measured, and a frame of a view the stream rendered before (same
 // set shape, image, camera and parameters), or of one with the camera moved
@@ -2429,6 +2453,7 @@ int tile_order(const ls_lineset* s, const ls_camera* cam, const ls_render_params
                RenderArgs& R, hipStream_t st) {
   int resident = 0, rc;
   if ((rc = resident_blocks(R, &resident))) return rc;
+  if (split_small(R, resident)) return LS_OK;
   if ((int64_t)R.n_tiles + (int64_t)R.split_n * (R.split_s - 1) <= resident) return LS_OK;
   OrderKey key;
   std::memset(&key, 0, sizeof(key));

@@ -45,7 +45,7 @@ struct RenderArgs {
   // spiral_r < 0
   int32_t spiral_x, spiral_y, spiral_r;
   // the tiles of the first split_n spiral positions (the innermost rings)
-  // are rendered by split_s workgroups each, on 8 / split_s pixel rows, so
+  // are rendered by split_s workgroups each, on 64 / split_s of its pixels, so
   // the waves over the densest part of the image hold fewer rays
   int32_t split_n, split_s;
   // ordered frames: the first top_n launch positions (the longest measured

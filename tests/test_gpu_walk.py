@@ -64,3 +64,25 @@ def test_coarse_walk_meets_the_same_voxels(grid):
         # layer, 0.01); at most one pixel in a hundred of these small images
         d = np.abs(g.cpu().numpy() - r).max(axis=-1)
         assert (d > 1e-4).mean() <= 0.01, (grid, k)
+
+
+# image sizes (8 x 8 pixel tiles) around the limits of every split: one ray per
+# workgroup, 32, 16, 8, 4 ways, and whole tiles; ragged edges
+@pytest.mark.parametrize("w,h", [(1, 1), (7, 9), (130, 97), (201, 160), (322, 257), (450, 401),
+                                 (641, 480)])
+@pytest.mark.parametrize("opaque,mode", [(True, 0), (False, 0), (True, 1), (False, 1)])
+def test_split_tiles_give_the_whole_image(w, h, opaque, mode):
+    ls = synth.abc_lineset(400, 60, 9)
+    grid = (48, 40, 56)
+    s = L.lineset_voxelize(ls.curve_off, grid, 32, xyz=ls.xyz, attr=ls.attr)
+    lut = U.dev(synth.lut_ramp(1.0) if opaque else synth.lut_importance_alpha())
+    cam = synth.orbit_cameras(grid, 1, w, w, h, orthographic=bool(w & 1))[0]
+    kw = dict(radius=0.4, mode=mode, opaque=opaque, shading=1)
+    out = torch.empty((h, w, 4), dtype=torch.float32, device="cuda")
+    b = L.Batch([(s, cam, lut, out, kw)])       # renders whole tiles
+    b.render()
+    for _ in range(3):                          # first and repeated frames of the view
+        img = torch.full((h, w, 4), -1.0, device="cuda")
+        L.lineset_render(s, cam, lut, out=img, **kw)
+        assert torch.equal(img, out)
+    b.close()
