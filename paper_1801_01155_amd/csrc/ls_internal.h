@@ -71,6 +71,18 @@ void ls_free_all(ls_lineset* s);
 int pool_alloc(size_t bytes, void** out, size_t* rounded);
 void pool_free(void* p);
 
+// Pinned host memory (pool.hip): kPinnedBytes a slot, cached for the process
+// and returned by lineset_pool_trim.
+constexpr size_t kPinnedBytes = 256;
+int pinned_alloc(void** out);
+void pinned_free(void* p);
+
+// Waits for the stream and reads `bytes` (a multiple of 4, at most
+// kPinnedBytes) of device memory behind the work queued on it: a one-workgroup
+// kernel writes them to pinned memory, which costs a launch where a copy to
+// pageable memory costs a staged copy and its own wait.
+int read_words(const void* dev, void* host, size_t bytes, hipStream_t st);
+
 // ---------------------------------------------------------------------------
 // Scans (scan.hip). out may alias in; writes n + 1 values (out[n] = total).
 // `block_sums` needs scan_block_sums_len(n) elements of T.
@@ -82,6 +94,9 @@ int exclusive_scan_u64(const uint64_t* in, uint64_t* out, int64_t n, uint64_t* b
 
 // Fill kernels (no hipMemset, so callers may capture them in graphs).
 int fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t st);
+// Clears three ranges of words in one launch (null: none).
+int clear_u32(uint32_t* a, int64_t na, uint32_t* b, int64_t nb, uint32_t* c, int64_t nc,
+              hipStream_t st);
 
 // ---------------------------------------------------------------------------
 // Voxelization (vox.hip).
@@ -98,8 +113,9 @@ int vox_snap(const float* xyz, int64_t nv, SnapArgs sa, int32_t* lat, hipStream_
 // lists_only: the occupancy words and list statistics may be left out.
 int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t* curve_off,
               const uint8_t* attr, const uint8_t* vattr, hipStream_t st, bool lists_only = false);
-// Occupancy words and list statistics of s->offsets (allocates s->occupancy).
-int vox_occupancy(ls_lineset* s, hipStream_t st);
+// Occupancy words and list statistics of s->offsets (allocates s->occupancy if
+// need be; cleared: its statistics words are zero already).
+int vox_occupancy(ls_lineset* s, hipStream_t st, bool cleared = false);
 
 // ---------------------------------------------------------------------------
 // Density pyramid and illumination (lod.hip, illum.hip).

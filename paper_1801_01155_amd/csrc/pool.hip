@@ -120,9 +120,52 @@ void pool_free(void* p) {
   P.live.erase(it);
 }
 
+namespace {
+
+// Pinned slots come from chunks of kPinnedSlots; a chunk is added only when
+// every slot is in use, so there are as many as calls that ever overlapped.
+constexpr int kPinnedSlots = 16;
+std::mutex g_pin_mu;
+std::vector<void*> g_pin_chunks;
+std::vector<void*> g_pin_free;
+
+}  // namespace
+
+int pinned_alloc(void** out) {
+  std::lock_guard<std::mutex> lk(g_pin_mu);
+  if (g_pin_free.empty()) {
+    void* p = nullptr;
+    if (hipHostMalloc(&p, kPinnedSlots * kPinnedBytes, hipHostMallocPortable) != hipSuccess) {
+      (void)hipGetLastError();
+      ls_set_error("pinned host allocation failed");
+      return LS_ENOMEM;
+    }
+    g_pin_chunks.push_back(p);
+    for (int k = 0; k < kPinnedSlots; ++k)
+      g_pin_free.push_back(static_cast<char*>(p) + k * kPinnedBytes);
+  }
+  *out = g_pin_free.back();
+  g_pin_free.pop_back();
+  return LS_OK;
+}
+
+void pinned_free(void* p) {
+  std::lock_guard<std::mutex> lk(g_pin_mu);
+  g_pin_free.push_back(p);
+}
+
 extern "C" {
 
 void lineset_pool_trim(void) {
+  {
+    // a free slot has no device work: its reader waited for the stream
+    std::lock_guard<std::mutex> lk(g_pin_mu);
+    if (g_pin_free.size() == g_pin_chunks.size() * kPinnedSlots) {
+      for (void* p : g_pin_chunks) (void)hipHostFree(p);
+      g_pin_chunks.clear();
+      g_pin_free.clear();
+    }
+  }
   int cur = 0;
   (void)hipGetDevice(&cur);
   std::lock_guard<std::mutex> lk(g_mu);

@@ -269,14 +269,12 @@ extern "C" int lineset_update(ls_lineset_t s, const ls_update_desc* d, void* hip
     const int64_t words = (s->n_curves + 31) / 32;
     int* err = nullptr;
     if ((rc = T.get(&mask, (size_t)words)) || (rc = T.get(&err, 1))) return rc;
-    if ((rc = fill_u32(mask, 0u, words, st)) || (rc = fill_u32((uint32_t*)err, 0u, 1, st)))
-      return rc;
+    if ((rc = clear_u32(mask, words, (uint32_t*)err, 1, nullptr, 0, st))) return rc;
     hipLaunchKernelGGL(k_mark_removed, dim3(blocks_for(d->n_remove)), dim3(kBlock), 0, st, ids,
                        d->n_remove, s->n_curves, mask, err);
     LS_HIP(hipGetLastError());
     int herr = 0;
-    LS_HIP(hipMemcpyAsync(&herr, err, sizeof(int), hipMemcpyDeviceToHost, st));
-    LS_HIP(hipStreamSynchronize(st));
+    if ((rc = read_words(err, &herr, sizeof(int), st))) return rc;
     if (herr) {
       ls_set_error("lineset_update: a removed curve id is outside [0, %lld)",
                    (long long)s->n_curves);
@@ -311,8 +309,7 @@ extern "C" int lineset_update(ls_lineset_t s, const ls_update_desc* d, void* hip
   LS_HIP(hipGetLastError());
   if ((rc = exclusive_scan_u32(fresh.offsets, fresh.offsets, nvox, sums, st))) return rc;
   uint32_t total = 0;
-  LS_HIP(hipMemcpyAsync(&total, fresh.offsets + nvox, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-  LS_HIP(hipStreamSynchronize(st));
+  if ((rc = read_words(fresh.offsets + nvox, &total, sizeof(uint32_t), st))) return rc;
 
   // 4. records
   if ((rc = ls_alloc(&fresh, (void**)&fresh.records, sizeof(uint64_t) * (total ? total : 1))))

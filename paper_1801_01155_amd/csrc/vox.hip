@@ -1251,17 +1251,27 @@ inline unsigned curve_blocks(int64_t n) {
   return (unsigned)((n + kWavesPerBlock - 1) / kWavesPerBlock);
 }
 
-// Temporary device buffer from the memory cache; released after the stream
-// it was used on has drained.
+// Temporary device buffers from the memory cache; released after the stream
+// they were used on has drained (one wait for all of them).
+struct Drain {
+  hipStream_t st;
+  bool idle = false;   // the stream was waited for after the last use
+  explicit Drain(hipStream_t s) : st(s) {}
+  void wait() {
+    if (!idle) (void)hipStreamSynchronize(st);
+    idle = true;
+  }
+};
+
 struct DeviceBuf {
   void* p = nullptr;
-  hipStream_t st = nullptr;
-  explicit DeviceBuf(hipStream_t s) : st(s) {}
+  Drain& d;
+  explicit DeviceBuf(Drain& drain) : d(drain) {}
   DeviceBuf(const DeviceBuf&) = delete;
   DeviceBuf& operator=(const DeviceBuf&) = delete;
   ~DeviceBuf() {
     if (p) {
-      (void)hipStreamSynchronize(st);
+      d.wait();
       pool_free(p);
     }
   }
@@ -1280,7 +1290,8 @@ int vox_bbox(const float* xyz, int64_t nv, double lo[3], double hi[3], hipStream
   if (nv <= 0) return LS_OK;
   int64_t blocks = (nv + kBlock - 1) / kBlock;
   if (blocks > 1024) blocks = 1024;
-  DeviceBuf part(st), bad(st);
+  Drain drain(st);
+  DeviceBuf part(drain), bad(drain);
   int rc;
   if ((rc = part.alloc(sizeof(double) * 6 * blocks)) || (rc = bad.alloc(sizeof(int)))) return rc;
   LS_HIP(hipMemsetAsync(bad.p, 0, sizeof(int), st));
@@ -1357,14 +1368,27 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
   static_assert(sizeof(Header) == sizeof(uint64_t) + sizeof(SnapArgs) + 2 * sizeof(int),
                 "header layout");
   const size_t slot_bytes = sizeof(uint64_t) * (C + 1);
-  DeviceBuf slots(st), sums64(st), lattice(st);
+  Drain drain(st);
+  DeviceBuf slots(drain), sums64(drain), lattice(drain);
   if ((rc = slots.alloc(slot_bytes + sizeof(SnapArgs) + 2 * sizeof(int))) ||
       (rc = sums64.alloc(sizeof(uint64_t) * scan_block_sums_len(C))) ||
       (rc = lattice.alloc(sizeof(double) * 6 * bb_blocks)))
     return rc;
   SnapArgs* sad = reinterpret_cast<SnapArgs*>(slots.as<char>() + slot_bytes);
   int* errp = reinterpret_cast<int*>(sad + 1);
-  LS_HIP(hipMemsetAsync(errp, 0, 2 * sizeof(int), st));
+  // the offsets array and, where the lists cannot go by bricks, the words that
+  // start at zero: one launch clears them with the error flags
+  if ((rc = ls_alloc(s, (void**)&s->offsets, sizeof(uint32_t) * (s->nvox + 1)))) return rc;
+  const bool small = s->nvox < kBrickMinVoxels;
+  if (small) {
+    if ((rc = occupancy_alloc(s))) return rc;
+    const int64_t nm = (int64_t)s->macro[0] * s->macro[1] * s->macro[2];
+    if ((rc = clear_u32(reinterpret_cast<uint32_t*>(errp), 2, s->offsets, s->nvox + 1,
+                        reinterpret_cast<uint32_t*>(s->occupancy + nm), 4, st)))
+      return rc;
+  } else if ((rc = clear_u32(reinterpret_cast<uint32_t*>(errp), 2, nullptr, 0, nullptr, 0, st))) {
+    return rc;
+  }
   if (float_in) {
     double* part = lattice.as<double>();
     if ((reinterpret_cast<uintptr_t>(xyz) & 15) == 0)
@@ -1391,8 +1415,7 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
                                st)))
     return rc;
   Header hh{};
-  LS_HIP(hipMemcpyAsync(&hh, slots.as<uint64_t>() + C, sizeof(Header), hipMemcpyDeviceToHost, st));
-  LS_HIP(hipStreamSynchronize(st));
+  if ((rc = read_words(slots.as<uint64_t>() + C, &hh, sizeof(Header), st))) return rc;
   const uint64_t n_slots = hh.n_slots;
   const int herr = hh.err[0];
   const SnapArgs hsa = hh.sa;
@@ -1418,8 +1441,7 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
   }
   s->n_slots = (int64_t)n_slots;
 
-  // 2. offsets array (owned by the set) and the way its lists are formed
-  if ((rc = ls_alloc(s, (void**)&s->offsets, sizeof(uint32_t) * (s->nvox + 1)))) return rc;
+  // 2. the way the lists are formed
   BrickGrid bg{};
   for (int a = 0; a < 3; ++a) {
     bg.g[a] = s->grid[a];
@@ -1431,14 +1453,14 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
                       (int64_t)n_slots <= kBrickMaxMean * bg.n;
 
   // 3. emit
-  DeviceBuf rec(st), vox(st), rank(st), sums32(st), ends_slots(st);
+  DeviceBuf rec(drain), vox(drain), rank(drain), sums32(drain), ends_slots(drain);
   if ((rc = rec.alloc(sizeof(uint64_t) * n_slots)) || (rc = vox.alloc(sizeof(uint32_t) * n_slots)) ||
       (rc = sums32.alloc(sizeof(uint32_t) * scan_block_sums_len(s->nvox))))
     return rc;
   if (!bricks) {
     // the offsets array doubles as the histogram
     if ((rc = rank.alloc(sizeof(uint32_t) * n_slots)) ||
-        (rc = fill_u32(s->offsets, 0u, s->nvox + 1, st)))
+        (!small && (rc = fill_u32(s->offsets, 0u, s->nvox + 1, st))))
       return rc;
   }
   if (vattr && (rc = ends_slots.alloc(sizeof(uint16_t) * (n_slots ? n_slots : 1)))) return rc;
@@ -1458,7 +1480,7 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
   }
 
   // 4. counts -> offsets (in place)
-  DeviceBuf brick(st), runs(st), items(st), part(st), sums_b(st);
+  DeviceBuf brick(drain), runs(drain), items(drain), part(drain), sums_b(drain);
   int64_t n_groups = 0;
   const size_t item_max = 3 * (size_t)(n_slots / kFillCap) + 1;
   uint32_t* n_items = nullptr;
@@ -1510,12 +1532,10 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
                        s->offsets + s->nvox, n_items,
                        reinterpret_cast<unsigned long long*>(s->occupancy + nm), d_lh);
     LS_HIP(hipGetLastError());
-    LS_HIP(hipMemcpyAsync(&lh, d_lh, sizeof(lh), hipMemcpyDeviceToHost, st));
-  } else {
-    LS_HIP(hipMemcpyAsync(&lh.n_records, s->offsets + s->nvox, sizeof(uint32_t),
-                          hipMemcpyDeviceToHost, st));
+    if ((rc = read_words(d_lh, &lh, sizeof(lh), st))) return rc;
+  } else if ((rc = read_words(s->offsets + s->nvox, &lh.n_records, sizeof(uint32_t), st))) {
+    return rc;
   }
-  LS_HIP(hipStreamSynchronize(st));
   const uint32_t n_rec = lh.n_records, h_items = lh.n_items;
   s->n_records = n_rec;
   if (bricks) {
@@ -1531,7 +1551,7 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
   if (vattr && (rc = ls_alloc(s, (void**)&s->ends, sizeof(uint16_t) * (n_rec ? n_rec : 1))))
     return rc;
   uint16_t* ends = vattr ? s->ends : nullptr;
-  DeviceBuf idx(st), count(st);
+  DeviceBuf idx(drain), count(drain);
   if (bricks && !long_list) {
     if (n_rec > 0) {
       hipLaunchKernelGGL(k_brick_fill, dim3(8 * ((bg.n + 7) / 8)), dim3(kBlock), 0, st,
@@ -1571,24 +1591,25 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
   }
 
   // 6. macro-cell occupancy and list statistics (k_brick_count's by now)
-  if (!bricks && !lists_only && (rc = vox_occupancy(s, st))) return rc;
+  if (!bricks && !lists_only && (rc = vox_occupancy(s, st, small))) return rc;
   LS_HIP(hipStreamSynchronize(st));
+  drain.idle = true;
   return LS_OK;
 }
 
 // Macro-cell occupancy words and list statistics of s->offsets; the
 // statistics stay on the device after the occupancy words until
 // lineset_info asks for them.
-int vox_occupancy(ls_lineset* s, hipStream_t st) {
+int vox_occupancy(ls_lineset* s, hipStream_t st, bool cleared) {
   GridArgs ga;
   for (int a = 0; a < 3; ++a) ga.g[a] = s->grid[a];
   ga.bins = s->bins;
   ga.bin_shift = 0;
   int rc;
-  if ((rc = occupancy_alloc(s))) return rc;
+  if (!s->occupancy && (rc = occupancy_alloc(s))) return rc;
   const int64_t nm = (int64_t)s->macro[0] * s->macro[1] * s->macro[2];
   char* stats = reinterpret_cast<char*>(s->occupancy + nm);
-  LS_HIP(hipMemsetAsync(stats, 0, 16, st));
+  if (!cleared && (rc = fill_u32(reinterpret_cast<uint32_t*>(stats), 0u, 4, st))) return rc;
   hipLaunchKernelGGL(k_occupancy, dim3(blocks_for(nm)), dim3(kBlock), 0, st, s->offsets, ga,
                      s->macro[0], s->macro[1], s->macro[2], (unsigned long long*)s->occupancy,
                      reinterpret_cast<unsigned long long*>(stats),
