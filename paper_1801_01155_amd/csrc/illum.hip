@@ -151,7 +151,7 @@ __global__ __launch_bounds__(kBlock) void k_shadow(Pyramid P, Cones C, Sched S, 
 // tile and walks its 8 voxels along z. Every sample k of every cone lies
 // within s_k (voxel units) of its voxel, so on level l the taps of the whole
 // tile fall inside a box of (tile extent on l) + 2 m_l cells per axis,
-// m_l = ceil(max s_k / 2^l) + 2 over the samples on l. The block first
+// m_l = ceil(max s_k / 2^l) + 1 over the samples on l. The block first
 // copies each level's box into LDS (coordinates clamped to the level, which
 // makes plain trilinear interpolation of the copy the clamp-to-edge
 // interpolation of the level).
@@ -202,14 +202,15 @@ struct Tap {
   float w;
 };
 
-// Per (cone, sample): the z planes and the inside-the-grid ranges.
-struct alignas(64) ZRec {
+// Per (cone, sample): the z planes, the inside-the-grid ranges, and for each
+// phase ph the weights of planes c_0 + (p_z >> l) + {0, 1, 2}: two neighbours of
+// them carry the linear interpolation times the sample's D, the third is 0.
+struct alignas(128) ZRec {
   int32_t c0;          // byte offset in LDS of plane c_0 (box base included)
-  int32_t delta;       // bit ph: c_ph - c_0 (0 or 1)
   int32_t lo[3], hi[3];  // inside-the-grid voxel ranges (lo > hi: none)
-  float w[8];          // z weight of phase ph
+  float w[8][3];
 };
-static_assert(sizeof(ZRec) == 64, "ZRec is one 64-byte scalar load");
+static_assert(sizeof(ZRec) == 128, "ZRec is two 64-byte scalar loads");
 
 // Planes a column interpolates on level L for 8 voxels: (8 >> L) + 1 on
 // level 0 (one phase), one more on coarser levels (the phases' c_ph may
@@ -280,8 +281,12 @@ __global__ __launch_bounds__(kColThreads) void k_col_table(Pyramid P, Cones C, S
     for (int ph = 0; ph < 8; ++ph) {
       float fl;
       col_coord(ph, lv, f, &fl, &w);
-      r.w[ph] = ph < nph ? w : 0.f;
-      if (ph < nph && fl > fl0) r.delta |= 1 << ph;
+      const int d = ph < nph && fl > fl0 ? 1 : 0;
+      for (int j = 0; j < 3; ++j) r.w[ph][j] = 0.f;
+      if (ph < nph) {
+        r.w[ph][d] = (1.f - w) * S.D[k];
+        r.w[ph][d + 1] = w * S.D[k];
+      }
     }
     const int32_t c0 = min(max((int32_t)fl0 + CL.m[q], 0), CL.sz[q][2] - col_planes_rt(lv));
     r.c0 = (CL.base[q] + c0 * CL.sz[q][0] * CL.sz[q][1]) * (int32_t)sizeof(float);
@@ -292,50 +297,51 @@ __global__ __launch_bounds__(kColThreads) void k_col_table(Pyramid P, Cones C, S
 }
 
 // One (cone, sample) on level L for a thread's column: the planes' bilinear
-// values, then each voxel's z interpolation. Dm is the sample's weight D, or
-// 0 when the column is outside the grid in x or y.
+// values by four weights (0 when the column is outside the grid in x or y),
+// then each voxel's z interpolation, whose weights are wave-uniform and hold
+// the sample's D: 4 operations per plane and 2 (level 0) or 3 per voxel.
+// Interpolating by differences (x, then y, then z, then times D) took 6 and 3
+// to 5; the kernel issues vector instructions all the time: 256^3, 16 cones and
+// the shadow cone, 434 us so.
 // kRowB, kPlaneB > 0: the box strides (bytes) are compile-time constants, so
 // every read of the sample is an immediate offset from one address.
 template <int L, int kRowB = 0, int kPlaneB = 0>
 __device__ inline void col_sample(const char* box, const ZRec& z, int32_t plane_bytes,
-                                  int32_t row_bytes, float wx, float wy, float Dm, int32_t vz0,
+                                  int32_t row_bytes, float wx, float wy, bool in_xy, int32_t vz0,
                                   float occ[kColZ]) {
   constexpr int R = col_planes<L>();
   if (kRowB > 0) {
     plane_bytes = kPlaneB;
     row_bytes = kRowB;
   }
+  const float y1 = in_xy ? wy : 0.f, y0 = in_xy ? 1.f - wy : 0.f;
+  const float w01 = wx * y0, w00 = y0 - w01, w11 = wx * y1, w10 = y1 - w11;
   float pl[R];
 #pragma unroll
   for (int j = 0; j < R; ++j) {
     const float* r0 = reinterpret_cast<const float*>(box + j * plane_bytes);
     const float* r1 = reinterpret_cast<const float*>(box + j * plane_bytes + row_bytes);
-    const float a = __builtin_fmaf(wx, r0[1] - r0[0], r0[0]);
-    const float b = __builtin_fmaf(wx, r1[1] - r1[0], r1[0]);
-    pl[j] = __builtin_fmaf(wy, b - a, a);
+    pl[j] = __builtin_fmaf(w11, r1[1], __builtin_fmaf(w10, r1[0],
+                           __builtin_fmaf(w01, r0[1], w00 * r0[0])));
   }
-  float val[kColZ];
-#pragma unroll
-  for (int pz = 0; pz < kColZ; ++pz) {
-    constexpr int kMask = (1 << L) - 1;
-    const int ph = pz & kMask, i = pz >> L;
-    float p0 = pl[i], p1 = pl[i + 1];
-    if (L > 0 && ((z.delta >> ph) & 1)) {
-      p0 = pl[i + 1];
-      p1 = pl[(L > 0 ? i + 2 : i + 1)];
-    }
-    val[pz] = __builtin_fmaf(z.w[ph], p1 - p0, p0);
-  }
+  constexpr int kMask = (1 << L) - 1;
   if (vz0 >= z.lo[2] && vz0 + kColZ - 1 <= z.hi[2]) {
     // the common case: every voxel of the column segment is inside along z
 #pragma unroll
-    for (int pz = 0; pz < kColZ; ++pz) occ[pz] = __builtin_fmaf(val[pz], Dm, occ[pz]);
+    for (int pz = 0; pz < kColZ; ++pz) {
+      const int ph = pz & kMask, i = pz >> L;
+      occ[pz] = __builtin_fmaf(pl[i], z.w[ph][0], occ[pz]);
+      occ[pz] = __builtin_fmaf(pl[i + 1], z.w[ph][1], occ[pz]);
+      if (L > 0) occ[pz] = __builtin_fmaf(pl[L > 0 ? i + 2 : i], z.w[ph][2], occ[pz]);
+    }
   } else {
 #pragma unroll
     for (int pz = 0; pz < kColZ; ++pz) {
+      const int ph = pz & kMask, i = pz >> L;
       const int32_t vz = vz0 + pz;
-      const float d = vz >= z.lo[2] && vz <= z.hi[2] ? Dm : 0.f;
-      occ[pz] = __builtin_fmaf(val[pz], d, occ[pz]);
+      float v = __builtin_fmaf(pl[i + 1], z.w[ph][1], pl[i] * z.w[ph][0]);
+      if (L > 0) v = __builtin_fmaf(pl[L > 0 ? i + 2 : i], z.w[ph][2], v);
+      occ[pz] += vz >= z.lo[2] && vz <= z.hi[2] ? v : 0.f;
     }
   }
 }
@@ -348,9 +354,10 @@ __device__ inline void col_sample(const char* box, const ZRec& z, int32_t plane_
 // levels >= 3 and are interpolated per column (see below). AO averages the
 // other C.n - 1 cones.
 // kStd: the schedule samples levels 0, 1, 2, 3 (one sample each) with box
-// margin 3 on every level (the 16-cone radius-15 AO of aperture 1), so box
+// margin 2 on every level (the 16-cone radius-15 AO of aperture 1), so box
 // k has the compile-time extent kStdBox[k] and sample k the level k.
-constexpr int kStdBox[4][3] = {{22, 22, 14}, {14, 14, 10}, {10, 10, 8}, {8, 8, 7}};
+constexpr int kStdMargin = 2;
+constexpr int kStdBox[4][3] = {{20, 20, 12}, {12, 12, 8}, {8, 8, 6}, {6, 6, 5}};
 constexpr int std_row(int q) { return kStdBox[q][0] * 4; }
 constexpr int std_plane(int q) { return kStdBox[q][0] * kStdBox[q][1] * 4; }
 
@@ -377,7 +384,8 @@ __global__ __launch_bounds__(kColThreads) void k_cones_col(Pyramid P, Cones C, S
     for (int q = 0; q < 4; ++q) {
       const int sx = kStdBox[q][0], sy = kStdBox[q][1], n = sx * sy * kStdBox[q][2];
       const int32_t dx = P.dims[q][0], dy = P.dims[q][1], dz = P.dims[q][2];
-      const int32_t o0 = (t0[0] >> q) - 3, o1 = (t0[1] >> q) - 3, o2 = (t0[2] >> q) - 3;
+      const int32_t o0 = (t0[0] >> q) - kStdMargin, o1 = (t0[1] >> q) - kStdMargin,
+                    o2 = (t0[2] >> q) - kStdMargin;
       const float* __restrict__ rho = P.rho + P.off[q];
       float* box = lds + CL.base[q];
       // unrolled: eight independent loads in flight per thread (LoD + AO +
@@ -452,24 +460,23 @@ __global__ __launch_bounds__(kColThreads) void k_cones_col(Pyramid P, Cones C, S
       const ZRec z = zc[k];
       const Tap tx = ctx[k], ty = cty[k];
       const bool in_xy = vx >= z.lo[0] && vx <= z.hi[0] && vy >= z.lo[1] && vy <= z.hi[1];
-      const float Dm = in_xy ? S.D[k] : 0.f;
       const int q = CL.slot[k];
       const int32_t row_bytes = CL.sz[q][0] * (int32_t)sizeof(float);
       const int32_t plane_bytes = row_bytes * CL.sz[q][1];
       const char* box = reinterpret_cast<const char*>(lds) + z.c0 + tx.off + ty.off;
       if (kStd) {
         switch (k) {   // k is a constant of the unrolled loop
-          case 0: col_sample<0, std_row(0), std_plane(0)>(box, z, 0, 0, tx.w, ty.w, Dm, t0[2], occ); break;
-          case 1: col_sample<1, std_row(1), std_plane(1)>(box, z, 0, 0, tx.w, ty.w, Dm, t0[2], occ); break;
-          case 2: col_sample<2, std_row(2), std_plane(2)>(box, z, 0, 0, tx.w, ty.w, Dm, t0[2], occ); break;
-          default: col_sample<3, std_row(3), std_plane(3)>(box, z, 0, 0, tx.w, ty.w, Dm, t0[2], occ); break;
+          case 0: col_sample<0, std_row(0), std_plane(0)>(box, z, 0, 0, tx.w, ty.w, in_xy, t0[2], occ); break;
+          case 1: col_sample<1, std_row(1), std_plane(1)>(box, z, 0, 0, tx.w, ty.w, in_xy, t0[2], occ); break;
+          case 2: col_sample<2, std_row(2), std_plane(2)>(box, z, 0, 0, tx.w, ty.w, in_xy, t0[2], occ); break;
+          default: col_sample<3, std_row(3), std_plane(3)>(box, z, 0, 0, tx.w, ty.w, in_xy, t0[2], occ); break;
         }
       } else {
         switch (S.lv[k]) {
-          case 0: col_sample<0>(box, z, plane_bytes, row_bytes, tx.w, ty.w, Dm, t0[2], occ); break;
-          case 1: col_sample<1>(box, z, plane_bytes, row_bytes, tx.w, ty.w, Dm, t0[2], occ); break;
-          case 2: col_sample<2>(box, z, plane_bytes, row_bytes, tx.w, ty.w, Dm, t0[2], occ); break;
-          default: col_sample<3>(box, z, plane_bytes, row_bytes, tx.w, ty.w, Dm, t0[2], occ); break;
+          case 0: col_sample<0>(box, z, plane_bytes, row_bytes, tx.w, ty.w, in_xy, t0[2], occ); break;
+          case 1: col_sample<1>(box, z, plane_bytes, row_bytes, tx.w, ty.w, in_xy, t0[2], occ); break;
+          case 2: col_sample<2>(box, z, plane_bytes, row_bytes, tx.w, ty.w, in_xy, t0[2], occ); break;
+          default: col_sample<3>(box, z, plane_bytes, row_bytes, tx.w, ty.w, in_xy, t0[2], occ); break;
         }
       }
     }
@@ -619,7 +626,9 @@ bool make_col_levels(const ls_lineset* s, const Sched& S, ColLevels* T) {
       T->m[q] = 0;
       T->n++;
     }
-    const int m = (int)std::ceil((double)S.s[k] / (double)(1 << lv)) + 2;
+    // a sample r = s / 2^lv cells away reads cells floor(x), floor(x) + 1 with
+    // |x - cell| <= r + 1/2: within ceil(r) + 1
+    const int m = (int)std::ceil((double)S.s[k] / (double)(1 << lv)) + 1;
     T->m[q] = std::max(T->m[q], m);
     T->slot[k] = q;
   }
@@ -662,7 +671,7 @@ int launch_cones(ls_lineset* s, const Cones& C, const Sched& S, float* out, hipS
     Tap* xyt = reinterpret_cast<Tap*>(zt + (size_t)C.n * S.n);
     bool std4 = S.n == 4 && T.n == 4;
     for (int q = 0; std4 && q < 4; ++q)
-      std4 = S.lv[q] == q && T.lv[q] == q && T.slot[q] == q && T.m[q] == 3 &&
+      std4 = S.lv[q] == q && T.lv[q] == q && T.slot[q] == q && T.m[q] == kStdMargin &&
              T.sz[q][0] == kStdBox[q][0] && T.sz[q][1] == kStdBox[q][1] &&
              T.sz[q][2] == kStdBox[q][2];
     if (std4) {
