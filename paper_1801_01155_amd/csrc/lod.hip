@@ -9,6 +9,7 @@
 #include <algorithm>
 
 #include "ls_internal.h"
+#include "wave.h"
 
 namespace {
 
@@ -29,70 +30,43 @@ __device__ inline void decode_point(uint32_t code, float inv_bins, float p[3]) {
 // run of records, read 64 at a time by the whole wave (coalesced); each
 // line's length goes through a segmented scan over the lanes holding its
 // voxel's lines, and the voxel's lane collects its segment's total. A wave
-// costs (lines of its voxels) / 64 steps instead of its longest list.
-__device__ inline int wave_lane() { return (int)(threadIdx.x & 63); }
-
-__global__ __launch_bounds__(kBlock) void k_lod0(const uint32_t* offsets, const uint64_t* records,
-                                                 int64_t nvox, float inv_bins, const float* lut,
-                                                 int opaque, float* count, float* len, float* rho) {
-  const int lane = wave_lane();
-  const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const bool in = v < nvox;
-  uint32_t lo = 0, hi = 0;
-  if (in) {
-    lo = offsets[v];
-    hi = offsets[v + 1];
-  }
-  // the transfer function's opacities, staged once per block (a record's
-  // opacity is then not a global load that waits for the record)
-  static_assert(kBlock == 256, "one thread per transfer-function entry");
-  __shared__ float s_alpha[256];
-  s_alpha[threadIdx.x] = opaque ? 1.f : lut[4 * threadIdx.x + 3];
-  __syncthreads();
-  const uint32_t n = hi - lo;
-  // exclusive scan of the list lengths: this voxel's lines are the wave's
-  // lines [P, P + n), i.e. records lo0 + [P, P + n)
-  uint32_t inc = n;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t y = __shfl_up(inc, d, 64);
-    if (lane >= d) inc += y;
-  }
-  const uint32_t P = inc - n;
-  const uint32_t N = __shfl(inc, 63, 64);
-  const uint32_t lo0 = __shfl(lo, 0, 64);
-  float l = 0.f, r = 0.f;
+// costs (lines of its voxels) / 64 steps instead of its longest list. The
+// scans and the owners are DPP moves (wave.h): as chains of cross-lane reads
+// (18 per step) level 0 took 122 us at 256^3 with 9.5M records, against about 60
+// for its memory traffic; so 115.
+// Sums of the wave's voxels: this lane's list is [lo, lo + n).
+__device__ inline void lod_sums(const uint64_t* __restrict__ records, uint32_t lo, uint32_t n,
+                                float inv_bins, const float* s_alpha, uint32_t* own, float& l,
+                                float& r) {
+  // this voxel's lines are the wave's lines [P, P + n), records lo0 + [P, P + n)
+  uint32_t N;
+  const uint32_t P = wave_excl_scan(n, N);
+  const uint32_t lo0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
+  l = r = 0.f;
+  // the records of the next two steps are in flight while a step is summed
+  uint64_t r0 = 0, r1 = 0;
+  if ((uint32_t)wave_lane() < N) r0 = records[lo0 + (uint32_t)wave_lane()];
+  if ((uint32_t)wave_lane() + 64u < N) r1 = records[lo0 + (uint32_t)wave_lane() + 64u];
   for (uint32_t base = 0; base < N; base += 64) {
-    const uint32_t w = base + (uint32_t)lane;
-    // owner: the last lane whose P <= w (lists are in lane order)
-    int o = 0;
-#pragma unroll
-    for (int step = 32; step >= 1; step >>= 1) {
-      const uint32_t pq = __shfl(P, o + step, 64);
-      if (pq <= w) o += step;
-    }
+    const uint32_t w = base + (uint32_t)wave_lane();
+    const uint64_t rec = r0;
+    r0 = r1;
+    if (w + 128u < N) r1 = records[lo0 + w + 128u];
+    const int o = chunk_owner(own, P, n, base);
     float L = 0.f, Ls = 0.f;
     if (w < N) {
-      const uint64_t rec = records[lo0 + w];
       float a[3], b[3];
       decode_point((uint32_t)(rec & 0x7FFFu), inv_bins, a);
       decode_point((uint32_t)((rec >> 15) & 0x7FFFu), inv_bins, b);
       const float dx = b[0] - a[0], dy = b[1] - a[1], dz = b[2] - a[2];
       L = sqrtf(dx * dx + dy * dy + dz * dz);
-      const float sigma = s_alpha[(rec >> 32) & 0xFF];
-      Ls = L * sigma;
+      Ls = L * s_alpha[(rec >> 32) & 0xFF];
     }
-    // segmented inclusive scan: lanes of one owner form a contiguous run
-    const uint32_t po = __shfl(P, o, 64);
+    // lanes of one owner form a contiguous run
+    const uint32_t po = (uint32_t)__shfl((int)P, o, 64);
     const int seg0 = po > base ? (int)(po - base) : 0;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const float yl = __shfl_up(L, d, 64), yr = __shfl_up(Ls, d, 64);
-      if (lane - d >= seg0) {
-        L += yl;
-        Ls += yr;
-      }
-    }
+    L = wave_seg_sum(L, seg0);
+    Ls = wave_seg_sum(Ls, seg0);
     // this voxel's run in the chunk ends at lane min(P + n, base + 64) - 1
     // (all lanes shuffle; lanes without a run here discard the value)
     const bool here = n != 0 && P < base + 64u && P + n > base;
@@ -103,10 +77,86 @@ __global__ __launch_bounds__(kBlock) void k_lod0(const uint32_t* offsets, const 
       r += tr;
     }
   }
+}
+
+// The transfer function's opacities, staged once per block (a record's opacity
+// is then not a global load that waits for the record).
+__device__ inline void stage_alpha(const float* lut, int opaque, float* s_alpha) {
+  static_assert(kBlock == 256, "one thread per transfer-function entry");
+  s_alpha[threadIdx.x] = opaque ? 1.f : lut[4 * threadIdx.x + 3];
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(kBlock) void k_lod0(const uint32_t* __restrict__ offsets,
+                                                 const uint64_t* __restrict__ records,
+                                                 int64_t nvox, float inv_bins, const float* lut,
+                                                 int opaque, float* __restrict__ count,
+                                                 float* __restrict__ len, float* __restrict__ rho) {
+  __shared__ float s_alpha[256];
+  __shared__ uint32_t marks[kBlock];
+  const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  const bool in = v < nvox;
+  const uint32_t lo = in ? offsets[v] : 0u, n = in ? offsets[v + 1] - lo : 0u;
+  stage_alpha(lut, opaque, s_alpha);
+  float l, r;
+  lod_sums(records, lo, n, inv_bins, s_alpha, marks + (threadIdx.x & ~63u), l, r);
   if (!in) return;
   count[v] = (float)n;
   len[v] = l;
   rho[v] = r;
+}
+
+struct LodRows {
+  int32_t g[3], p[3];   // level 0 and level 1 dims
+  int64_t off1;         // level 1's first cell
+};
+
+// Levels 0 and 1 together: a block takes 64 x 2 x 2 voxels, a wave per row along
+// x, and averages its 32 level-1 cells from LDS (children in k_mip's order, so
+// the same bits), instead of reading the three fields of level 0 again. 256^3,
+// 9.5M records: 171 us for both as two kernels, 147 so; its traffic takes 75, what
+// is left is the latency of a block's few serial stages. Rows shorter than
+// kRowMin would leave too many lanes idle.
+constexpr int kRowMin = 48;
+
+__global__ __launch_bounds__(kBlock) void k_lod01(const uint32_t* __restrict__ offsets,
+                                                  const uint64_t* __restrict__ records,
+                                                  LodRows g, float inv_bins, const float* lut,
+                                                  int opaque, float* __restrict__ count,
+                                                  float* __restrict__ len,
+                                                  float* __restrict__ rho) {
+  __shared__ float s_alpha[256];
+  __shared__ uint32_t marks[kBlock];
+  __shared__ float s_row[3][kBlock];
+  const int lane = wave_lane(), wave = (int)(threadIdx.x >> 6);
+  const int x = 64 * (int)blockIdx.x + lane, y = 2 * (int)blockIdx.y + (wave & 1),
+            z = 2 * (int)blockIdx.z + (wave >> 1);
+  const bool in = x < g.g[0] && y < g.g[1] && z < g.g[2];
+  const int64_t v = x + (int64_t)g.g[0] * (y + (int64_t)g.g[1] * z);
+  const uint32_t lo = in ? offsets[v] : 0u, n = in ? offsets[v + 1] - lo : 0u;
+  stage_alpha(lut, opaque, s_alpha);
+  float l, r;
+  lod_sums(records, lo, n, inv_bins, s_alpha, marks + (threadIdx.x & ~63u), l, r);
+  if (in) {
+    count[v] = (float)n;
+    len[v] = l;
+    rho[v] = r;
+  }
+  // rows and voxels outside the grid hold 0
+  s_row[0][threadIdx.x] = (float)n;
+  s_row[1][threadIdx.x] = l;
+  s_row[2][threadIdx.x] = r;
+  __syncthreads();
+  const int c = wave, i = lane;   // field, cell
+  const int px = 32 * (int)blockIdx.x + i;
+  if (c >= 3 || i >= 32 || px >= g.p[0]) return;
+  float sum = 0.f;
+#pragma unroll
+  for (int k = 0; k < 8; ++k)   // x fastest, then y, then z
+    sum += s_row[c][64 * (k >> 1) + 2 * i + (k & 1)];
+  float* out = c == 0 ? count : (c == 1 ? len : rho);
+  out[g.off1 + px + (int64_t)g.p[0] * ((int)blockIdx.y + (int64_t)g.p[1] * (int)blockIdx.z)] =
+      sum * 0.125f;
 }
 
 struct MipArgs {
@@ -305,7 +355,20 @@ int lod_build(ls_lineset* s, const float* lut, int opaque, hipStream_t st) {
         (rc = ls_alloc(s, (void**)&s->lod_len, bytes)) || (rc = ls_alloc(s, (void**)&s->lod_rho, bytes)))
       return rc;
   }
-  if (s->nvox > 0) {
+  int L = 0;
+  if (s->grid[0] >= kRowMin && s->n_levels > 1) {
+    LodRows g{};
+    for (int a = 0; a < 3; ++a) {
+      g.g[a] = s->level_dims[0][a];
+      g.p[a] = s->level_dims[1][a];
+    }
+    g.off1 = s->level_off[1];
+    hipLaunchKernelGGL(k_lod01, dim3((g.g[0] + 63) / 64, g.p[1], g.p[2]), dim3(kBlock), 0, st,
+                       s->offsets, s->records, g, 1.0f / (float)s->bins, lut, opaque,
+                       s->lod_count, s->lod_len, s->lod_rho);
+    LS_HIP(hipGetLastError());
+    L = 1;
+  } else if (s->nvox > 0) {
     hipLaunchKernelGGL(k_lod0, dim3(blocks_for(s->nvox)), dim3(kBlock), 0, st, s->offsets,
                        s->records, s->nvox, 1.0f / (float)s->bins, lut, opaque, s->lod_count,
                        s->lod_len, s->lod_rho);
@@ -313,7 +376,6 @@ int lod_build(ls_lineset* s, const float* lut, int opaque, hipStream_t st) {
   }
   // large levels stream their children at full occupancy (a thread per
   // voxel); the small rest goes kBrickLevels levels per launch through LDS
-  int L = 0;
   for (; L + 1 < s->n_levels; ++L) {
     const int64_t p0 = s->level_off[L + 1];
     const int64_t n = s->level_off[L + 2] - p0;

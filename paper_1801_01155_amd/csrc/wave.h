@@ -44,6 +44,32 @@ __device__ inline uint32_t wave_excl_scan(uint32_t v, uint32_t& total) {
   return inc - v;
 }
 
+// Inclusive sum over the lanes [seg0, lane], seg0 the same for the lanes of one
+// contiguous segment.
+template <int kCtrl, int kRows>
+__device__ inline float dpp_or_0f(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, kRows, 0xF, false));
+}
+
+__device__ inline float wave_seg_sum(float v, int seg0) {
+  const int lane = wave_lane();
+  float y;
+  y = dpp_or_0f<0x111, 0xF>(v);
+  v += lane - 1 >= seg0 ? y : 0.f;
+  y = dpp_or_0f<0x112, 0xF>(v);
+  v += lane - 2 >= seg0 ? y : 0.f;
+  y = dpp_or_0f<0x114, 0xF>(v);
+  v += lane - 4 >= seg0 ? y : 0.f;
+  y = dpp_or_0f<0x118, 0xF>(v);
+  v += lane - 8 >= seg0 ? y : 0.f;
+  y = dpp_or_0f<0x142, 0xA>(v);   // the end of the row before, into rows 1 and 3
+  v += seg0 < (lane & 48) ? y : 0.f;
+  y = dpp_or_0f<0x143, 0xC>(v);   // lane 31, into rows 2 and 3
+  v += seg0 < 32 ? y : 0.f;
+  return v;
+}
+
 // Owner of pair base + lane among the wave's pairs (lane r owns [P_r, P_r +
 // n_r), in lane order): each owner marks its first pair of the chunk in the
 // wave's 64 words of LDS, and a running maximum spreads the marks.
