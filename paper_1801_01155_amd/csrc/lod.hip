@@ -285,15 +285,13 @@ __global__ __launch_bounds__(kBlock) void k_lodc0(const uint32_t* offsets, const
   rgb[3 * v + 2] = c[2];
 }
 
-// One coarser colour level: a thread per parent averages its 8 children
-// (x fastest, missing children beyond an odd side count as 0).
-__global__ __launch_bounds__(kBlock) void k_mipc(const float* child, float* parent, MipArgs m) {
-  const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const int64_t np = (int64_t)m.px * m.py * m.pz;
-  if (v >= np) return;
+// One coarser colour level: parent cell v averages its 8 children (x fastest,
+// missing children beyond an odd side count as 0).
+__device__ inline void mipc_cell(const float* child, float* parent, const MipArgs& m, int64_t v) {
   const int32_t x = (int32_t)(v % m.px), y = (int32_t)((v / m.px) % m.py),
                 z = (int32_t)(v / ((int64_t)m.px * m.py));
   float s[3] = {0.f, 0.f, 0.f};
+#pragma unroll
   for (int k = 0; k < 8; ++k) {
     const int32_t cx = 2 * x + (k & 1), cy = 2 * y + ((k >> 1) & 1), cz = 2 * z + (k >> 2);
     if (cx >= m.cx || cy >= m.cy || cz >= m.cz) continue;
@@ -305,6 +303,33 @@ __global__ __launch_bounds__(kBlock) void k_mipc(const float* child, float* pare
   parent[3 * v + 0] = s[0] * 0.125f;
   parent[3 * v + 1] = s[1] * 0.125f;
   parent[3 * v + 2] = s[2] * 0.125f;
+}
+
+__global__ __launch_bounds__(kBlock) void k_mipc(const float* __restrict__ child,
+                                                 float* __restrict__ parent, MipArgs m) {
+  const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (v < (int64_t)m.px * m.py * m.pz) mipc_cell(child, parent, m, v);
+}
+
+// The small top levels (up to kTailCells each) in one workgroup, level by level,
+// instead of a launch each.
+constexpr int64_t kTailCells = 1024;
+constexpr int kTailThreads = 1024;
+struct ColorTail {
+  int32_t n;              // levels written
+  int32_t dim[14][3];     // the level below them, then them
+  int64_t off[14];
+};
+
+__global__ __launch_bounds__(kTailThreads) void k_mipc_tail(ColorTail t, float* rgb) {
+  for (int l = 1; l <= t.n; ++l) {
+    const MipArgs m{t.dim[l - 1][0], t.dim[l - 1][1], t.dim[l - 1][2],
+                    t.dim[l][0],     t.dim[l][1],     t.dim[l][2]};
+    const int64_t n = (int64_t)m.px * m.py * m.pz;
+    for (int64_t v = threadIdx.x; v < n; v += kTailThreads)
+      mipc_cell(rgb + 3 * t.off[l - 1], rgb + 3 * t.off[l], m, v);
+    __syncthreads();
+  }
 }
 
 }  // namespace
@@ -321,12 +346,24 @@ int lod_color_build(ls_lineset* s, const float* lut, int opaque, hipStream_t st)
                        s->records, s->nvox, 1.0f / (float)s->bins, lut, opaque, s->lod_rgb);
     LS_HIP(hipGetLastError());
   }
-  for (int L = 0; L + 1 < s->n_levels; ++L) {
+  int L = 0;
+  for (; L + 1 < s->n_levels; ++L) {
     const int64_t n = s->level_off[L + 2] - s->level_off[L + 1];
+    if (n <= kTailCells) break;
     MipArgs m{s->level_dims[L][0],     s->level_dims[L][1],     s->level_dims[L][2],
               s->level_dims[L + 1][0], s->level_dims[L + 1][1], s->level_dims[L + 1][2]};
     hipLaunchKernelGGL(k_mipc, dim3(blocks_for(n)), dim3(kBlock), 0, st,
                        s->lod_rgb + 3 * s->level_off[L], s->lod_rgb + 3 * s->level_off[L + 1], m);
+    LS_HIP(hipGetLastError());
+  }
+  if (L + 1 < s->n_levels) {
+    ColorTail t{};
+    t.n = s->n_levels - 1 - L;   // at most 11 levels in all: sides up to 1024
+    for (int k = 0; k <= t.n; ++k) {
+      for (int a = 0; a < 3; ++a) t.dim[k][a] = s->level_dims[L + k][a];
+      t.off[k] = s->level_off[L + k];
+    }
+    hipLaunchKernelGGL(k_mipc_tail, dim3(1), dim3(kTailThreads), 0, st, t, s->lod_rgb);
     LS_HIP(hipGetLastError());
   }
   return LS_OK;

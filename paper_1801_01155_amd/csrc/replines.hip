@@ -123,21 +123,26 @@ __global__ __launch_bounds__(kBlock) void k_rep0(const uint32_t* __restrict__ of
   pre[v] = acc.code(bins);
 }
 
-// Level l + 1 from the joined lines of level l (thread per parent).
-__global__ __launch_bounds__(kBlock) void k_rep_up(const uint32_t* __restrict__ child, int32_t cx,
-                                                   int32_t cy, int32_t cz, int32_t px, int32_t py,
-                                                   int32_t pz, int32_t bins,
-                                                   uint32_t* __restrict__ pre) {
-  const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const int64_t np = (int64_t)px * py * pz;
-  if (v >= np) return;
+// Level l + 1 from the joined lines of level l: parent cell v.
+__device__ inline void rep_up_cell(const uint32_t* child, const int32_t c_dim[3],
+                                   const int32_t p_dim[3], int32_t bins, int64_t v, uint32_t* pre) {
+  const int32_t px = p_dim[0], py = p_dim[1];
+  const int32_t cx = c_dim[0], cy = c_dim[1], cz = c_dim[2];
   const int32_t x = (int32_t)(v % px), y = (int32_t)((v / px) % py), z = (int32_t)(v / ((int64_t)px * py));
+  // every child's code is loaded before any is used
+  uint32_t codes[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int32_t c[3] = {2 * x + (k & 1), 2 * y + ((k >> 1) & 1), 2 * z + (k >> 2)};
+    codes[k] = c[0] < cx && c[1] < cy && c[2] < cz
+                   ? child[c[0] + (int64_t)cx * (c[1] + (int64_t)cy * c[2])]
+                   : kNone;
+  }
   RepAcc acc;
+#pragma unroll
   for (int k = 0; k < 8; ++k) {
     const int32_t off[3] = {k & 1, (k >> 1) & 1, k >> 2};
-    const int32_t c[3] = {2 * x + off[0], 2 * y + off[1], 2 * z + off[2]};
-    if (c[0] >= cx || c[1] >= cy || c[2] >= cz) continue;
-    const uint32_t code = child[c[0] + (int64_t)cx * (c[1] + (int64_t)cy * c[2])];
+    const uint32_t code = codes[k];
     if (code == kNone) continue;
     int32_t a[3], b[3];
     end_units(code & 0x7FFFu, bins, a);
@@ -152,19 +157,15 @@ __global__ __launch_bounds__(kBlock) void k_rep_up(const uint32_t* __restrict__ 
   pre[v] = acc.code(bins);
 }
 
-// Joins the lines of one level across shared faces (thread per voxel).
-__global__ __launch_bounds__(kBlock) void k_rep_join(const uint32_t* __restrict__ pre, int32_t dx,
-                                                     int32_t dy, int32_t dz,
-                                                     uint32_t* __restrict__ out) {
-  const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const int64_t nv = (int64_t)dx * dy * dz;
-  if (v >= nv) return;
+// Joins the line of cell v of one level across shared faces.
+__device__ inline void rep_join_cell(const uint32_t* pre, const int32_t dim[3], int64_t v,
+                                     uint32_t* out) {
+  const int32_t dx = dim[0], dy = dim[1];
   const uint32_t code = pre[v];
   if (code == kNone) {
     out[v] = kNone;
     return;
   }
-  const int32_t dim[3] = {dx, dy, dz};
   const int32_t cell[3] = {(int32_t)(v % dx), (int32_t)((v / dx) % dy), (int32_t)(v / ((int64_t)dx * dy))};
   uint32_t ends[2] = {code & 0x7FFFu, (code >> 15) & 0x7FFFu};
   if ((ends[0] & 7u) != (ends[1] & 7u)) {
@@ -189,6 +190,49 @@ __global__ __launch_bounds__(kBlock) void k_rep_join(const uint32_t* __restrict_
   out[v] = ends[0] | (ends[1] << 15);
 }
 
+struct RepLevel {
+  int32_t dim[3];
+  int64_t off;   // first cell in the flat array
+  __host__ __device__ int64_t cells() const { return (int64_t)dim[0] * dim[1] * dim[2]; }
+};
+
+__global__ __launch_bounds__(kBlock) void k_rep_up(const uint32_t* __restrict__ child, RepLevel c,
+                                                   RepLevel p, int32_t bins,
+                                                   uint32_t* __restrict__ pre) {
+  const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (v < p.cells()) rep_up_cell(child, c.dim, p.dim, bins, v, pre);
+}
+
+__global__ __launch_bounds__(kBlock) void k_rep_join(const uint32_t* __restrict__ pre, RepLevel p,
+                                                     uint32_t* __restrict__ out) {
+  const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (v < p.cells()) rep_join_cell(pre, p.dim, v, out);
+}
+
+// The small top levels (up to kTailCells each), one workgroup: level by level,
+// with barriers where the levels above each took two launches (150 x 131 x 93:
+// 18 launches -> 7).
+constexpr int64_t kTailCells = 1024;
+constexpr int kTailThreads = 1024;
+struct RepTail {
+  int32_t n;                // levels written
+  RepLevel lv[14];          // the level below them, then them
+};
+
+__global__ __launch_bounds__(kTailThreads) void k_rep_tail(RepTail t, int32_t bins, uint32_t* pre,
+                                                           uint32_t* rep) {
+  for (int l = 1; l <= t.n; ++l) {
+    const RepLevel &c = t.lv[l - 1], &p = t.lv[l];
+    const int64_t n = p.cells();
+    for (int64_t v = threadIdx.x; v < n; v += kTailThreads)
+      rep_up_cell(rep + c.off, c.dim, p.dim, bins, v, pre);
+    __syncthreads();
+    for (int64_t v = threadIdx.x; v < n; v += kTailThreads)
+      rep_join_cell(pre, p.dim, v, rep + p.off);
+    __syncthreads();
+  }
+}
+
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
 }  // namespace
@@ -208,15 +252,24 @@ int rep_build(ls_lineset* s, hipStream_t st) {
     return rc;
   hipLaunchKernelGGL(k_rep0, dim3(blocks_for(s->nvox)), dim3(kBlock), 0, st, s->offsets,
                      s->records, s->nvox, s->bins, pre);
-  hipLaunchKernelGGL(k_rep_join, dim3(blocks_for(s->nvox)), dim3(kBlock), 0, st, pre,
-                     dims[0][0], dims[0][1], dims[0][2], s->rep);
-  for (int l = 1; l < n_levels; ++l) {
-    const int64_t np = (int64_t)dims[l][0] * dims[l][1] * dims[l][2];
-    hipLaunchKernelGGL(k_rep_up, dim3(blocks_for(np)), dim3(kBlock), 0, st,
-                       s->rep + loff[l - 1], dims[l - 1][0], dims[l - 1][1], dims[l - 1][2],
-                       dims[l][0], dims[l][1], dims[l][2], s->bins, pre);
-    hipLaunchKernelGGL(k_rep_join, dim3(blocks_for(np)), dim3(kBlock), 0, st, pre, dims[l][0],
-                       dims[l][1], dims[l][2], s->rep + loff[l]);
+  auto level = [&](int l) {
+    return RepLevel{{dims[l][0], dims[l][1], dims[l][2]}, loff[l]};
+  };
+  hipLaunchKernelGGL(k_rep_join, dim3(blocks_for(s->nvox)), dim3(kBlock), 0, st, pre, level(0),
+                     s->rep);
+  int l = 1;
+  for (; l < n_levels && level(l).cells() > kTailCells; ++l) {
+    const RepLevel p = level(l);
+    hipLaunchKernelGGL(k_rep_up, dim3(blocks_for(p.cells())), dim3(kBlock), 0, st,
+                       s->rep + loff[l - 1], level(l - 1), p, s->bins, pre);
+    hipLaunchKernelGGL(k_rep_join, dim3(blocks_for(p.cells())), dim3(kBlock), 0, st, pre, p,
+                       s->rep + p.off);
+  }
+  if (l < n_levels) {
+    RepTail t{};
+    t.n = n_levels - l;   // at most 11 levels in all: sides up to 1024
+    for (int k = 0; k <= t.n; ++k) t.lv[k] = level(l - 1 + k);
+    hipLaunchKernelGGL(k_rep_tail, dim3(1), dim3(kTailThreads), 0, st, t, s->bins, pre, s->rep);
   }
   const hipError_t e = hipGetLastError();
   // the temporary returns to the cache once the stream has passed its readers
