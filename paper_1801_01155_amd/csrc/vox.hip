@@ -205,6 +205,7 @@ struct Ev {
   int fa, exit_side;                // face axis, side of the exited voxel's face
   int planes;                       // planes crossed at this event (1 to 3)
   int32_t ncell[3];                 // the entered voxel
+  uint32_t xl[3];                   // low 32 bits of the point times den (face codes requested)
 };
 
 // a * b for a, b below 2^24: two full-rate 24-bit multiplies.
@@ -259,7 +260,7 @@ __device__ inline void for_each_event(const int32_t P0[3], const int32_t P1[3], 
 #pragma unroll
     for (int b = 0; b < 3; ++b) ev.ncell[b] = ncell[b];
     if (kCodes) {
-      uint32_t xl[3];
+      uint32_t* xl = ev.xl;
       event_low(P0, d, ev.den, ev.nf, xl);
       ev.exit_code = face_code(fa, exit_side, xl, ev.den, cell, ga);
       // one plane crossed: the entered voxel has the same in-face cells, so
@@ -279,24 +280,35 @@ __device__ inline void for_each_event(const int32_t P0[3], const int32_t P1[3], 
   }
 }
 
-// The last event of the lanes before this one (or of earlier chunks).
+// The last event of the lanes before this one (or of earlier chunks): its point
+// is voxel corner + l / den in the voxel it enters (l in [0, 256 den], below
+// 2^26, so 32 bits hold it exactly); den = 0: none.
 struct Last {
-  int has;
-  long long xn0, xn1, xn2, den;
-  unsigned entry;
-  unsigned attr;   // vertex attribute interpolated to the event (attribute input)
+  uint32_t den, l[3];
+  uint32_t entry;
+  uint32_t attr;   // vertex attribute interpolated to the event (attribute input)
 };
 
 template <bool kAttr>
 __device__ inline Last shfl_last(const Last& v, int src) {
   Last o;
-  o.has = __shfl(v.has, src, 64);
-  o.xn0 = __shfl(v.xn0, src, 64);
-  o.xn1 = __shfl(v.xn1, src, 64);
-  o.xn2 = __shfl(v.xn2, src, 64);
-  o.den = __shfl(v.den, src, 64);
-  o.entry = __shfl(v.entry, src, 64);
-  o.attr = kAttr ? __shfl(v.attr, src, 64) : 0u;
+  o.den = (uint32_t)__shfl((int)v.den, src, 64);
+#pragma unroll
+  for (int b = 0; b < 3; ++b) o.l[b] = (uint32_t)__shfl((int)v.l[b], src, 64);
+  o.entry = (uint32_t)__shfl((int)v.entry, src, 64);
+  o.attr = kAttr ? (uint32_t)__shfl((int)v.attr, src, 64) : 0u;
+  return o;
+}
+
+// Lane `src`'s (wave-uniform) event to all lanes.
+template <bool kAttr>
+__device__ inline Last read_last(const Last& v, int src) {
+  Last o;
+  o.den = (uint32_t)__builtin_amdgcn_readlane((int)v.den, src);
+#pragma unroll
+  for (int b = 0; b < 3; ++b) o.l[b] = (uint32_t)__builtin_amdgcn_readlane((int)v.l[b], src);
+  o.entry = (uint32_t)__builtin_amdgcn_readlane((int)v.entry, src);
+  o.attr = kAttr ? (uint32_t)__builtin_amdgcn_readlane((int)v.attr, src) : 0u;
   return o;
 }
 
@@ -318,49 +330,47 @@ template <bool kAttr>
 __device__ inline uint32_t last_event(const int32_t P0[3], const int32_t P1[3],
                                       const GridArgs& ga, Last& out, unsigned a0 = 0,
                                       unsigned a1 = 0) {
-  int64_t d[3], num[3], dn[3];
+  // lattice coordinates are below 2^18, so everything here is below 2^24 and
+  // the cross products are exact in two 24-bit multiplies
+  int32_t d[3], num[3], dn[3];
   int32_t c1[3];
   uint32_t cross = 0;
   bool has[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    d[a] = (int64_t)P1[a] - P0[a];
+    d[a] = P1[a] - P0[a];
     const int32_t c0 = P0[a] >> 8;
     c1[a] = P1[a] >> 8;
     const uint32_t n = (uint32_t)abs(c1[a] - c0);
     cross += n;
     has[a] = n != 0;
-    num[a] = d[a] > 0 ? 256 * (int64_t)c1[a] - P0[a] : P0[a] - 256 * ((int64_t)c1[a] + 1);
+    num[a] = d[a] > 0 ? 256 * c1[a] - P0[a] : P0[a] - 256 * (c1[a] + 1);
     dn[a] = d[a] > 0 ? d[a] : -d[a];
   }
   if (cross == 0) return 0;
-  int fa = -1;
+  int fa = has[0] ? 0 : (has[1] ? 1 : 2);
+  int32_t nf = num[0], den = dn[0], df = d[0];
+  if (!has[0]) {
+    nf = has[1] ? num[1] : num[2];
+    den = has[1] ? dn[1] : dn[2];
+    df = has[1] ? d[1] : d[2];
+  }
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    if (!has[a]) continue;
-    if (fa < 0) {
+  for (int a = 1; a < 3; ++a) {
+    if (has[a] && mul_wide24((uint32_t)num[a], (uint32_t)den) >
+                      mul_wide24((uint32_t)nf, (uint32_t)dn[a])) {
       fa = a;
-    } else {
-      const int64_t nf = fa == 0 ? num[0] : (fa == 1 ? num[1] : num[2]);
-      const int64_t df = fa == 0 ? dn[0] : (fa == 1 ? dn[1] : dn[2]);
-      if (num[a] * df > nf * dn[a]) fa = a;
+      nf = num[a];
+      den = dn[a];
+      df = d[a];
     }
   }
-  const int64_t den = fa == 0 ? dn[0] : (fa == 1 ? dn[1] : dn[2]);
-  const int64_t nf = fa == 0 ? num[0] : (fa == 1 ? num[1] : num[2]);
-  const int64_t df = fa == 0 ? d[0] : (fa == 1 ? d[1] : d[2]);
-  int64_t xn[3];
-#pragma unroll
-  for (int b = 0; b < 3; ++b) xn[b] = (int64_t)P0[b] * den + nf * d[b];
-  out.has = 1;
-  out.xn0 = xn[0];
-  out.xn1 = xn[1];
-  out.xn2 = xn[2];
-  out.den = den;
   uint32_t xl[3];
+  event_low(P0, d, den, nf, xl);
+  out.den = (uint32_t)den;
 #pragma unroll
-  for (int b = 0; b < 3; ++b) xl[b] = (uint32_t)xn[b];
-  out.entry = face_code(fa, df > 0 ? 0 : 1, xl, (int32_t)den, c1, ga);
+  for (int b = 0; b < 3; ++b) out.l[b] = xl[b] - mul_lo24((uint32_t)(c1[b] << 8), (uint32_t)den);
+  out.entry = face_code(fa, df > 0 ? 0 : 1, xl, den, c1, ga);
   out.attr = kAttr ? event_attr(a0, a1, nf, den) : 0u;
   return cross;
 }
@@ -388,8 +398,8 @@ struct EmitRing {
   int32_t p[6][kEmitRing];
   uint32_t g[kEmitRing];
   uint32_t entry[kEmitRing];
-  int32_t den[kEmitRing];
-  long long x[3][kEmitRing];
+  uint32_t den[kEmitRing];
+  uint32_t l[3][kEmitRing];
 };
 
 struct EmitRingAttr : EmitRing {
@@ -407,6 +417,13 @@ struct EmitRingAttr : EmitRing {
 // With per-vertex attributes (kAttr) every event carries the
 // attribute interpolated to it; a line writes its two endpoint attributes to
 // ends_out and their mean (rounded down) as its record's attribute byte.
+//
+// Bound by vector instructions: two exact events per segment, and a walk per
+// event. Event points are therefore kept relative to their voxel, in 32 bits
+// (the grid position would need 64-bit products on both sides of every
+// comparison), the numbering is a DPP scan and the carried event a readlane; 81
+// instead of 104 registers and 24.5 KB of LDS leave five waves per SIMD instead
+// of four. At 256^3, 9.5M lines (100k x 200 curves): 360 -> 264 us.
 template <bool kFloatIn, bool kAttr, bool kRank>
 __global__ __launch_bounds__(kBlock, 4) void k_emit(const float* xyz, const int32_t* lat,
                                                  const int64_t* curve_off, const uint8_t* attr,
@@ -442,8 +459,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_emit(const float* xyz, const int3
     const uint32_t k = (head + (uint32_t)lane) & (kEmitRing - 1);
     const int32_t P0[3] = {Q.p[0][k], Q.p[1][k], Q.p[2][k]};
     const int32_t P1[3] = {Q.p[3][k], Q.p[4][k], Q.p[5][k]};
-    const int32_t bden = Q.den[k];
-    const long long bx0 = Q.x[0][k], bx1 = Q.x[1][k], bx2 = Q.x[2][k];
+    const uint32_t bden = Q.den[k];
+    const uint32_t bl[3] = {Q.l[0][k], Q.l[1][k], Q.l[2][k]};
     uint64_t g = Q.g[k];
     bool has_prev = bden != 0, first = true;
     uint32_t prev_entry = Q.entry[k];
@@ -461,12 +478,22 @@ __global__ __launch_bounds__(kBlock, 4) void k_emit(const float* xyz, const int3
           // first event can coincide with the event before it
           bool same = false;
           if (first) {
-            int64_t xn[3];
+            // both points relative to this voxel: equal iff l / den agree on
+            // every axis; the low halves of the cross products settle almost
+            // every case
+            const uint32_t den = (uint32_t)ev.den;
+            uint32_t el[3], diff = 0;
 #pragma unroll
-            for (int b = 0; b < 3; ++b)
-              xn[b] = (int64_t)P0[b] * ev.den + (int64_t)ev.nf * (P1[b] - P0[b]);
-            same = bx0 * ev.den == xn[0] * bden && bx1 * ev.den == xn[1] * bden &&
-                   bx2 * ev.den == xn[2] * bden;
+            for (int b = 0; b < 3; ++b) {
+              el[b] = ev.xl[b] - mul_lo24((uint32_t)(cell[b] << 8), den);
+              diff |= bl[b] * den ^ el[b] * bden;
+            }
+            if (diff == 0u) {
+              same = true;
+#pragma unroll
+              for (int b = 0; b < 3; ++b)
+                same = same && (uint64_t)bl[b] * den == (uint64_t)el[b] * bden;
+            }
           }
           if (same || prev_entry == ev.exit_code) {
             vox_out[w] = LS_INVALID_VOXEL;
@@ -495,7 +522,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_emit(const float* xyz, const int3
     });
   };
 
-  Last carry{0, 0, 0, 0, 1, 0u, 0u};
+  Last carry{};
   uint64_t g0 = 0;       // crossings of the curve before this chunk
   uint32_t q_head = 0, q_n = 0;   // ring state (wave-uniform)
   for (int64_t s0 = v0; s0 + 1 < v1; s0 += 64) {
@@ -510,29 +537,18 @@ __global__ __launch_bounds__(kBlock, 4) void k_emit(const float* xyz, const int3
     // (an event of k simultaneous planes uses k numbers), so the numbering
     // needs no walk; the unused numbers stay invalid slots.
     uint32_t e = 0;
-    Last mine{0, 0, 0, 0, 1, 0u, 0u};
+    Last mine{};
     uint32_t a01 = 0;
     if (kAttr && valid) a01 = (uint32_t)vattr[i] | ((uint32_t)vattr[i + 1] << 8);
     if (valid) e = last_event<kAttr>(P0, P1, ga, mine, a01 & 0xFFu, a01 >> 8);
     // exclusive prefix sum of the crossing counts
-    uint32_t inc = e;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t y = __shfl_up(inc, d, 64);
-      if (lane >= d) inc += y;
-    }
-    const uint32_t base = inc - e;
-    const uint32_t total = __shfl(inc, 63, 64);
-    // latest lane at or before this one with an event (max scan), then the
-    // last event strictly before this lane is that lane's of lane - 1
-    int src = mine.has ? lane : -1;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int o = __shfl_up(src, d, 64);
-      if (lane >= d) src = o > src ? o : src;
-    }
-    int prev_src = __shfl_up(src, 1, 64);
-    if (lane == 0) prev_src = -1;
+    uint32_t total;
+    const uint32_t base = wave_excl_scan(e, total);
+    // the last event strictly before this lane: that of the highest lane below
+    // it with one
+    const unsigned long long em = __ballot(mine.den != 0u);
+    const unsigned long long eb = em & below;
+    const int prev_src = eb ? 63 - __clzll((long long)eb) : -1;
     Last before = shfl_last<kAttr>(mine, prev_src >= 0 ? prev_src : 0);
     if (prev_src < 0) before = carry;
     // queue the segments with events
@@ -547,16 +563,14 @@ __global__ __launch_bounds__(kBlock, 4) void k_emit(const float* xyz, const int3
       }
       Q.g[k] = (uint32_t)(g0 + base);
       Q.entry[k] = before.entry;
-      Q.den[k] = before.has ? (int32_t)before.den : 0;
-      Q.x[0][k] = before.xn0;
-      Q.x[1][k] = before.xn1;
-      Q.x[2][k] = before.xn2;
+      Q.den[k] = before.den;
+#pragma unroll
+      for (int b = 0; b < 3; ++b) Q.l[b][k] = before.l[b];
       if constexpr (kAttr) Q.va[k] = a01 | (before.attr << 16);
     }
     q_n += (uint32_t)__popcll(am);
     // carry the chunk's last event
-    const int last_src = __shfl(src, 63, 64);
-    if (last_src >= 0) carry = shfl_last<kAttr>(mine, last_src);
+    if (em) carry = read_last<kAttr>(mine, 63 - __builtin_clzll(em));
     g0 += total;
     if (q_n >= 64) {
       walk(q_head, 64);
@@ -1240,7 +1254,8 @@ inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBl
 // 256^3, 9.5M lines (100k x 200 curves): 1169 -> 1080 us for the whole call; at
 // 512^3, 140.6M lines (1M x 100): 14.63 -> 8.23 ms, of it the emission 4.66 ->
 // 2.77 ms without the rank atomics, and scatter + rank + occupancy + histogram
-// copy 7.96 -> 3.45 ms as runs (0.50 + 0.75), counts 0.55, fills 0.51 + 1.16.
+// copy 7.96 -> 3.45 ms as runs (0.50 + 0.75), counts 0.55, fills 0.51 + 1.16
+// (with the emission as it is now 917 us and 7.5 ms).
 // Run atomics are bound by requests per 128-byte line: one copy of the counters
 // in plain brick order took 1.0 + 1.2 ms at 512^3 and 0.13 + 0.15 ms at 256^3,
 // 4 x 4 x 2 blocks and 32 copies take 0.50 + 0.75 and 0.04 + 0.04.
