@@ -1,31 +1,48 @@
 // Exclusive prefix sums (reduce-then-scan) and fill kernels for gfx950.
 //
-// A tile is 256 threads x 16 items. Pass 1 reduces each tile to one sum,
-// pass 2 scans the tile sums in one workgroup, pass 3 rescans each tile with
-// its offset. One tile needs pass 3 alone; up to kSumTiles tiles, pass 3 adds up
+// A tile is kThreads x 16 items. Pass 1 reduces each tile to one sum, pass 2
+// scans the tile sums in one workgroup, pass 3 rescans each tile with its
+// offset. One tile needs pass 3 alone; up to kSumTiles tiles, pass 3 adds up
 // the sums before its tile itself (a launch less; launches are what short scans
-// cost: 64^3 voxels 3 -> 2, 1000 curves 3 -> 1). Tiles are staged through LDS so global loads and stores stay
-// coalesced while each thread scans 16 consecutive items in registers.
+// cost: 64^3 voxels 3 -> 2, 1000 curves 3 -> 1).
+//
+// Bound by memory: each wave takes rows of 64 x 16 bytes, loaded and stored as
+// they lie, and scans the rows in registers (DPP moves for 32-bit items).
+// Against tiles of 4096 staged through LDS: 16.7M items (256^3) 48 -> 32 us,
+// 134M (512^3) 450 -> 300 us of kernels (5.3 TB/s).
 #include <cstring>
 
 #include "ls_internal.h"
+#include "wave.h"
 
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kItems = 16;
-constexpr int kTile = kThreads * kItems;
-constexpr int kWaves = kThreads / 64;
+constexpr int kItems = 16;       // per thread
+constexpr int kSmallThreads = 256;
+constexpr int kLargeThreads = 1024;
 
 template <typename T>
 __device__ inline T wave_inclusive_scan(T x) {
-  const int lane = threadIdx.x & 63;
+  if constexpr (sizeof(T) == 4) {
+    return wave_incl_sum(x);
+  } else {
+    const int lane = threadIdx.x & 63;
 #pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    T y = __shfl_up(x, d, 64);
-    if (lane >= d) x += y;
+    for (int d = 1; d < 64; d <<= 1) {
+      T y = __shfl_up(x, d, 64);
+      if (lane >= d) x += y;
+    }
+    return x;
   }
-  return x;
+}
+
+template <typename T>
+__device__ inline T wave_last(T x) {
+  return __shfl(x, 63, 64);
+}
+template <>
+__device__ inline uint32_t wave_last(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
 }
 
 template <typename T>
@@ -35,32 +52,55 @@ __device__ inline T wave_reduce(T x) {
   return x;
 }
 
-// Loads a tile into `items` in blocked order (thread t owns elements
-// t*kItems .. t*kItems + kItems - 1), via LDS, zero beyond n.
+// A thread's items: kRows rows of 16 bytes; a wave's row is 64 x 16 bytes in
+// memory, its rows follow one another. Zero beyond n.
 template <typename T>
-__device__ inline void load_tile(const T* in, int64_t base, int64_t n, T (&items)[kItems],
-                                 T* lds) {
-#pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    int64_t i = base + (int64_t)k * kThreads + threadIdx.x;
-    lds[k * kThreads + threadIdx.x] = i < n ? in[i] : T(0);
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < kItems; ++k) items[k] = lds[threadIdx.x * kItems + k];
-  __syncthreads();
-}
+struct Rows {
+  static constexpr int kPer = 16 / (int)sizeof(T);
+  static constexpr int kRows = kItems / kPer;
+  T v[kRows][kPer];
+};
 
 template <typename T>
-__global__ __launch_bounds__(kThreads) void k_tile_reduce(const T* in, int64_t n, T* sums) {
+__device__ inline int64_t row_index(int64_t base, int r) {
+  return base + (int64_t)(threadIdx.x >> 6) * (64 * kItems) +
+         (int64_t)(r * 64 + (int)(threadIdx.x & 63)) * Rows<T>::kPer;
+}
+
+// whole: all of the tile lies below n and the array is 16-byte aligned.
+template <typename T>
+__device__ inline void load_rows(const T* in, int64_t base, int64_t n, bool whole, Rows<T>& x) {
+  if (whole) {
+    uint4 q[Rows<T>::kRows];
+#pragma unroll
+    for (int r = 0; r < Rows<T>::kRows; ++r)
+      q[r] = *reinterpret_cast<const uint4*>(in + row_index<T>(base, r));
+#pragma unroll
+    for (int r = 0; r < Rows<T>::kRows; ++r) __builtin_memcpy(x.v[r], &q[r], 16);
+  } else {
+#pragma unroll
+    for (int r = 0; r < Rows<T>::kRows; ++r)
+#pragma unroll
+      for (int j = 0; j < Rows<T>::kPer; ++j) {
+        const int64_t i = row_index<T>(base, r) + j;
+        x.v[r][j] = i < n ? in[i] : T(0);
+      }
+  }
+}
+
+template <typename T, int kThreads>
+__global__ __launch_bounds__(kThreads) void k_tile_reduce(const T* in, int64_t n, bool aligned,
+                                                          T* sums) {
+  constexpr int kWaves = kThreads / 64;
   __shared__ T wsum[kWaves];
-  int64_t base = (int64_t)blockIdx.x * kTile;
+  const int64_t base = (int64_t)blockIdx.x * (kThreads * kItems);
+  Rows<T> x;
+  load_rows(in, base, n, aligned && base + kThreads * kItems <= n, x);
   T acc = 0;
 #pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    int64_t i = base + (int64_t)k * kThreads + threadIdx.x;
-    if (i < n) acc += in[i];
-  }
+  for (int r = 0; r < Rows<T>::kRows; ++r)
+#pragma unroll
+    for (int j = 0; j < Rows<T>::kPer; ++j) acc += x.v[r][j];
   acc = wave_reduce(acc);
   if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = acc;
   __syncthreads();
@@ -100,78 +140,116 @@ __global__ __launch_bounds__(1024) void k_scan_sums(T* sums, int64_t n, T* total
 // exclusive scan; the last tile then also writes the total to out[n].
 constexpr int kSumTiles = 1024;
 
-template <typename T, bool kSums>
+template <typename T, int kThreads, bool kSums>
 __global__ __launch_bounds__(kThreads) void k_tile_scan(const T* in, T* out, int64_t n,
-                                                        const T* tiles) {
-  __shared__ T lds[kTile];
-  __shared__ T wsum[kWaves];
-  int64_t base = (int64_t)blockIdx.x * kTile;
+                                                        bool aligned, const T* tiles) {
+  constexpr int kWaves = kThreads / 64;
+  constexpr int kRows = Rows<T>::kRows, kPer = Rows<T>::kPer;
+  __shared__ T wsum[kWaves], bsum[kWaves];
+  const int wave = threadIdx.x >> 6;
+  const int64_t base = (int64_t)blockIdx.x * (kThreads * kItems);
+  const bool whole = aligned && base + kThreads * kItems <= n;
+  Rows<T> x;
+  load_rows(in, base, n, whole, x);
   T before = 0;
   if (kSums && tiles) {
     for (unsigned t = threadIdx.x; t < blockIdx.x; t += kThreads) before += tiles[t];
     before = wave_reduce(before);
-    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = before;
-    __syncthreads();
-    before = 0;
-    for (int w = 0; w < kWaves; ++w) before += wsum[w];
-    __syncthreads();
   }
-  T items[kItems];
-  load_tile(in, base, n, items, lds);
-  T tsum = 0;
+  // exclusive scan within the wave, row by row
+  T total = 0;
 #pragma unroll
-  for (int k = 0; k < kItems; ++k) tsum += items[k];
-  T inc = wave_inclusive_scan(tsum);
-  if ((threadIdx.x & 63) == 63) wsum[threadIdx.x >> 6] = inc;
-  __syncthreads();
-  T pre = kSums ? before : tiles[blockIdx.x];
-  for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) pre += wsum[w];
-  pre += inc - tsum;
+  for (int r = 0; r < kRows; ++r) {
+    T own = 0;
 #pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    T x = items[k];
-    lds[threadIdx.x * kItems + k] = pre;
-    pre += x;
+    for (int j = 0; j < kPer; ++j) {
+      const T v = x.v[r][j];
+      x.v[r][j] = own;
+      own += v;
+    }
+    const T inc = wave_inclusive_scan(own);
+    const T pre = total + inc - own;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) x.v[r][j] += pre;
+    total += wave_last(inc);
   }
-  // items beyond n are 0: the last thread's running sum is the total
-  if (kSums && blockIdx.x == gridDim.x - 1 && threadIdx.x == kThreads - 1) out[n] = pre;
+  if ((threadIdx.x & 63) == 0) {
+    wsum[wave] = total;
+    bsum[wave] = before;
+  }
   __syncthreads();
+  T pre = kSums ? T(0) : tiles[blockIdx.x];
 #pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    int64_t i = base + (int64_t)k * kThreads + threadIdx.x;
-    if (i < n) out[i] = lds[k * kThreads + threadIdx.x];
+  for (int w = 0; w < kWaves; ++w) {
+    pre += w < wave ? wsum[w] : T(0);
+    if (kSums) pre += bsum[w];
+  }
+#pragma unroll
+  for (int r = 0; r < kRows; ++r)
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) x.v[r][j] += pre;
+  // items beyond n are 0: the last wave's running sum is the total
+  if (kSums && blockIdx.x == gridDim.x - 1 && threadIdx.x == kThreads - 1) out[n] = pre + total;
+  if (whole) {
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+      uint4 q;
+      __builtin_memcpy(&q, x.v[r], 16);
+      *reinterpret_cast<uint4*>(out + row_index<T>(base, r)) = q;
+    }
+  } else {
+#pragma unroll
+    for (int r = 0; r < kRows; ++r)
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        const int64_t i = row_index<T>(base, r) + j;
+        if (i < n) out[i] = x.v[r][j];
+      }
   }
 }
 
-template <typename T>
-int scan_impl(const T* in, T* out, int64_t n, T* sums, hipStream_t st) {
-  int64_t tiles = (n + kTile - 1) / kTile;
-  if (tiles == 0) {
-    // total of an empty range
-    hipLaunchKernelGGL((k_scan_sums<T>), dim3(1), dim3(1024), 0, st, sums, (int64_t)0, out);
-    LS_HIP(hipGetLastError());
-    return LS_OK;
-  }
+template <typename T, int kThreads>
+int scan_tiles(const T* in, T* out, int64_t n, T* sums, hipStream_t st) {
+  const int64_t tiles = (n + kThreads * kItems - 1) / (kThreads * kItems);
+  const bool aligned =
+      ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
+  const dim3 grid((unsigned)tiles), block(kThreads);
   if (tiles == 1) {
-    hipLaunchKernelGGL((k_tile_scan<T, true>), dim3(1), dim3(kThreads), 0, st, in, out, n,
+    hipLaunchKernelGGL((k_tile_scan<T, kThreads, true>), grid, block, 0, st, in, out, n, aligned,
                        (const T*)nullptr);
     LS_HIP(hipGetLastError());
     return LS_OK;
   }
-  hipLaunchKernelGGL((k_tile_reduce<T>), dim3((unsigned)tiles), dim3(kThreads), 0, st, in, n, sums);
+  hipLaunchKernelGGL((k_tile_reduce<T, kThreads>), grid, block, 0, st, in, n, aligned, sums);
   LS_HIP(hipGetLastError());
   if (tiles <= kSumTiles) {
-    hipLaunchKernelGGL((k_tile_scan<T, true>), dim3((unsigned)tiles), dim3(kThreads), 0, st, in,
-                       out, n, (const T*)sums);
+    hipLaunchKernelGGL((k_tile_scan<T, kThreads, true>), grid, block, 0, st, in, out, n, aligned,
+                       (const T*)sums);
     LS_HIP(hipGetLastError());
     return LS_OK;
   }
   hipLaunchKernelGGL((k_scan_sums<T>), dim3(1), dim3(1024), 0, st, sums, tiles, out + n);
   LS_HIP(hipGetLastError());
-  hipLaunchKernelGGL((k_tile_scan<T, false>), dim3((unsigned)tiles), dim3(kThreads), 0, st, in, out, n,
+  hipLaunchKernelGGL((k_tile_scan<T, kThreads, false>), grid, block, 0, st, in, out, n, aligned,
                      (const T*)sums);
   LS_HIP(hipGetLastError());
   return LS_OK;
+}
+
+// Large tiles once small ones would be more than kSumTiles: 16.7M items then
+// need two launches instead of three and a short sum; below, small tiles fill
+// more of the chip.
+template <typename T>
+int scan_impl(const T* in, T* out, int64_t n, T* sums, hipStream_t st) {
+  if (n <= 0) {
+    // total of an empty range
+    hipLaunchKernelGGL((k_scan_sums<T>), dim3(1), dim3(1024), 0, st, sums, (int64_t)0, out);
+    LS_HIP(hipGetLastError());
+    return LS_OK;
+  }
+  if (n <= (int64_t)kSumTiles * kSmallThreads * kItems)
+    return scan_tiles<T, kSmallThreads>(in, out, n, sums, st);
+  return scan_tiles<T, kLargeThreads>(in, out, n, sums, st);
 }
 
 __global__ void k_fill_u32(uint32_t* p, uint32_t v, int64_t n) {
@@ -195,7 +273,9 @@ __global__ void k_read_words(const uint32_t* src, uint32_t* dst, int n) {
 
 }  // namespace
 
-int64_t scan_block_sums_len(int64_t n) { return (n + kTile - 1) / kTile + 1; }
+int64_t scan_block_sums_len(int64_t n) {
+  return (n + kSmallThreads * kItems - 1) / (kSmallThreads * kItems) + 1;
+}
 
 int exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* sums,
                        hipStream_t st) {
