@@ -149,6 +149,10 @@ constexpr int kWavesPerBlock = kBlock / 64;
 
 // Per-curve count of line slots: plane crossings - 1 (an upper bound of the
 // lines; simultaneous crossings merge into one event). Validates the input.
+// Bound by reading the vertices and by the snap's fp64 instructions, so each is
+// loaded and snapped once and its neighbour comes by a DPP move: 20M vertices
+// 73 -> 54 us, 100M 441 -> 352 us. (In the emission, whose own work hides the
+// loads, the same made no difference.)
 template <bool kFloatIn>
 __global__ __launch_bounds__(kBlock) void k_count(const float* xyz, const int32_t* lat,
                                                   const int64_t* curve_off, int64_t n_curves,
@@ -168,27 +172,29 @@ __global__ __launch_bounds__(kBlock) void k_count(const float* xyz, const int32_
   }
   unsigned long long crossings = 0;
   bool bad = false;
-  // two 64-vertex chunks per pass, every load issued before any is used;
-  // indices are clamped to the curve's last vertex (v1 > v0 inside the loop)
-  // so the loads need no branch, and clamped lanes add nothing
-  for (int64_t s0 = v0; s0 < v1; s0 += 128) {
-    int32_t q[2][3], r[2][3];
+  // 128 vertices per pass, loaded and snapped once, the next one's read from
+  // the next lane; the pass's last vertex is the next pass's first. Indices are
+  // clamped to the curve's last vertex (v1 > v0 inside the loop), so the loads
+  // need no branch, and a repeated vertex adds nothing.
+  for (int64_t s0 = v0; s0 + 1 < v1 || (s0 == v0 && v0 < v1); s0 += 127) {
+    int32_t q[2][3];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int64_t v = s0 + 64 * h + lane;
       load_vertex<kFloatIn>(xyz, lat, v < v1 ? v : v1 - 1, sa, q[h]);
-      load_vertex<kFloatIn>(xyz, lat, v + 1 < v1 ? v + 1 : v1 - 1, sa, r[h]);
     }
+    uint32_t n = 0;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int64_t v = s0 + 64 * h + lane;
-      if (v < v1) bad |= !in_range(q[h], ga);
-      if (v + 1 < v1) {
+      bad |= !in_range(q[h], ga);
 #pragma unroll
-        for (int a = 0; a < 3; ++a)
-          crossings += (unsigned long long)abs((r[h][a] >> 8) - (q[h][a] >> 8));
+      for (int a = 0; a < 3; ++a) {
+        const int32_t k = q[h][a] >> 8;
+        const int32_t last = h == 0 ? __builtin_amdgcn_readfirstlane(q[1][a] >> 8) : k;
+        n += (uint32_t)abs(wave_next(k, last) - k);
       }
     }
+    crossings += n;
   }
   if (bad) atomicOr(err, kErrRange);
 #pragma unroll
@@ -1255,7 +1261,7 @@ inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBl
 // 512^3, 140.6M lines (1M x 100): 14.63 -> 8.23 ms, of it the emission 4.66 ->
 // 2.77 ms without the rank atomics, and scatter + rank + occupancy + histogram
 // copy 7.96 -> 3.45 ms as runs (0.50 + 0.75), counts 0.55, fills 0.51 + 1.16
-// (with the emission as it is now 917 us and 7.5 ms).
+// (with counting, emission and scans as they are now 870 us and 7.35 ms).
 // Run atomics are bound by requests per 128-byte line: one copy of the counters
 // in plain brick order took 1.0 + 1.2 ms at 512^3 and 0.13 + 0.15 ms at 256^3,
 // 4 x 4 x 2 blocks and 32 copies take 0.50 + 0.75 and 0.04 + 0.04.

@@ -44,6 +44,11 @@ __device__ inline uint32_t wave_excl_scan(uint32_t v, uint32_t& total) {
   return inc - v;
 }
 
+// The next lane's value; `last` (wave-uniform) in lane 63.
+__device__ inline int32_t wave_next(int32_t v, int32_t last) {
+  return __builtin_amdgcn_update_dpp(last, v, 0x130, 0xF, 0xF, false);   // wave_shl 1
+}
+
 // Inclusive sum over the lanes [seg0, lane], seg0 the same for the lanes of one
 // contiguous segment.
 template <int kCtrl, int kRows>
