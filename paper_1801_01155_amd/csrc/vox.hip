@@ -648,7 +648,15 @@ __global__ __launch_bounds__(kBlock) void k_rank(const uint64_t* idx, const uint
 // load tells the ray caster which voxels of the macro cell it can skip
 // (a zero word: the whole macro cell). The same pass counts the non-empty
 // voxels and the longest list (wave and block reduction, one atomic each per
-// workgroup).
+// workgroup; these, at some 10 ns each on one line, bound it from 128^3 on, so
+// more lanes per cell only lose there: 128^3 106 -> 112 us for the whole call
+// with four). Grids of up to kOccFew cells leave the chip idle with a lane per
+// cell: four lanes share one (64^3: 123 -> 118 us for the whole call). Rows
+// that end at a side that is no multiple of 4 are five clamped loads issued
+// together (201x97x130: 178 -> 170 us, against a test and two loads per voxel).
+constexpr int64_t kOccFew = 8192;
+
+template <int kLanes>
 __global__ __launch_bounds__(kBlock) void k_occupancy(const uint32_t* offsets, GridArgs ga,
                                                       int32_t mx, int32_t my, int32_t mz,
                                                       unsigned long long* occ,
@@ -656,44 +664,49 @@ __global__ __launch_bounds__(kBlock) void k_occupancy(const uint32_t* offsets, G
                                                       unsigned int* max_list) {
   __shared__ unsigned long long s_ne[kBlock / 64];
   __shared__ unsigned s_mx[kBlock / 64];
-  int64_t m = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  int64_t nm = (int64_t)mx * my * mz;
-  unsigned long long ne = 0;
+  constexpr int kCells = 64 / kLanes, kRows = 16 / kLanes;   // per wave, per lane
+  const int lane = threadIdx.x & 63, part = lane / kCells;
+  const int64_t wave = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  const int64_t m = wave * kCells + (lane & (kCells - 1));
+  const int64_t nm = (int64_t)mx * my * mz;
+  unsigned long long bits = 0;
   unsigned mxl = 0;
   if (m < nm) {
-    int32_t bx = (int32_t)(m % mx), by = (int32_t)((m / mx) % my),
-            bz = (int32_t)(m / ((int64_t)mx * my));
-    unsigned long long bits = 0;
-    if ((ga.g[0] & 3) == 0) {
-      // whole macro cells along x: a row of 4 voxels is one aligned 16-byte
-      // load of their offsets plus the next row start
+    const int32_t bx = (int32_t)(m % mx), by = (int32_t)((m / mx) % my),
+                  bz = (int32_t)(m / ((int64_t)mx * my));
+    const int w = ga.g[0] - 4 * bx;   // voxels of the cell's rows below the side
 #pragma unroll 4
-      for (int r = 0; r < 16; ++r) {
-        const int32_t y = 4 * by + (r & 3), z = 4 * bz + (r >> 2);
-        if (y >= ga.g[1] || z >= ga.g[2]) continue;
-        const int64_t v = 4 * (int64_t)bx + (int64_t)ga.g[0] * (y + (int64_t)ga.g[1] * z);
+    for (int k = 0; k < kRows; ++k) {
+      const int r = part * kRows + k;
+      const int32_t y = 4 * by + (r & 3), z = 4 * bz + (r >> 2);
+      if (y >= ga.g[1] || z >= ga.g[2]) continue;
+      const int64_t v = 4 * (int64_t)bx + (int64_t)ga.g[0] * (y + (int64_t)ga.g[1] * z);
+      uint32_t o[5];
+      if ((ga.g[0] & 3) == 0) {
+        // whole macro cells along x: the row of 4 voxels is one aligned
+        // 16-byte load of their offsets plus the next row start
         const uint4 a = *reinterpret_cast<const uint4*>(offsets + v);
-        const uint32_t e = offsets[v + 4];
-        const unsigned n[4] = {a.y - a.x, a.z - a.y, a.w - a.z, e - a.w};
+        o[0] = a.x;
+        o[1] = a.y;
+        o[2] = a.z;
+        o[3] = a.w;
+        o[4] = offsets[v + 4];
+      } else {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          if (n[c] > 0) bits |= 1ull << (4 * r + c);
-          mxl = n[c] > mxl ? n[c] : mxl;
-        }
+        for (int c = 0; c < 5; ++c) o[c] = offsets[v + (c < w ? c : w)];
       }
-    } else {
-      for (int k = 0; k < 64; ++k) {
-        const int32_t x = 4 * bx + (k & 3), y = 4 * by + ((k >> 2) & 3), z = 4 * bz + (k >> 4);
-        if (x >= ga.g[0] || y >= ga.g[1] || z >= ga.g[2]) continue;
-        const int64_t v = x + (int64_t)ga.g[0] * (y + (int64_t)ga.g[1] * z);
-        const unsigned n = offsets[v + 1] - offsets[v];
-        if (n > 0) bits |= 1ull << k;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const unsigned n = o[c + 1] - o[c];
+        if (n > 0) bits |= 1ull << (4 * r + c);
         mxl = n > mxl ? n : mxl;
       }
     }
-    occ[m] = bits;
-    ne = (unsigned long long)__popcll(bits);
   }
+  unsigned long long ne = (unsigned long long)__popcll(bits);
+#pragma unroll
+  for (int d = kCells; d < 64; d <<= 1) bits |= __shfl_xor(bits, d, 64);
+  if (part == 0 && m < nm) occ[m] = bits;
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) {
     ne += __shfl_xor(ne, d, 64);
@@ -1631,10 +1644,16 @@ int vox_occupancy(ls_lineset* s, hipStream_t st, bool cleared) {
   const int64_t nm = (int64_t)s->macro[0] * s->macro[1] * s->macro[2];
   char* stats = reinterpret_cast<char*>(s->occupancy + nm);
   if (!cleared && (rc = fill_u32(reinterpret_cast<uint32_t*>(stats), 0u, 4, st))) return rc;
-  hipLaunchKernelGGL(k_occupancy, dim3(blocks_for(nm)), dim3(kBlock), 0, st, s->offsets, ga,
-                     s->macro[0], s->macro[1], s->macro[2], (unsigned long long*)s->occupancy,
-                     reinterpret_cast<unsigned long long*>(stats),
-                     reinterpret_cast<unsigned int*>(stats + 8));
+  auto launch = [&](auto kernel, int lanes) {
+    hipLaunchKernelGGL(kernel, dim3(blocks_for(nm * lanes)), dim3(kBlock), 0, st, s->offsets, ga,
+                       s->macro[0], s->macro[1], s->macro[2], (unsigned long long*)s->occupancy,
+                       reinterpret_cast<unsigned long long*>(stats),
+                       reinterpret_cast<unsigned int*>(stats + 8));
+  };
+  if (nm <= kOccFew)
+    launch(k_occupancy<4>, 4);
+  else
+    launch(k_occupancy<1>, 1);
   LS_HIP(hipGetLastError());
   s->stats_pending = true;
   return LS_OK;
