@@ -307,7 +307,10 @@ typedef struct {
  * keeps, per (device, stream), the tile times of the stream's last 64 such
  * views (4 bytes per tile each), one ordering buffer and, after a mode 1
  * frame, one buffer of 8 bytes per 4^3 voxels of its grid, until the process
- * ends; enlarging them synchronises the stream once. */
+ * ends; enlarging them synchronises the stream once. Frames of several threads
+ * on one stream may use them; frames under capture and on hipStreamPerThread
+ * use none of this (their tiles start in the order of the rings around the
+ * grid's centre). */
 int lineset_render(ls_lineset_t set, const ls_camera* cam, const ls_render_params* params,
                    float* rgba_out, void* hip_stream);
 

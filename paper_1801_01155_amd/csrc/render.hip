@@ -2322,7 +2322,9 @@ namespace {
 // Launch-order state per (device, stream): the tile times of the stream's
 // last kOrderViews distinct views (least recently used replaced), and one
 // work buffer (bucket counters, per-tile buckets, the order). Work queued on
-// one stream runs in order, so its frames share these buffers. A buffer that
+// one stream runs in order, so its frames share these buffers; the lock is held
+// from a frame's first use of them until its last kernel is queued, so frames of
+// several threads on one stream do not queue between each other's. A buffer that
 // must grow is replaced after synchronising the stream; all are kept until
 // the process ends.
 constexpr int kOrderViews = 64;
@@ -2388,6 +2390,21 @@ struct StreamOrder {
 std::mutex g_order_mu;
 std::map<std::pair<int, hipStream_t>, StreamOrder> g_order;
 
+// False where a frame must not use its stream's buffers: under capture (the
+// graph may be replayed on another stream, beside that stream's frames or after
+// a buffer was replaced) and on hipStreamPerThread (one handle for the streams
+// of all threads). Its tiles then start in the order of the rings, and the
+// neighbour mode's kernel forms the grown words itself.
+bool keeps_order(hipStream_t st) {
+  if (st == hipStreamPerThread) return false;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return cs == hipStreamCaptureStatusNone;
+}
+
 // Replaces *p (after synchronising st) by a block of at least `bytes`.
 int grow(void** p, size_t* have, size_t bytes, hipStream_t st) {
   if (*have >= bytes) return LS_OK;
@@ -2448,13 +2465,15 @@ bool split_small(RenderArgs& R, int resident) {
 // Plain frames with more workgroups than the device holds at once: tile
 // times are measured, and a frame of a view the stream rendered before (same
 // set shape, image, camera and parameters), or of one with the camera moved
-// slightly, is launched in the order of those times.
+// slightly, is launched in the order of those times. lk: left locked if the
+// frame uses the stream's buffers.
 int tile_order(const ls_lineset* s, const ls_camera* cam, const ls_render_params* p,
-               RenderArgs& R, hipStream_t st) {
+               RenderArgs& R, hipStream_t st, std::unique_lock<std::mutex>& lk) {
   int resident = 0, rc;
   if ((rc = resident_blocks(R, &resident))) return rc;
   if (split_small(R, resident)) return LS_OK;
   if ((int64_t)R.n_tiles + (int64_t)R.split_n * (R.split_s - 1) <= resident) return LS_OK;
+  if (!keeps_order(st)) return LS_OK;
   OrderKey key;
   std::memset(&key, 0, sizeof(key));
   for (int a = 0; a < 3; ++a) key.grid[a] = s->grid[a];
@@ -2465,7 +2484,7 @@ int tile_order(const ls_lineset* s, const ls_camera* cam, const ls_render_params
   int dev = 0;
   LS_HIP(hipGetDevice(&dev));
   const int64_t n = R.n_tiles;
-  std::lock_guard<std::mutex> lk(g_order_mu);
+  if (!lk.owns_lock()) lk.lock();
   StreamOrder& so = g_order[{dev, st}];
   ++so.clock;
   int v = -1;
@@ -2552,19 +2571,14 @@ int tile_order(const ls_lineset* s, const ls_camera* cam, const ls_render_params
 namespace {
 
 // Neighbour-mode frames: the grown occupancy of the set, formed anew for each
-// frame (the set may have changed) in the stream's buffer. Not under capture:
-// a graph may be replayed after the buffer was replaced, so there the kernel
-// forms the words itself.
-int grow_occupancy(RenderArgs& R, hipStream_t st) {
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    return LS_OK;
-  }
+// frame (the set may have changed) in the stream's buffer. lk: left locked if the
+// frame uses it.
+int grow_occupancy(RenderArgs& R, hipStream_t st, std::unique_lock<std::mutex>& lk) {
+  if (!keeps_order(st)) return LS_OK;
   const int64_t nm = (int64_t)R.mg[0] * R.mg[1] * R.mg[2];
   int dev = 0, rc;
   LS_HIP(hipGetDevice(&dev));
-  std::lock_guard<std::mutex> lk(g_order_mu);
+  if (!lk.owns_lock()) lk.lock();
   StreamOrder& so = g_order[{dev, st}];
   if ((rc = grow(&so.grown, &so.grown_bytes, sizeof(uint64_t) * nm, st))) return rc;
   unsigned long long* g = static_cast<unsigned long long*>(so.grown);
@@ -2582,8 +2596,10 @@ int render_frame(const ls_lineset* s, const ls_camera* cam, const ls_render_para
   RenderArgs R;
   make_render_args(s, cam, p, out, 1, 1, dev_counters, &R);
   int rc;
-  if (R.mode != 0 && (rc = grow_occupancy(R, st))) return rc;
-  if (R.spiral_r >= 0 && (rc = tile_order(s, cam, p, R, st))) return rc;
+  // held until the frame is queued: its kernels read the stream's buffers
+  std::unique_lock<std::mutex> lk(g_order_mu, std::defer_lock);
+  if (R.mode != 0 && (rc = grow_occupancy(R, st, lk))) return rc;
+  if (R.spiral_r >= 0 && (rc = tile_order(s, cam, p, R, st, lk))) return rc;
   return launch_render(R, st);
 }
 
