@@ -2264,7 +2264,7 @@ int make_render_args(const ls_lineset* s, const ls_camera* cam, const ls_render_
       if (wx == 1 && wy == 1 && !R.opaque && std::isfinite(r_tiles) &&
           work <= kSplitMaxWork) {
         const int rs = (int)std::min(kSplitFrac * r_tiles, (double)R.spiral_r);
-        R.split_n = (2 * rs + 1) * (2 * rs + 1);
+        R.split_n = (int)std::min<int64_t>((2 * (int64_t)rs + 1) * (2 * (int64_t)rs + 1), 1 << 28);
         R.split_s = work <= kSplit4MaxWork ? 4 : 2;
       }
     }
@@ -2474,6 +2474,9 @@ int tile_order(const ls_lineset* s, const ls_camera* cam, const ls_render_params
   if (split_small(R, resident)) return LS_OK;
   if ((int64_t)R.n_tiles + (int64_t)R.split_n * (R.split_s - 1) <= resident) return LS_OK;
   if (!keeps_order(st)) return LS_OK;
+  // an ordered frame has a position per tile; the split rings (of an image much
+  // longer than wide, or with the grid's centre at its edge) may hold more places
+  R.split_n = std::min(R.split_n, R.n_tiles);
   OrderKey key;
   std::memset(&key, 0, sizeof(key));
   for (int a = 0; a < 3; ++a) key.grid[a] = s->grid[a];
