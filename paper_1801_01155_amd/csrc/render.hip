@@ -1816,16 +1816,53 @@ __device__ inline void load_lut(const RenderArgs& R, float4* lut_lds) {
     lut_lds[k] = reinterpret_cast<const float4*>(R.lut)[k];
 }
 
+// Tile at position b of the ring order. The rings lie around the projection of the
+// grid centre, where rays cross the most voxels: the costliest tiles start first
+// instead of setting the frame's tail (256x256, split all 16 ways: 75 us; rows
+// outwards from the centre 89). A ring's places outside the image have no
+// position, so the launch is as large as the image however long it is or wherever
+// the centre lies.
+__device__ inline int ring_tile(const RenderArgs& R, int b) {
+  const int cx = R.spiral_x, cy = R.spiral_y, tx = R.tiles_x, ty = R.n_tiles / R.tiles_x;
+  int r = 0, last = R.spiral_r;   // the first ring that ends beyond position b
+  while (r < last) {
+    const int mid = (r + last) >> 1;
+    if (ring_tiles(cx, cy, tx, ty, mid) > b) last = mid;
+    else r = mid + 1;
+  }
+  if (r == 0) return cy * tx + cx;
+  int k = b - ring_tiles(cx, cy, tx, ty, r - 1);
+  // its sides inside the image: x = cx + r, y = cy + r, x = cx - r, y = cy - r,
+  // each without the corner that the side before it holds
+  const int xa = max(cx - r, 0), ya = max(cy - r, 0), yb = min(cy + r, ty - 1);
+  if (cx + r < tx) {
+    const int y0 = max(cy - r + 1, 0), n = yb - y0 + 1;
+    if (k < n) return (y0 + k) * tx + cx + r;
+    k -= n;
+  }
+  if (cy + r < ty) {
+    const int x1 = min(cx + r - 1, tx - 1), n = x1 - xa + 1;
+    if (k < n) return (cy + r) * tx + x1 - k;
+    k -= n;
+  }
+  if (cx - r >= 0) {
+    const int y1 = min(cy + r - 1, ty - 1), n = y1 - ya + 1;
+    if (k < n) return (y1 - k) * tx + cx - r;
+    k -= n;
+  }
+  return (cy - r) * tx + max(cx - r + 1, 0) + k;
+}
+
 template <int kMode, bool kCount, bool kVdi, bool kOpaque>
 __global__ __launch_bounds__(kBlock, kMode == 1 ? 2 : 1) void k_render(RenderArgs R) {
   const unsigned long long t_start = R.times ? wall_clock64() : 0ull;
   int b = blockIdx.x;
   int tile;
   bool live;
-  int sub = 0, nsub = 1;   // sub-tile (rows sub * 8 / nsub ...) of a split tile
+  int sub = 0, nsub = 1;   // part of a split tile: its pixels from sub * 64 / nsub on
   if (R.spiral_r >= 0) {
     // launch positions: the first top_n tiles (the longest measured ones of
-    // an ordered frame) split four ways, the next split_n split_s ways, the
+    // an ordered frame) split top_s ways, the next split_n split_s ways, the
     // rest whole; in groups of kXcds tiles x nsub parts, as workgroups are
     // dealt to the XCDs round-robin, so in a full group the parts of a tile
     // share an XCD (and its L2) as its lists are read again
@@ -1858,34 +1895,8 @@ __global__ __launch_bounds__(kBlock, kMode == 1 ? 2 : 1) void k_render(RenderArg
       tile = R.order[b];
       live = tile >= 0 && tile < R.n_tiles;
     } else {
-    // Tiles in square rings around the projection of the grid centre, where
-    // rays cross the most voxels: the costliest tiles start first instead of
-    // setting the frame's tail. Ring r holds workgroups [(2r-1)^2, (2r+1)^2).
-    int s = (int)sqrtf((float)b);
-    while (s * s > b) --s;
-    while ((s + 1) * (s + 1) <= b) ++s;
-    const int r = (s + 1) / 2;
-    int dx = 0, dy = 0;
-    if (r > 0) {
-      const int k = b - (2 * r - 1) * (2 * r - 1), side = 2 * r;
-      if (k < side) {
-        dx = r;
-        dy = -r + 1 + k;
-      } else if (k < 2 * side) {
-        dx = r - 1 - (k - side);
-        dy = r;
-      } else if (k < 3 * side) {
-        dx = -r;
-        dy = r - 1 - (k - 2 * side);
-      } else {
-        dx = -r + 1 + (k - 3 * side);
-        dy = -r;
-      }
-    }
-    const int tx = R.spiral_x + dx, ty = R.spiral_y + dy;
-    const int tiles_y = R.n_tiles / R.tiles_x;
-    live = tx >= 0 && ty >= 0 && tx < R.tiles_x && ty < tiles_y;
-    tile = ty * R.tiles_x + tx;
+      tile = ring_tile(R, b);
+      live = true;
     }
   } else {
     // Workgroup b runs on XCD b % 8. XCD x renders the tile rows x, x + 8,
@@ -2264,7 +2275,7 @@ int make_render_args(const ls_lineset* s, const ls_camera* cam, const ls_render_
       if (wx == 1 && wy == 1 && !R.opaque && std::isfinite(r_tiles) &&
           work <= kSplitMaxWork) {
         const int rs = (int)std::min(kSplitFrac * r_tiles, (double)R.spiral_r);
-        R.split_n = (int)std::min<int64_t>((2 * (int64_t)rs + 1) * (2 * (int64_t)rs + 1), 1 << 28);
+        R.split_n = ring_tiles(cx, cy, R.tiles_x, ty_n, rs);
         R.split_s = work <= kSplit4MaxWork ? 4 : 2;
       }
     }
@@ -2306,10 +2317,9 @@ size_t render_lds_bytes(const RenderArgs& R, unsigned threads) {
 int launch_render(const RenderArgs& R, hipStream_t st) {
   const int tiles_y = R.n_tiles / R.tiles_x;
   const unsigned blocks =
-      R.order ? (unsigned)(R.n_tiles + (R.top_s - 1) * R.top_n + R.split_n * (R.split_s - 1))
-      : R.spiral_r >= 0 ? (unsigned)((2 * R.spiral_r + 1) * (2 * R.spiral_r + 1) +
-                                     R.split_n * (R.split_s - 1))
-                        : (unsigned)(kXcds * ((tiles_y + kXcds - 1) / kXcds) * R.tiles_x);
+      R.spiral_r >= 0 ? (unsigned)(R.n_tiles + (R.top_s - 1) * R.top_n +
+                                   R.split_n * (R.split_s - 1))
+                      : (unsigned)(kXcds * ((tiles_y + kXcds - 1) / kXcds) * R.tiles_x);
   const unsigned threads = (unsigned)(64 * R.wx * R.wy);
   const dim3 grid(blocks), block(threads);
   hipLaunchKernelGGL(render_kernel(R), grid, block, render_lds_bytes(R, threads), st, R);
@@ -2458,7 +2468,7 @@ bool split_small(RenderArgs& R, int resident) {
   while (s < 64 && 2 * s * (int64_t)R.n_tiles <= most) s *= 2;
   if (s < kSmallSplit || s <= R.split_s) return false;
   R.split_s = s;
-  R.split_n = (2 * R.spiral_r + 1) * (2 * R.spiral_r + 1);
+  R.split_n = R.n_tiles;
   return true;
 }
 
@@ -2474,9 +2484,6 @@ int tile_order(const ls_lineset* s, const ls_camera* cam, const ls_render_params
   if (split_small(R, resident)) return LS_OK;
   if ((int64_t)R.n_tiles + (int64_t)R.split_n * (R.split_s - 1) <= resident) return LS_OK;
   if (!keeps_order(st)) return LS_OK;
-  // an ordered frame has a position per tile; the split rings (of an image much
-  // longer than wide, or with the grid's centre at its edge) may hold more places
-  R.split_n = std::min(R.split_n, R.n_tiles);
   OrderKey key;
   std::memset(&key, 0, sizeof(key));
   for (int a = 0; a < 3; ++a) key.grid[a] = s->grid[a];

@@ -40,9 +40,9 @@ struct RenderArgs {
   RenderCounters* counters;
   int32_t wx, wy;                 // tile = wx x wy waves of 8 x 8 pixels
   int32_t tiles_x, n_tiles, tiles_per_xcd;
-  // plain launch order: tiles in square rings around the tile (spiral_x,
-  // spiral_y) out to ring spiral_r, or rows interleaved over the XCDs when
-  // spiral_r < 0
+  // plain launch order: the image's tiles in square rings around the tile
+  // (spiral_x, spiral_y) out to ring spiral_r, or rows interleaved over the XCDs
+  // when spiral_r < 0
   int32_t spiral_x, spiral_y, spiral_r;
   // the tiles of the first split_n spiral positions (the innermost rings)
   // are rendered by split_s workgroups each, on 64 / split_s of its pixels, so
@@ -75,6 +75,14 @@ struct BatchPlan {
 // waves); a line each, they are the fastest: 2.42 against 2.57 ms (40 views of
 // two sets 2.32 against 2.53; 4 small views the same).
 constexpr BatchPlan kDefaultPlan{1, 1, 0};
+
+// Tiles of an image of tx x ty tiles within the square rings 0 .. r around the
+// tile (x, y).
+__host__ __device__ inline int ring_tiles(int x, int y, int tx, int ty, int r) {
+  const int x0 = x < r ? x : r, x1 = tx - 1 - x < r ? tx - 1 - x : r;
+  const int y0 = y < r ? y : r, y1 = ty - 1 - y < r ? ty - 1 - y : r;
+  return (x0 + x1 + 1) * (y0 + y1 + 1);
+}
 
 int make_render_args(const ls_lineset* s, const ls_camera* cam, const ls_render_params* p,
                      float* out, int wx, int wy, RenderCounters* dev_counters, RenderArgs* R);

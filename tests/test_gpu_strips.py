@@ -54,3 +54,12 @@ def _check(lines, w, h, opaque, mode, shift, ortho):
 @pytest.mark.parametrize("shift,ortho", [(0.0, True), (1.0, True), (1.0, False)])
 def test_ordered_strips(lines, w, h, shift, ortho):
     _check(lines, w, h, False, 1, shift, ortho)
+
+
+# small frames split all their tiles; longer strips are whole or ordered
+@pytest.mark.parametrize("w,h", [(4096, 8), (8, 4096), (2048, 61), (32768, 8), (16384, 5),
+                                 (256, 256), (401, 300)])
+@pytest.mark.parametrize("opaque,mode", [(True, 0), (False, 0), (True, 1)])
+@pytest.mark.parametrize("shift,ortho", [(0.0, True), (1.0, True), (1.0, False)])
+def test_strips_and_edges(lines, w, h, opaque, mode, shift, ortho):
+    _check(lines, w, h, opaque, mode, shift, ortho)
