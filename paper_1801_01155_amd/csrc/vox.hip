@@ -412,6 +412,14 @@ struct EmitRingAttr : EmitRing {
   uint32_t va[kEmitRing];   // a0 | a1 << 8 | (attribute at the event before) << 16
 };
 
+// LDS of a k_emit workgroup that takes ranks: a quarter of a CU's 160 KB, so four
+// waves run per SIMD. Its returning atomics are what it waits for, and from six
+// waves on (what its rings leave room for) they hold each other up. Whole call with
+// 6, 5, 4, 3 waves: 14.2M lines in 64^3 1505, 1420, 1267, 1202 us; 19.8M in 160^3
+// 1844, 1665, 1581, 1597; few lines in large grids are a little faster with more
+// (3.9M in 512^3 1099, 1102, 1106, 1116).
+constexpr size_t kEmitRankLds = 40960;
+
 // Lines of every curve in curve order: the line inside a voxel runs from
 // one event's entry point to the next event's exit point; it is dropped if
 // the two exact points or the two quantized endpoints coincide. The line
@@ -1506,8 +1514,10 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
          {k_emit<false, true, false>, k_emit<false, true, true>}},
         {{k_emit<true, false, false>, k_emit<true, false, true>},
          {k_emit<true, true, false>, k_emit<true, true, true>}}};
+    const size_t rings = kWavesPerBlock * (vattr ? sizeof(EmitRingAttr) : sizeof(EmitRing));
+    static_assert(kWavesPerBlock * sizeof(EmitRingAttr) <= kEmitRankLds, "rings fit");
     hipLaunchKernelGGL(kernels[float_in][vattr != nullptr][!bricks], dim3(curve_blocks(C)),
-                       dim3(kBlock), 0, st, xyz, lat, curve_off, attr, vattr, C, s->curve_base, sad,
+                       dim3(kBlock), bricks ? 0 : kEmitRankLds - rings, st, xyz, lat, curve_off, attr, vattr, C, s->curve_base, sad,
                        ga, slots.as<uint64_t>(), rec.as<uint64_t>(), eo, vox.as<uint32_t>(),
                        rank.as<uint32_t>(), s->offsets, bg.nk[0], bg.nk[0] * bg.nk[1]);
     LS_HIP(hipGetLastError());
