@@ -5,6 +5,7 @@
 
 #include <cstdint>
 #include <cstdio>
+#include <cstring>
 
 #include "lineset.h"
 
@@ -77,10 +78,24 @@ constexpr size_t kPinnedBytes = 256;
 int pinned_alloc(void** out);
 void pinned_free(void* p);
 
-// Waits for the stream and reads `bytes` (a multiple of 4, at most
-// kPinnedBytes) of device memory behind the work queued on it: a one-workgroup
-// kernel writes them to pinned memory, which costs a launch where a copy to
-// pageable memory costs a staged copy and its own wait.
+// Launches a kernel that writes `bytes` (at most kPinnedBytes) to the pinned words
+// it is given, waits for the stream and copies them to `host`: a launch, where a
+// copy to pageable memory costs a staged copy and its own wait.
+template <typename Launch>
+int read_pinned(void* host, size_t bytes, hipStream_t st, Launch&& launch) {
+  void* slot = nullptr;
+  int rc;
+  if ((rc = pinned_alloc(&slot))) return rc;
+  launch(static_cast<uint32_t*>(slot));
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  if (e == hipSuccess) std::memcpy(host, slot, bytes);
+  pinned_free(slot);
+  LS_HIP(e);
+  return LS_OK;
+}
+
+// The same of `bytes` (a multiple of 4) of device memory.
 int read_words(const void* dev, void* host, size_t bytes, hipStream_t st);
 
 // ---------------------------------------------------------------------------

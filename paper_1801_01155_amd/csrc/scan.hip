@@ -10,8 +10,6 @@
 // they lie, and scans the rows in registers (DPP moves for 32-bit items).
 // Against tiles of 4096 staged through LDS: 16.7M items (256^3) 48 -> 32 us,
 // 134M (512^3) 450 -> 300 us of kernels (5.3 TB/s).
-#include <cstring>
-
 #include "ls_internal.h"
 #include "wave.h"
 
@@ -312,15 +310,8 @@ int clear_u32(uint32_t* a, int64_t na, uint32_t* b, int64_t nb, uint32_t* c, int
 
 int read_words(const void* dev, void* host, size_t bytes, hipStream_t st) {
   static_assert(kPinnedBytes / 4 <= 64, "one wave copies a slot");
-  void* slot = nullptr;
-  int rc;
-  if ((rc = pinned_alloc(&slot))) return rc;
-  hipLaunchKernelGGL(k_read_words, dim3(1), dim3(64), 0, st, static_cast<const uint32_t*>(dev),
-                     static_cast<uint32_t*>(slot), (int)(bytes / 4));
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  if (e == hipSuccess) std::memcpy(host, slot, bytes);
-  pinned_free(slot);
-  LS_HIP(e);
-  return LS_OK;
+  return read_pinned(host, bytes, st, [&](uint32_t* dst) {
+    hipLaunchKernelGGL(k_read_words, dim3(1), dim3(64), 0, st, static_cast<const uint32_t*>(dev),
+                       dst, (int)(bytes / 4));
+  });
 }

@@ -30,6 +30,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstddef>
 #include <type_traits>
 #include <vector>
 
@@ -143,9 +144,65 @@ __device__ inline uint32_t face_code(int axis, int side, const uint32_t xl[3], i
   return (uint32_t)(2 * axis + side) | ((uint32_t)bu << 3) | ((uint32_t)bw << 9);
 }
 
+// Brick index of voxel (x, y, z): brick << 9 | voxel in its brick (8^3 voxels, x
+// fastest). Bricks are numbered in blocks of 4 x 4 x 2 (x fastest), the blocks
+// row by row (nbx along x, nbxy in a layer): the bricks a curve visits in turn
+// then mostly share a 128-byte line of an array of words per brick, and
+// atomics of a wave that meet in one line travel as one request.
+__device__ inline uint32_t brick_index(uint32_t x, uint32_t y, uint32_t z, uint32_t nbx,
+                                       uint32_t nbxy) {
+  return (((x >> 5) + nbx * (y >> 5) + nbxy * (z >> 4)) << 14) |
+         ((x & 7u) | (y & 7u) << 3 | (z & 7u) << 6 | (x >> 3 & 3u) << 9 | (y >> 3 & 3u) << 11 |
+          (z >> 3 & 1u) << 13);
+}
+
+constexpr int kRunShift = 9;   // of the voxel in its brick
+
+// Words of the line sample, and the word of a brick: its own up to kSampleWords
+// bricks, a hashed one beyond (also of the indices that vertices outside the grid
+// give).
+constexpr uint32_t kSampleWords = 1u << 12;
+__host__ __device__ inline uint32_t sample_slot(uint32_t brick) {
+  return (brick ^ (brick >> 12) * 0x9E5u) & (kSampleWords - 1);
+}
+
 // One wave per curve; lane l of the wave handles segment s0 + l, 64 segments
 // at a time, so vertex loads and record writes are contiguous across lanes.
 constexpr int kWavesPerBlock = kBlock / 64;
+
+// Line sample: thread i takes the i-th of kSamples even parts of the vertices and in
+// it a hashed vertex and its successor, and adds the crossings between them, at
+// most 8, to the word of the brick that holds a hashed point of that segment. (A
+// curve's last vertex gives a segment to the next curve, as crowded as the curves
+// are; the limit keeps its weight near the others'.)
+constexpr int kSamples = 4096;
+constexpr int kSampleBlocks = kSamples / kBlock;
+
+template <bool kFloatIn>
+__device__ inline void sample_line(int i, const float* xyz, const int32_t* lat, int64_t n_vertices,
+                                   const SnapArgs& sa, uint32_t nbx, uint32_t nbxy,
+                                   uint32_t* sample) {
+  if (n_vertices < 2) return;
+  uint32_t x = (uint32_t)i * 0x9E3779B1u;
+  x = (x ^ x >> 15) * 0xC2B2AE3Du;
+  x ^= x >> 13;
+  const int64_t v0 = (n_vertices - 1) * i / kSamples, v1 = (n_vertices - 1) * (i + 1) / kSamples;
+  const int64_t v = v0 + (int64_t)((uint64_t)x * (uint64_t)(v1 - v0) >> 32);
+  int32_t p[3], q[3];
+  load_vertex<kFloatIn>(xyz, lat, v, sa, p);
+  load_vertex<kFloatIn>(xyz, lat, v + 1, sa, q);
+  const uint32_t f = (x * 0x165667B1u) >> 20;   // 12 bits: place on the segment
+  uint32_t n = 0, c[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    n += (uint32_t)abs((q[a] >> 8) - (p[a] >> 8));
+    c[a] = (uint32_t)((p[a] + ((int32_t)((uint32_t)(q[a] - p[a]) * f) >> 12)) >> 8);
+  }
+  // (vertices outside the grid give some word: the call fails later)
+  if (n != 0u)
+    atomicAdd(sample + sample_slot(brick_index(c[0], c[1], c[2], nbx, nbxy) >> kRunShift),
+              min(n, 8u));
+}
 
 // Per-curve count of line slots: plane crossings - 1 (an upper bound of the
 // lines; simultaneous crossings merge into one event). Validates the input.
@@ -153,14 +210,26 @@ constexpr int kWavesPerBlock = kBlock / 64;
 // loaded and snapped once and its neighbour comes by a DPP move: 20M vertices
 // 73 -> 54 us, 100M 441 -> 352 us. (In the emission, whose own work hides the
 // loads, the same made no difference.)
+// sample (or null): the first kSampleBlocks workgroups take the line sample.
 template <bool kFloatIn>
 __global__ __launch_bounds__(kBlock) void k_count(const float* xyz, const int32_t* lat,
                                                   const int64_t* curve_off, int64_t n_curves,
                                                   int64_t n_vertices, const SnapArgs* sap,
-                                                  GridArgs ga, uint64_t* slots, int* err) {
+                                                  GridArgs ga, uint64_t* slots, int* err,
+                                                  uint32_t* sample, uint32_t nbx,
+                                                  uint32_t nbxy) {
   const int lane = threadIdx.x & 63;
   const SnapArgs sa = kFloatIn ? *sap : SnapArgs{};
-  const int64_t c = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+  int64_t b = blockIdx.x;
+  if (sample) {
+    if (b < kSampleBlocks) {
+      sample_line<kFloatIn>((int)(b * kBlock + threadIdx.x), xyz, lat, n_vertices, sa, nbx, nbxy,
+                            sample);
+      return;
+    }
+    b -= kSampleBlocks;
+  }
+  const int64_t c = b * kWavesPerBlock + (threadIdx.x >> 6);
   if (c >= n_curves) return;  // wave-uniform
   const int64_t v0 = curve_off[c], v1 = curve_off[c + 1];
   if (v0 < 0 || v1 < v0 || v1 > n_vertices || (c == 0 && v0 != 0)) {
@@ -381,18 +450,6 @@ __device__ inline uint32_t last_event(const int32_t P0[3], const int32_t P1[3],
   return cross;
 }
 
-// Brick index of voxel (x, y, z): brick << 9 | voxel in its brick (8^3 voxels, x
-// fastest). Bricks are numbered in blocks of 4 x 4 x 2 (x fastest), the blocks
-// row by row (nbx along x, nbxy in a layer): the bricks a curve visits in turn
-// then mostly share a 128-byte line of an array of words per brick, and
-// atomics of a wave that meet in one line travel as one request.
-__device__ inline uint32_t brick_index(uint32_t x, uint32_t y, uint32_t z, uint32_t nbx,
-                                       uint32_t nbxy) {
-  return (((x >> 5) + nbx * (y >> 5) + nbxy * (z >> 4)) << 14) |
-         ((x & 7u) | (y & 7u) << 3 | (z & 7u) << 6 | (x >> 3 & 3u) << 9 | (y >> 3 & 3u) << 11 |
-          (z >> 3 & 1u) << 13);
-}
-
 // Segments with events wait in a per-wave ring in LDS until 64 of them
 // (or the curve's last ones) can be walked together, so the event walk runs
 // on full waves instead of on the lanes of each 64-segment chunk that happen
@@ -419,6 +476,7 @@ struct EmitRingAttr : EmitRing {
 // 1844, 1665, 1581, 1597; few lines in large grids are a little faster with more
 // (3.9M in 512^3 1099, 1102, 1106, 1116).
 constexpr size_t kEmitRankLds = 40960;
+constexpr uint64_t kEmitFew = 1u << 19;
 
 // Lines of every curve in curve order: the line inside a voxel runs from
 // one event's entry point to the next event's exit point; it is dropped if
@@ -761,7 +819,6 @@ __global__ __launch_bounds__(kBlock) void k_occupancy(const uint32_t* offsets, G
 // scattered gather. The fills are bound by the latency of a brick's serial
 // stages (offsets, runs, slots, records), so each keeps kAhead loads per lane
 // in flight; the figures stand at kBrickMinVoxels.
-constexpr int kRunShift = 9;                 // see brick_index
 constexpr uint32_t kBrickVox = 1u << kRunShift;
 
 struct BrickGrid {
@@ -1273,12 +1330,23 @@ __global__ __launch_bounds__(kBlock) void k_snap(const float* xyz, int64_t nv, S
 
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
-// Lists are formed by bricks from this many voxels and line slots on, and up to
-// this many slots per brick on average; else by one rank atomic per line in
-// k_emit, k_scatter and k_rank. Below 2^22 lines the atomics cost less than the
-// brick passes' launches (201x97x130, 70k lines: 128 us of kernels against
-// 165); small grids of long lists have too few bricks for the chip. Measured at
-// 256^3, 9.5M lines (100k x 200 curves): 1169 -> 1080 us for the whole call; at
+// How the lists are formed: by bricks, or by one rank atomic per line in k_emit,
+// k_scatter and k_rank. Whole calls, atomics against bricks, in us:
+//  - kBrickMinSlots: few lines cost less than the brick passes' launches. In 128^3
+//    0.55M lines 131 and 133, 1.1M 184 and 155, 2.2M 266 and 181; in 160^3 0.55M
+//    141 and 149, 1.1M 183 and 165.
+//  - kBrickMinMean: each brick costs its workgroups, so a grid with few lines per
+//    brick loses. Even at 1.6M lines in 256^3 (49 a brick), 7.2M in 400^3 (53),
+//    13M in 512^3 (50), 21M in 640^3 (40), 30M in 1000x1000x400 (37); 10M in 640^3
+//    (19) 2341 and 3011, 17.7M in 512^3 (68) 2308 and 2011.
+//  - kMaxShare, kMinSpread: a workgroup counts four bricks and ranges of a large
+//    brick each read all its lines, so sets crowded into few bricks lose. All
+//    lines in 16^3 voxels (8 bricks) of 256^3, 9.4M: 3370 and 7250; 32^3 (64 bricks)
+//    1205 and 1710, 40^3 (125) 1112 and 1121, 48^3 (216) 965 and 842; 29M in 40^3
+//    4000 and 4685, 48^3 3045 and 3170, 56^3 (343) 2880 and 2450. One crowded
+//    brick among others: 1/41 of 24M lines in 256^3 2165 and 2510, 1/93 1965 and
+//    1746.
+// At 256^3, 9.5M lines (100k x 200 curves): 1169 -> 1080 us for the whole call; at
 // 512^3, 140.6M lines (1M x 100): 14.63 -> 8.23 ms, of it the emission 4.66 ->
 // 2.77 ms without the rank atomics, and scatter + rank + occupancy + histogram
 // copy 7.96 -> 3.45 ms as runs (0.50 + 0.75), counts 0.55, fills 0.51 + 1.16
@@ -1287,8 +1355,75 @@ inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBl
 // in plain brick order took 1.0 + 1.2 ms at 512^3 and 0.13 + 0.15 ms at 256^3,
 // 4 x 4 x 2 blocks and 32 copies take 0.50 + 0.75 and 0.04 + 0.04.
 constexpr int64_t kBrickMinVoxels = int64_t(1) << 20;
-constexpr int64_t kBrickMinSlots = int64_t(1) << 22;
-constexpr int64_t kBrickMaxMean = 2048;
+constexpr int64_t kBrickMinSlots = int64_t(1) << 20;
+constexpr int64_t kBrickMinMean = 48;
+constexpr uint64_t kMaxShare = 64;    // the fullest brick holds at most 1/64 of the lines
+constexpr uint64_t kMinSpread = 192;  // sum over bricks of share^2 at most 1/192
+
+// The line sample: lines, of the fullest word, and the sum of the words' squares.
+struct Sample {
+  uint32_t total, most;
+  unsigned long long squares;
+};
+
+bool by_bricks(int64_t nvox, int64_t n_slots, int64_t n_bricks, const Sample& m) {
+  return nvox >= kBrickMinVoxels && n_slots >= kBrickMinSlots &&
+         n_slots >= kBrickMinMean * n_bricks && kMaxShare * m.most <= m.total &&
+         kMinSpread * m.squares <= (unsigned long long)m.total * m.total;
+}
+
+// Writes what the host reads after k_count to pinned memory: `words` words from
+// src, then the line sample's sums if the slot count (src's first 64 bits) makes
+// bricks possible.
+__global__ __launch_bounds__(kBlock) void k_read_counts(const uint32_t* __restrict__ src, int words,
+                                                      const uint32_t* __restrict__ sample,
+                                                      uint32_t* dst) {
+  __shared__ uint32_t s_total, s_most;
+  __shared__ unsigned long long s_sq;
+  if (threadIdx.x < (unsigned)words) dst[threadIdx.x] = src[threadIdx.x];
+  if (*reinterpret_cast<const uint64_t*>(src) < (uint64_t)kBrickMinSlots) return;   // uniform
+  if (threadIdx.x == 0) {
+    s_total = s_most = 0u;
+    s_sq = 0ull;
+  }
+  __syncthreads();
+  constexpr int kPer = (int)kSampleWords / (4 * kBlock);
+  uint4 q[kPer];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k)
+    q[k] = reinterpret_cast<const uint4*>(sample)[k * kBlock + threadIdx.x];
+  uint32_t total = 0, most = 0;
+  unsigned long long sq = 0;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const uint32_t w[4] = {q[k].x, q[k].y, q[k].z, q[k].w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      total += w[j];
+      most = max(most, w[j]);
+      sq += (unsigned long long)w[j] * w[j];
+    }
+  }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) {
+    total += (uint32_t)__shfl_xor((int)total, d, 64);
+    most = max(most, (uint32_t)__shfl_xor((int)most, d, 64));
+    sq += __shfl_xor(sq, d, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    atomicAdd(&s_total, total);
+    atomicMax(&s_most, most);
+    atomicAdd(&s_sq, sq);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    dst[words] = s_total;
+    dst[words + 1] = s_most;
+    dst[words + 2] = (uint32_t)s_sq;
+    dst[words + 3] = (uint32_t)(s_sq >> 32);
+  }
+}
+
 inline unsigned curve_blocks(int64_t n) {
   return (unsigned)((n + kWavesPerBlock - 1) / kWavesPerBlock);
 }
@@ -1406,12 +1541,15 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
     uint64_t n_slots;
     SnapArgs sa;
     int err[2];
+    Sample sample;   // from k_read_counts
   };
-  static_assert(sizeof(Header) == sizeof(uint64_t) + sizeof(SnapArgs) + 2 * sizeof(int),
+  constexpr int kCounts = (int)(offsetof(Header, sample) / sizeof(uint32_t));
+  static_assert(4 * kCounts == sizeof(uint64_t) + sizeof(SnapArgs) + 2 * sizeof(int) &&
+                    sizeof(Header) == 4 * kCounts + sizeof(Sample),
                 "header layout");
   const size_t slot_bytes = sizeof(uint64_t) * (C + 1);
   Drain drain(st);
-  DeviceBuf slots(drain), sums64(drain), lattice(drain);
+  DeviceBuf slots(drain), sums64(drain), lattice(drain), sample(drain);
   if ((rc = slots.alloc(slot_bytes + sizeof(SnapArgs) + 2 * sizeof(int))) ||
       (rc = sums64.alloc(sizeof(uint64_t) * scan_block_sums_len(C))) ||
       (rc = lattice.alloc(sizeof(double) * 6 * bb_blocks)))
@@ -1422,13 +1560,22 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
   // start at zero: one launch clears them with the error flags
   if ((rc = ls_alloc(s, (void**)&s->offsets, sizeof(uint32_t) * (s->nvox + 1)))) return rc;
   const bool small = s->nvox < kBrickMinVoxels;
+  BrickGrid bg{};
+  for (int a = 0; a < 3; ++a) {
+    bg.g[a] = s->grid[a];
+    bg.m[a] = (s->grid[a] + 3) / 4;
+    bg.nk[a] = (uint32_t)(s->grid[a] + (a < 2 ? 31 : 15)) / (a < 2 ? 32 : 16);
+  }
+  bg.n = 32 * bg.nk[0] * bg.nk[1] * bg.nk[2];
+  if (!small && (rc = sample.alloc(sizeof(uint32_t) * kSampleWords))) return rc;
   if (small) {
     if ((rc = occupancy_alloc(s))) return rc;
     const int64_t nm = (int64_t)s->macro[0] * s->macro[1] * s->macro[2];
     if ((rc = clear_u32(reinterpret_cast<uint32_t*>(errp), 2, s->offsets, s->nvox + 1,
                         reinterpret_cast<uint32_t*>(s->occupancy + nm), 4, st)))
       return rc;
-  } else if ((rc = clear_u32(reinterpret_cast<uint32_t*>(errp), 2, nullptr, 0, nullptr, 0, st))) {
+  } else if ((rc = clear_u32(reinterpret_cast<uint32_t*>(errp), 2, sample.as<uint32_t>(),
+                             kSampleWords, nullptr, 0, st))) {
     return rc;
   }
   if (float_in) {
@@ -1445,19 +1592,30 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
   }
   // 1. per-curve slot counts + validation
   if (C > 0) {
+    const unsigned count_blocks = curve_blocks(C) + (small ? 0 : kSampleBlocks);
     if (float_in)
-      hipLaunchKernelGGL((k_count<true>), dim3(curve_blocks(C)), dim3(kBlock), 0, st, xyz, lat,
-                         curve_off, C, s->n_vertices, sad, ga, slots.as<uint64_t>(), errp);
+      hipLaunchKernelGGL((k_count<true>), dim3(count_blocks), dim3(kBlock), 0, st, xyz, lat,
+                         curve_off, C, s->n_vertices, sad, ga, slots.as<uint64_t>(), errp,
+                         sample.as<uint32_t>(), bg.nk[0], bg.nk[0] * bg.nk[1]);
     else
-      hipLaunchKernelGGL((k_count<false>), dim3(curve_blocks(C)), dim3(kBlock), 0, st, xyz, lat,
-                         curve_off, C, s->n_vertices, sad, ga, slots.as<uint64_t>(), errp);
+      hipLaunchKernelGGL((k_count<false>), dim3(count_blocks), dim3(kBlock), 0, st, xyz, lat,
+                         curve_off, C, s->n_vertices, sad, ga, slots.as<uint64_t>(), errp,
+                         sample.as<uint32_t>(), bg.nk[0], bg.nk[0] * bg.nk[1]);
     LS_HIP(hipGetLastError());
   }
   if ((rc = exclusive_scan_u64(slots.as<uint64_t>(), slots.as<uint64_t>(), C, sums64.as<uint64_t>(),
                                st)))
     return rc;
   Header hh{};
-  if ((rc = read_words(slots.as<uint64_t>() + C, &hh, sizeof(Header), st))) return rc;
+  if (small) {
+    if ((rc = read_words(slots.as<uint64_t>() + C, &hh, 4 * kCounts, st))) return rc;
+  } else if ((rc = read_pinned(&hh, sizeof(Header), st, [&](uint32_t* dst) {
+               hipLaunchKernelGGL(k_read_counts, dim3(1), dim3(kBlock), 0, st,
+                                  reinterpret_cast<const uint32_t*>(slots.as<uint64_t>() + C),
+                                  kCounts, sample.as<uint32_t>(), dst);
+             }))) {
+    return rc;
+  }
   const uint64_t n_slots = hh.n_slots;
   const int herr = hh.err[0];
   const SnapArgs hsa = hh.sa;
@@ -1484,15 +1642,7 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
   s->n_slots = (int64_t)n_slots;
 
   // 2. the way the lists are formed
-  BrickGrid bg{};
-  for (int a = 0; a < 3; ++a) {
-    bg.g[a] = s->grid[a];
-    bg.m[a] = (s->grid[a] + 3) / 4;
-    bg.nk[a] = (uint32_t)(s->grid[a] + (a < 2 ? 31 : 15)) / (a < 2 ? 32 : 16);
-  }
-  bg.n = 32 * bg.nk[0] * bg.nk[1] * bg.nk[2];
-  const bool bricks = s->nvox >= kBrickMinVoxels && (int64_t)n_slots >= kBrickMinSlots &&
-                      (int64_t)n_slots <= kBrickMaxMean * bg.n;
+  const bool bricks = by_bricks(s->nvox, s->n_slots, bg.n, hh.sample);
 
   // 3. emit
   DeviceBuf rec(drain), vox(drain), rank(drain), sums32(drain), ends_slots(drain);
@@ -1501,9 +1651,15 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
     return rc;
   if (!bricks) {
     // the offsets array doubles as the histogram
-    if ((rc = rank.alloc(sizeof(uint32_t) * n_slots)) ||
-        (!small && (rc = fill_u32(s->offsets, 0u, s->nvox + 1, st))))
-      return rc;
+    if ((rc = rank.alloc(sizeof(uint32_t) * n_slots))) return rc;
+    if (!small) {
+      if (!lists_only && (rc = occupancy_alloc(s))) return rc;
+      const int64_t nm = (int64_t)s->macro[0] * s->macro[1] * s->macro[2];
+      if ((rc = clear_u32(s->offsets, s->nvox + 1,
+                          lists_only ? nullptr : reinterpret_cast<uint32_t*>(s->occupancy + nm), 4,
+                          nullptr, 0, st)))
+        return rc;
+    }
   }
   if (vattr && (rc = ends_slots.alloc(sizeof(uint16_t) * (n_slots ? n_slots : 1)))) return rc;
   uint16_t* eo = vattr ? ends_slots.as<uint16_t>() : nullptr;
@@ -1514,10 +1670,12 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
          {k_emit<false, true, false>, k_emit<false, true, true>}},
         {{k_emit<true, false, false>, k_emit<true, false, true>},
          {k_emit<true, true, false>, k_emit<true, true, true>}}};
+    // (few lines do not, and then more waves hide more: 70k lines 22.4 and 24.1 us)
+    const bool few = n_slots < kEmitFew;
     const size_t rings = kWavesPerBlock * (vattr ? sizeof(EmitRingAttr) : sizeof(EmitRing));
     static_assert(kWavesPerBlock * sizeof(EmitRingAttr) <= kEmitRankLds, "rings fit");
     hipLaunchKernelGGL(kernels[float_in][vattr != nullptr][!bricks], dim3(curve_blocks(C)),
-                       dim3(kBlock), bricks ? 0 : kEmitRankLds - rings, st, xyz, lat, curve_off, attr, vattr, C, s->curve_base, sad,
+                       dim3(kBlock), bricks || few ? 0 : kEmitRankLds - rings, st, xyz, lat, curve_off, attr, vattr, C, s->curve_base, sad,
                        ga, slots.as<uint64_t>(), rec.as<uint64_t>(), eo, vox.as<uint32_t>(),
                        rank.as<uint32_t>(), s->offsets, bg.nk[0], bg.nk[0] * bg.nk[1]);
     LS_HIP(hipGetLastError());
@@ -1635,7 +1793,7 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
   }
 
   // 6. macro-cell occupancy and list statistics (k_brick_count's by now)
-  if (!bricks && !lists_only && (rc = vox_occupancy(s, st, small))) return rc;
+  if (!bricks && !lists_only && (rc = vox_occupancy(s, st, true))) return rc;
   LS_HIP(hipStreamSynchronize(st));
   drain.idle = true;
   return LS_OK;
