@@ -149,9 +149,10 @@ __global__ __launch_bounds__(kBlock) void k_shadow(Pyramid P, Cones C, Sched S, 
 // LDS-tiled cone tracing by voxel columns. A block handles a tile of
 // 16 x 16 x 8 voxels; each of its 256 threads owns one (x, y) column of the
 // tile and walks its 8 voxels along z. Every sample k of every cone lies
-// within s_k (voxel units) of its voxel, so on level l the taps of the whole
+// within s_k u (voxel units) of its voxel along each axis (u = 1, or the largest
+// component of a longer light), so on level l the taps of the whole
 // tile fall inside a box of (tile extent on l) + 2 m_l cells per axis,
-// m_l = ceil(max s_k / 2^l) + 1 over the samples on l. The block first
+// m_l = floor(max s_k u / 2^l + 1/2 - 2^-(l+1)) + 1 over the samples on l. The block first
 // copies each level's box into LDS (coordinates clamped to the level, which
 // makes plain trilinear interpolation of the copy the clamp-to-edge
 // interpolation of the level).
@@ -617,10 +618,14 @@ Pyramid make_pyramid(const ls_lineset* s) {
 
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
-// Boxes of the column kernel for schedule S; false if a level above 3 is
-// sampled or the boxes exceed the LDS budget (then the untiled kernels run).
-bool make_col_levels(const ls_lineset* s, const Sched& S, ColLevels* T) {
+// Boxes of the column kernel for cones C on schedule S; false if a level above 3
+// is sampled or the boxes exceed the LDS budget (then the untiled kernels run).
+bool make_col_levels(const ls_lineset* s, const Cones& C, const Sched& S, ColLevels* T) {
   *T = ColLevels{};
+  // a light may be longer than 1: its samples lie farther out
+  double reach = 1.0;
+  for (int c = 0; c < C.n; ++c)
+    for (int a = 0; a < 3; ++a) reach = std::max(reach, std::fabs(C.dir[c][a]));
   for (int k = 0; k < S.n; ++k) {
     const int lv = S.lv[k];
     if (lv > 3) return false;
@@ -631,10 +636,11 @@ bool make_col_levels(const ls_lineset* s, const Sched& S, ColLevels* T) {
       T->m[q] = 0;
       T->n++;
     }
-    // a sample r = s / 2^lv cells away reads cells floor(x), floor(x) + 1 with
-    // |x - cell| <= r + 1/2: within ceil(r) + 1
-    const int m = (int)std::ceil((double)S.s[k] / (double)(1 << lv)) + 1;
-    T->m[q] = std::max(T->m[q], m);
+    // a sample reads cells floor(x), floor(x) + 1, with x at most r + 1/2 -
+    // 2^-(lv + 1) cells from its voxel's cell (the voxel centre's offset in it)
+    const double r = ((double)S.s[k] * reach + 0.5 * (double)((1 << lv) - 1)) / (double)(1 << lv);
+    if (!(r < 64.0)) return false;
+    T->m[q] = std::max(T->m[q], (int)std::floor(r) + 1);
     T->slot[k] = q;
   }
   const int ext[3] = {kColX, kColY, kColZ};
@@ -662,7 +668,7 @@ int launch_cones(ls_lineset* s, const Cones& C, const Sched& S, float* out, hipS
   // the column kernel pays one LDS fill per tile; with few samples per voxel
   // (the single shadow cone) direct gathers are cheaper
   ColLevels T;
-  if (C.n >= 4 && S.n >= 1 && S.n <= kColMaxSamples && make_col_levels(s, S, &T)) {
+  if (C.n >= 4 && S.n >= 1 && S.n <= kColMaxSamples && make_col_levels(s, C, S, &T)) {
     const size_t lds = sizeof(float) * (size_t)T.base[T.n];
     const dim3 grid((unsigned)(8 * T.tiles_per_xcd)), block(kColThreads);
     const Pyramid P = make_pyramid(s);
@@ -757,14 +763,14 @@ int illum_ao_shadow(ls_lineset* s, int n_cones, float radius, const float light[
   // 8 voxels then span at most two level cells along z)
   for (int k = S.n; k < SH.n; ++k)
     if (SH.lv[k] < 3) return LS_OK;
-  ColLevels T;
-  if (S.n < 1 || S.n > kColMaxSamples || !make_col_levels(s, S, &T)) return LS_OK;
-  int rc;
-  if (!s->ao && (rc = ls_alloc(s, (void**)&s->ao, sizeof(float) * (size_t)s->nvox))) return rc;
-  if (!s->sh && (rc = ls_alloc(s, (void**)&s->sh, sizeof(float) * (size_t)s->nvox))) return rc;
   Cones C = ao_cones(n_cones, radius, aperture);
   for (int a = 0; a < 3; ++a) C.dir[n_cones][a] = (double)light[a];
   C.n = n_cones + 1;
+  ColLevels T;
+  if (S.n < 1 || S.n > kColMaxSamples || !make_col_levels(s, C, S, &T)) return LS_OK;
+  int rc;
+  if (!s->ao && (rc = ls_alloc(s, (void**)&s->ao, sizeof(float) * (size_t)s->nvox))) return rc;
+  if (!s->sh && (rc = ls_alloc(s, (void**)&s->sh, sizeof(float) * (size_t)s->nvox))) return rc;
   if ((rc = launch_cones(s, C, S, s->ao, st, true, &SH, s->sh))) return rc;
   *applied = true;
   return LS_OK;
