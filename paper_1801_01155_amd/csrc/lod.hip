@@ -109,14 +109,22 @@ __global__ __launch_bounds__(kBlock) void k_lod0(const uint32_t* __restrict__ of
 struct LodRows {
   int32_t g[3], p[3];   // level 0 and level 1 dims
   int64_t off1;         // level 1's first cell
+  int32_t turn;         // log2 of the rows of blocks after which the columns turn
 };
 
 // Levels 0 and 1 together: a block takes 64 x 2 x 2 voxels, a wave per row along
 // x, and averages its 32 level-1 cells from LDS (children in k_mip's order, so
 // the same bits), instead of reading the three fields of level 0 again. 256^3,
 // 9.5M records: 171 us for both as two kernels, 147 so; its traffic takes 75, what
-// is left is the latency of a block's few serial stages. Rows shorter than
-// kRowMin would leave too many lanes idle.
+// is left is the latency of a block's few serial stages.
+// Blocks go to the XCDs, and within one to its shader engines, in turn along x
+// first. With two or four blocks to a row each XCD would see the same columns of
+// the grid only, and half of them the partly empty last one (80^3, 6.3M records
+// 92.8 us, 200^3, 16M 178), so the columns turn, every eight blocks of an XCD (70
+// to 90 and 118; every block: 93 and 182, as that keeps to the same engines).
+constexpr int kTurnRows = 3;   // log2 of an XCD's blocks between turns
+
+// Rows shorter than kRowMin would leave too many lanes idle.
 constexpr int kRowMin = 48;
 
 __global__ __launch_bounds__(kBlock) void k_lod01(const uint32_t* __restrict__ offsets,
@@ -129,7 +137,9 @@ __global__ __launch_bounds__(kBlock) void k_lod01(const uint32_t* __restrict__ o
   __shared__ uint32_t marks[kBlock];
   __shared__ float s_row[3][kBlock];
   const int lane = wave_lane(), wave = (int)(threadIdx.x >> 6);
-  const int x = 64 * (int)blockIdx.x + lane, y = 2 * (int)blockIdx.y + (wave & 1),
+  const uint32_t row = blockIdx.y + gridDim.y * blockIdx.z;
+  const int bx = (int)((blockIdx.x + (row >> g.turn)) % gridDim.x);
+  const int x = 64 * bx + lane, y = 2 * (int)blockIdx.y + (wave & 1),
             z = 2 * (int)blockIdx.z + (wave >> 1);
   const bool in = x < g.g[0] && y < g.g[1] && z < g.g[2];
   const int64_t v = x + (int64_t)g.g[0] * (y + (int64_t)g.g[1] * z);
@@ -148,7 +158,7 @@ __global__ __launch_bounds__(kBlock) void k_lod01(const uint32_t* __restrict__ o
   s_row[2][threadIdx.x] = r;
   __syncthreads();
   const int c = wave, i = lane;   // field, cell
-  const int px = 32 * (int)blockIdx.x + i;
+  const int px = 32 * bx + i;
   if (c >= 3 || i >= 32 || px >= g.p[0]) return;
   float sum = 0.f;
 #pragma unroll
@@ -400,7 +410,12 @@ int lod_build(ls_lineset* s, const float* lut, int opaque, hipStream_t st) {
       g.p[a] = s->level_dims[1][a];
     }
     g.off1 = s->level_off[1];
-    hipLaunchKernelGGL(k_lod01, dim3((g.g[0] + 63) / 64, g.p[1], g.p[2]), dim3(kBlock), 0, st,
+    const int nx = (g.g[0] + 63) / 64;
+    // nx blocks to a row: a column is back on its XCD after 8 / gcd(nx, 8) rows
+    g.turn = 3;
+    while (g.turn > 0 && nx % (16 >> g.turn) == 0) --g.turn;
+    g.turn += kTurnRows;
+    hipLaunchKernelGGL(k_lod01, dim3(nx, g.p[1], g.p[2]), dim3(kBlock), 0, st,
                        s->offsets, s->records, g, 1.0f / (float)s->bins, lut, opaque,
                        s->lod_count, s->lod_len, s->lod_rho);
     LS_HIP(hipGetLastError());
