@@ -124,8 +124,24 @@ struct LodRows {
 // to 90 and 118; every block: 93 and 182, as that keeps to the same engines).
 constexpr int kTurnRows = 3;   // log2 of an XCD's blocks between turns
 
-// Rows shorter than kRowMin would leave too many lanes idle.
-constexpr int kRowMin = 48;
+// Where that is faster than k_lod0 and k_mip (whole density pyramids, us, two
+// kernels against this one; "few" and "many": 10k and 300k curves of 100
+// vertices). One block per row, cubes: 24^3 few 33 and 20, 32^3 28 and 19, many
+// 212 and 112, 64^3 28 and 24, 80 and 78; in 400 x 400 rows of 24 53 and 56, of 40
+// 71 and 61. Else the lanes beyond the last row end idle: 80^3 (3/8 idle) few 32
+// and 29, many 74 and 90, 95^3 (1/4) 37 and 30, 82 and 83, 193^3 (1/4) 71 and 66,
+// 125 and 109, 208^3 (3/16) 82 and 72, 148 and 131. Beyond 2^23.5 voxels memory
+// counts: 104 x 400 x 400 (3/16) 151 and 154, 156 and 167, 257^3 (1/5) 166 and
+// 182, 264^3 (7/40) 182 and 184, 184 and 193, 272^3 (3/20) 200 and 183, 260 and
+// 227.
+constexpr int kRowMin = 32;
+constexpr int64_t kRowLarge = int64_t(3) << 22;
+
+bool rows_together(const ls_lineset* s) {
+  const int64_t g = s->grid[0], lanes = (g + 63) / 64 * 64;
+  if (s->n_levels < 2 || g < kRowMin) return false;
+  return lanes == 64 || (s->nvox <= kRowLarge ? 4 * g >= 3 * lanes : 6 * g >= 5 * lanes);
+}
 
 __global__ __launch_bounds__(kBlock) void k_lod01(const uint32_t* __restrict__ offsets,
                                                   const uint64_t* __restrict__ records,
@@ -403,7 +419,7 @@ int lod_build(ls_lineset* s, const float* lut, int opaque, hipStream_t st) {
       return rc;
   }
   int L = 0;
-  if (s->grid[0] >= kRowMin && s->n_levels > 1) {
+  if (rows_together(s)) {
     LodRows g{};
     for (int a = 0; a < 3; ++a) {
       g.g[a] = s->level_dims[0][a];

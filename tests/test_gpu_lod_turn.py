@@ -1,5 +1,6 @@
 """Levels 0 and 1 of the density pyramid over grids of one to nine blocks to a row,
-with enough rows that the columns of blocks turn, against the oracle."""
+with enough rows that the columns of blocks turn, and on either side of the rule
+that forms the two levels together (sides, idle lanes, voxels), against the oracle."""
 import numpy as np
 import pytest
 
