@@ -953,7 +953,7 @@ __device__ inline void for_each_line(const unsigned long long* __restrict__ runs
 __global__ __launch_bounds__(kCountThreads) void k_brick_count(
     const uint32_t* __restrict__ brick, const unsigned long long* __restrict__ runs,
     const uint32_t* __restrict__ vox, BrickGrid bg, uint32_t* counts, unsigned long long* occ,
-    unsigned long long* part, uint32_t* n_items, BrickItem* items) {
+    unsigned long long* part, uint32_t* n_items, BrickItem* items, BrickItem* longs) {
   __shared__ uint32_t hist[kGroupBricks * kBrickVox];
   __shared__ uint32_t s_ne, s_mx, own[kCountThreads], s_lines[kGroupBricks];
   __shared__ RunLists lists;
@@ -1007,8 +1007,8 @@ __global__ __launch_bounds__(kCountThreads) void k_brick_count(
     atomicMax(&s_mx, mx);
   }
   __syncthreads();
-  // bricks beyond k_brick_fill's room, cut into voxel ranges of at most
-  // kItemCap lines (or one voxel)
+  // bricks beyond k_brick_fill's room, cut into voxel ranges of at most kItemCap
+  // lines; a voxel of more goes to the long ones (n_items[1])
   if (threadIdx.x < nb) {
     const uint32_t b = b0 + threadIdx.x, n = s_lines[threadIdx.x];
     if (n > kFillCap && n <= kItemCap) {
@@ -1019,7 +1019,9 @@ __global__ __launch_bounds__(kCountThreads) void k_brick_count(
       for (uint32_t v = 0; v <= kBrickVox; ++v) {
         const uint32_t c = v < kBrickVox ? h[v] : 0u;
         if (v == kBrickVox || (sum + c > kItemCap && v > v0)) {
-          if (sum > 0) items[atomicAdd(n_items, 1u)] = BrickItem{b, (uint16_t)v0, (uint16_t)v};
+          const BrickItem it{b, (uint16_t)v0, (uint16_t)v};
+          if (sum > kItemCap) longs[atomicAdd(n_items + 1, 1u)] = it;
+          else if (sum > 0) items[atomicAdd(n_items, 1u)] = it;
           v0 = v;
           sum = 0;
         }
@@ -1034,7 +1036,7 @@ __global__ __launch_bounds__(kCountThreads) void k_brick_count(
 // What the host reads once the lists are counted.
 struct ListHeader {
   unsigned long long nonempty, max_list;
-  uint32_t n_records, n_items;
+  uint32_t n_records, n_items, n_longs, pad;
 };
 
 // Sums k_brick_count's list statistics (non-empty voxels, longest list; the two
@@ -1070,7 +1072,7 @@ __global__ __launch_bounds__(1024) void k_list_stats(const unsigned long long* _
   if (threadIdx.x == 0) {
     stats[0] = s_ne;
     stats[1] = s_mx;
-    *out = ListHeader{s_ne, s_mx, *n_records, *n_items};
+    *out = ListHeader{s_ne, s_mx, *n_records, n_items[0], n_items[1], 0u};
   }
 }
 
@@ -1179,8 +1181,7 @@ __global__ __launch_bounds__(kBlock) void k_brick_fill(
                                ends);
 }
 
-// The listed voxel ranges of larger bricks, dealt over the grid. (A voxel of
-// more than kItemCap lines is not reached: vox_build takes the other path.)
+// The listed voxel ranges of larger bricks, dealt over the grid.
 constexpr size_t kItemLds = kItemCap * (sizeof(uint32_t) + sizeof(uint16_t));
 
 __global__ __launch_bounds__(kItemThreads) void k_brick_items(
@@ -1205,22 +1206,80 @@ __global__ __launch_bounds__(kItemThreads) void k_brick_items(
   }
 }
 
-// Slots given by brick index turned into row-major voxels, with a rank from a
-// per-voxel counter (what k_emit<kRank> writes): the way back to k_scatter and
-// k_rank for sets with a voxel of more than kItemCap lines.
-__global__ __launch_bounds__(kBlock) void k_unbrick(uint32_t* vox, int64_t n_slots, BrickGrid bg,
-                                                    uint32_t* count, uint32_t* rank) {
-  const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (e >= n_slots) return;
-  const uint32_t bv = vox[e];
-  if (bv == LS_INVALID_VOXEL) return;
-  const uint32_t i = bv & (kBrickVox - 1);
+// A voxel of more than kItemCap lines: a workgroup collects its slots in the
+// order it meets them (idx, at the voxel's places in the CSR), then a thread per
+// line counts the lines of smaller slots, from LDS. Taking the whole set through
+// k_scatter and k_rank instead, after the brick passes, took 2131 us for 11M lines
+// in 256^3 with 4 voxels of 9000, 3744 with 26.5M (without bricks from the start
+// 1954 and 3102), so 818 and 1442; 44M with 4 voxels of 60k 10.8 ms, so 2.9.
+constexpr uint32_t kLongTile = 4096;
+constexpr uint32_t kLongLaunch = 32768;   // voxels per launch (grid limit)
+
+// The voxel of a long item and its lines [lo, lo + n).
+__device__ inline void long_voxel(const BrickGrid& bg, const BrickItem& it,
+                                  const uint32_t* __restrict__ offsets, uint32_t& lo, uint32_t& n) {
   uint32_t bc[3];
-  bg.brick(bv >> kRunShift, bc);
-  const uint32_t x = 8 * bc[0] + (i & 7u), y = 8 * bc[1] + (i >> 3 & 7u), z = 8 * bc[2] + (i >> 6);
-  const uint32_t v = (uint32_t)(x + (int64_t)bg.g[0] * (y + (int64_t)bg.g[1] * z));
-  vox[e] = v;
-  rank[e] = atomicAdd(count + v, 1u);
+  bg.brick(it.brick, bc);
+  const uint32_t i = it.v0, x = 8 * bc[0] + (i & 7u), y = 8 * bc[1] + (i >> 3 & 7u),
+                 z = 8 * bc[2] + (i >> 6);
+  const int64_t v = x + (int64_t)bg.g[0] * (y + (int64_t)bg.g[1] * z);
+  lo = offsets[v];
+  n = offsets[v + 1] - lo;
+}
+
+__global__ __launch_bounds__(kItemThreads) void k_long_gather(
+    const uint32_t* __restrict__ brick, const unsigned long long* __restrict__ runs,
+    const uint32_t* __restrict__ vox, BrickGrid bg, const uint32_t* __restrict__ offsets,
+    const BrickItem* __restrict__ longs, uint32_t* __restrict__ idx) {
+  __shared__ uint32_t own[kItemThreads], s_n;
+  __shared__ RunLists lists;
+  const BrickItem it = longs[blockIdx.x];
+  uint32_t lo, n;
+  long_voxel(bg, it, offsets, lo, n);
+  if (threadIdx.x == 0) s_n = 0u;
+  run_lists(brick, bg.n, it.brick, 1u, lists);
+  __syncthreads();
+  const uint32_t lane = threadIdx.x & 63u;
+  for_each_line<kItemThreads>(
+      runs, lists, vox, own + (threadIdx.x & ~63u), [&](uint32_t e, uint32_t bv) {
+        if ((bv & (kBrickVox - 1)) != it.v0) return;
+        // one atomic for the wave's lanes that came here
+        const unsigned long long m = __ballot(1);
+        const uint32_t first = (uint32_t)__builtin_ctzll(m);
+        uint32_t at = 0;
+        if (lane == first) at = atomicAdd(&s_n, (uint32_t)__popcll(m));
+        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+        idx[lo + at + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = e;
+      });
+}
+
+__global__ __launch_bounds__(kBlock) void k_long_rank(
+    const uint32_t* __restrict__ idx, const uint64_t* __restrict__ rec,
+    const uint16_t* __restrict__ ends_in, BrickGrid bg, const uint32_t* __restrict__ offsets,
+    const BrickItem* __restrict__ longs, uint64_t* __restrict__ records,
+    uint16_t* __restrict__ ends) {
+  __shared__ uint4 tile[kLongTile / 4];
+  uint32_t lo, n;
+  long_voxel(bg, longs[blockIdx.y], offsets, lo, n);
+  for (uint64_t p0 = (uint64_t)blockIdx.x * kBlock; p0 < n; p0 += (uint64_t)gridDim.x * kBlock) {
+    const bool in = p0 + threadIdx.x < n;
+    const uint32_t e = in ? idx[lo + p0 + threadIdx.x] : 0u;
+    uint32_t r = 0;
+    for (uint64_t q0 = 0; q0 < n; q0 += kLongTile) {
+      __syncthreads();
+      for (uint32_t q = threadIdx.x; q < kLongTile; q += kBlock)
+        reinterpret_cast<uint32_t*>(tile)[q] = q0 + q < n ? idx[lo + q0 + q] : 0xFFFFFFFFu;
+      __syncthreads();
+      for (uint32_t q = 0; q < kLongTile / 4; ++q) {
+        const uint4 t = tile[q];   // the same for all lanes
+        r += (t.x < e ? 1u : 0u) + (t.y < e ? 1u : 0u) + (t.z < e ? 1u : 0u) + (t.w < e ? 1u : 0u);
+      }
+    }
+    if (in) {
+      records[lo + r] = rec[e];
+      if (ends) ends[lo + r] = ends_in[e];
+    }
+  }
 }
 
 // Per-block bounds of the vertices (min and max are exact in fp32; widened
@@ -1684,18 +1743,20 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
   // 4. counts -> offsets (in place)
   DeviceBuf brick(drain), runs(drain), items(drain), part(drain), sums_b(drain);
   int64_t n_groups = 0;
+  // (and long voxels after the items)
   const size_t item_max = 3 * (size_t)(n_slots / kFillCap) + 1;
+  const size_t long_max = (size_t)(n_slots / kItemCap) + 1;
   uint32_t* n_items = nullptr;
   uint32_t* cursor = nullptr;
   if (bricks) {
-    // run counts (kReps copies, one past the last), run cursors, item count
+    // run counts (kReps copies, one past the last), run cursors, item counts
     n_groups = bg.n / kGroupBricks;
     const int64_t nc = (int64_t)kReps * bg.n;
-    const size_t words = 2 * (size_t)nc + 2;
+    const size_t words = 2 * (size_t)nc + 3;
     if ((rc = brick.alloc(sizeof(uint32_t) * words)) ||
         (rc = sums_b.alloc(sizeof(uint32_t) * scan_block_sums_len(nc))) ||
         (rc = runs.alloc(sizeof(uint64_t) * (n_slots ? n_slots : 1))) ||
-        (rc = items.alloc(sizeof(BrickItem) * item_max)) ||
+        (rc = items.alloc(sizeof(BrickItem) * (item_max + long_max))) ||
         (rc = part.alloc(sizeof(ListHeader) + sizeof(uint64_t) * n_groups)) ||
         (rc = occupancy_alloc(s)))
       return rc;
@@ -1720,7 +1781,7 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
                        runs.as<unsigned long long>(), vox.as<uint32_t>(), bg, s->offsets,
                        reinterpret_cast<unsigned long long*>(s->occupancy),
                        reinterpret_cast<unsigned long long*>(part.as<ListHeader>() + 1), n_items,
-                       items.as<BrickItem>());
+                       items.as<BrickItem>(), items.as<BrickItem>() + item_max);
     LS_HIP(hipGetLastError());
   }
   if ((rc = exclusive_scan_u32(s->offsets, s->offsets, s->nvox, sums32.as<uint32_t>(), st)))
@@ -1745,16 +1806,14 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
     s->max_list = (int64_t)lh.max_list;
     s->stats_pending = false;
   }
-  // a voxel too long for one workgroup's LDS: scatter and rank through memory
-  const bool long_list = bricks && s->max_list > (int64_t)kItemCap;
 
   // 5. the records, list by list
   if ((rc = ls_alloc(s, (void**)&s->records, sizeof(uint64_t) * (n_rec ? n_rec : 1)))) return rc;
   if (vattr && (rc = ls_alloc(s, (void**)&s->ends, sizeof(uint16_t) * (n_rec ? n_rec : 1))))
     return rc;
   uint16_t* ends = vattr ? s->ends : nullptr;
-  DeviceBuf idx(drain), count(drain);
-  if (bricks && !long_list) {
+  DeviceBuf idx(drain);
+  if (bricks) {
     if (n_rec > 0) {
       hipLaunchKernelGGL(k_brick_fill, dim3(8 * ((bg.n + 7) / 8)), dim3(kBlock), 0, st,
                          brick.as<uint32_t>(), runs.as<unsigned long long>(),
@@ -1765,20 +1824,24 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
                            brick.as<uint32_t>(), runs.as<unsigned long long>(),
                            vox.as<uint32_t>(), rec.as<uint64_t>(), eo, bg, s->offsets, n_items,
                            items.as<BrickItem>(), s->records, ends);
+      if (lh.n_longs > 0) {
+        const BrickItem* longs = items.as<BrickItem>() + item_max;
+        if ((rc = idx.alloc(sizeof(uint32_t) * (size_t)n_rec))) return rc;
+        hipLaunchKernelGGL(k_long_gather, dim3(lh.n_longs), dim3(kItemThreads), 0, st,
+                           brick.as<uint32_t>(), runs.as<unsigned long long>(),
+                           vox.as<uint32_t>(), bg, s->offsets, longs, idx.as<uint32_t>());
+        // the longest voxel's lines at once, unless the voxels fill the device
+        const unsigned across =
+            std::min(blocks_for(s->max_list), std::max(16u, 65536u / lh.n_longs));
+        for (uint32_t k = 0; k < lh.n_longs; k += kLongLaunch)
+          hipLaunchKernelGGL(k_long_rank, dim3(across, std::min(kLongLaunch, lh.n_longs - k)),
+                             dim3(kBlock), 0, st, idx.as<uint32_t>(), rec.as<uint64_t>(), eo, bg,
+                             s->offsets, longs + k, s->records, ends);
+      }
       LS_HIP(hipGetLastError());
     }
   } else {
     if ((rc = idx.alloc(sizeof(uint64_t) * (n_rec ? n_rec : 1)))) return rc;
-    if (long_list) {
-      if ((rc = rank.alloc(sizeof(uint32_t) * n_slots)) ||
-          (rc = count.alloc(sizeof(uint32_t) * s->nvox)) ||
-          (rc = fill_u32(count.as<uint32_t>(), 0u, s->nvox, st)))
-        return rc;
-      hipLaunchKernelGGL(k_unbrick, dim3(blocks_for((int64_t)n_slots)), dim3(kBlock), 0, st,
-                         vox.as<uint32_t>(), (int64_t)n_slots, bg, count.as<uint32_t>(),
-                         rank.as<uint32_t>());
-      LS_HIP(hipGetLastError());
-    }
     if (n_slots > 0) {
       hipLaunchKernelGGL(k_scatter, dim3(blocks_for((int64_t)n_slots)), dim3(kBlock), 0, st,
                          vox.as<uint32_t>(), rank.as<uint32_t>(), (int64_t)n_slots, s->offsets,
