@@ -808,7 +808,8 @@ __global__ __launch_bounds__(kBlock) void k_occupancy(const uint32_t* offsets, G
 //   k_brick_count  workgroup per 4 bricks along x: voxel histogram in LDS,
 //                  written to the offsets array (counts), with the occupancy
 //                  words and list statistics of its macro cells; lists the
-//                  bricks too large for k_brick_fill as (brick, voxel range)
+//                  bricks too large for k_brick_fill as (brick, voxel range),
+//                  their voxels of many lines by themselves (k_long_rank)
 //   scan           voxel offsets (CSR)
 //   k_brick_fill   workgroup per brick (k_brick_items: per listed range):
 //                  places the slots of its lines by voxel in LDS, ranks each
@@ -866,6 +867,7 @@ __global__ __launch_bounds__(kBlock) void k_runs(const uint32_t* __restrict__ vo
 // tables: 8 workgroups per CU), and that one listed range may hold.
 constexpr uint32_t kFillCap = 2048;
 constexpr uint32_t kItemCap = 8192;
+constexpr uint32_t kLongMin = 1024;   // lines of a voxel that goes by itself (k_long_rank)
 constexpr int kGroupBricks = 4;      // bricks per k_brick_count workgroup, along x
 constexpr int kCountThreads = 512;
 constexpr int kItemThreads = 1024;
@@ -953,7 +955,8 @@ __device__ inline void for_each_line(const unsigned long long* __restrict__ runs
 __global__ __launch_bounds__(kCountThreads) void k_brick_count(
     const uint32_t* __restrict__ brick, const unsigned long long* __restrict__ runs,
     const uint32_t* __restrict__ vox, BrickGrid bg, uint32_t* counts, unsigned long long* occ,
-    unsigned long long* part, uint32_t* n_items, BrickItem* items, BrickItem* longs) {
+    unsigned long long* part, uint32_t* n_items, BrickItem* items, BrickItem* longs,
+    uint32_t* long_bricks) {
   __shared__ uint32_t hist[kGroupBricks * kBrickVox];
   __shared__ uint32_t s_ne, s_mx, own[kCountThreads], s_lines[kGroupBricks];
   __shared__ RunLists lists;
@@ -1008,25 +1011,39 @@ __global__ __launch_bounds__(kCountThreads) void k_brick_count(
   }
   __syncthreads();
   // bricks beyond k_brick_fill's room, cut into voxel ranges of at most kItemCap
-  // lines; a voxel of more goes to the long ones (n_items[1])
+  // lines; voxels of more than kLongMin are listed by themselves
   if (threadIdx.x < nb) {
     const uint32_t b = b0 + threadIdx.x, n = s_lines[threadIdx.x];
-    if (n > kFillCap && n <= kItemCap) {
+    if (n > kFillCap && n <= kItemCap && s_mx <= kLongMin) {
       items[atomicAdd(n_items, 1u)] = BrickItem{b, 0, (uint16_t)kBrickVox};
-    } else if (n > kItemCap) {
+    } else if (n > kFillCap) {
       const uint32_t* h = hist + threadIdx.x * kBrickVox;
-      uint32_t v0 = 0, sum = 0;
-      for (uint32_t v = 0; v <= kBrickVox; ++v) {
-        const uint32_t c = v < kBrickVox ? h[v] : 0u;
-        if (v == kBrickVox || (sum + c > kItemCap && v > v0)) {
-          const BrickItem it{b, (uint16_t)v0, (uint16_t)v};
-          if (sum > kItemCap) longs[atomicAdd(n_items + 1, 1u)] = it;
-          else if (sum > 0) items[atomicAdd(n_items, 1u)] = it;
-          v0 = v;
-          sum = 0;
+      uint32_t v0 = 0, sum = 0, n_long = 0;
+      auto cut = [&](uint32_t v) {
+        if (sum > 0) items[atomicAdd(n_items, 1u)] = BrickItem{b, (uint16_t)v0, (uint16_t)v};
+        v0 = v;
+        sum = 0;
+      };
+      for (uint32_t v8 = 0; v8 < kBrickVox; v8 += 8) {   // one lane's chain: 8 loads at once
+        uint32_t c[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) c[j] = h[v8 + j];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          if (c[j] <= kLongMin) {
+            if (sum + c[j] > kItemCap) cut(v8 + j);
+            sum += c[j];
+          } else {
+            cut(v8 + j);
+            longs[atomicAdd(n_items + 1, 1u)] =
+                BrickItem{b, (uint16_t)(v8 + j), (uint16_t)(v8 + j + 1)};
+            ++n_long;
+            v0 = v8 + j + 1;
+          }
         }
-        sum += c;
       }
+      cut(kBrickVox);
+      if (n_long) long_bricks[atomicAdd(n_items + 2, 1u)] = b;
     }
   }
   if (threadIdx.x == 0)
@@ -1036,7 +1053,7 @@ __global__ __launch_bounds__(kCountThreads) void k_brick_count(
 // What the host reads once the lists are counted.
 struct ListHeader {
   unsigned long long nonempty, max_list;
-  uint32_t n_records, n_items, n_longs, pad;
+  uint32_t n_records, n_items, n_longs, n_long_bricks;
 };
 
 // Sums k_brick_count's list statistics (non-empty voxels, longest list; the two
@@ -1072,7 +1089,7 @@ __global__ __launch_bounds__(1024) void k_list_stats(const unsigned long long* _
   if (threadIdx.x == 0) {
     stats[0] = s_ne;
     stats[1] = s_mx;
-    *out = ListHeader{s_ne, s_mx, *n_records, n_items[0], n_items[1], 0u};
+    *out = ListHeader{s_ne, s_mx, *n_records, n_items[0], n_items[1], n_items[2]};
   }
 }
 
@@ -1206,12 +1223,14 @@ __global__ __launch_bounds__(kItemThreads) void k_brick_items(
   }
 }
 
-// A voxel of more than kItemCap lines: a workgroup collects its slots in the
-// order it meets them (idx, at the voxel's places in the CSR), then a thread per
-// line counts the lines of smaller slots, from LDS. Taking the whole set through
-// k_scatter and k_rank instead, after the brick passes, took 2131 us for 11M lines
-// in 256^3 with 4 voxels of 9000, 3744 with 26.5M (without bricks from the start
-// 1954 and 3102), so 818 and 1442; 44M with 4 voxels of 60k 10.8 ms, so 2.9.
+// Voxels of more than kLongMin lines: a workgroup per brick collects their slots in
+// the order it meets them (idx, at the voxel's places in the CSR), then a thread per
+// line counts the lines of smaller slots, from LDS, over the whole device where
+// k_brick_items would compare them in one workgroup. Whole calls without bricks and
+// with them, in us: 26.5M lines in 256^3 with 4 voxels of 9000 3094 and 1414, 44M
+// with 4 of 60k 10123 and 2858; 9000 curves from one point, 10M lines (voxels of up
+// to 1600) 1012 and, with kLongMin 512, 1024, 2048, 8192, 815, 852, 1132, 1083; 400
+// seeds on a line of 1500 curves, 66M 6257 and 5510, 5388, 5351, 5382.
 constexpr uint32_t kLongTile = 4096;
 constexpr uint32_t kLongLaunch = 32768;   // voxels per launch (grid limit)
 
@@ -1230,27 +1249,29 @@ __device__ inline void long_voxel(const BrickGrid& bg, const BrickItem& it,
 __global__ __launch_bounds__(kItemThreads) void k_long_gather(
     const uint32_t* __restrict__ brick, const unsigned long long* __restrict__ runs,
     const uint32_t* __restrict__ vox, BrickGrid bg, const uint32_t* __restrict__ offsets,
-    const BrickItem* __restrict__ longs, uint32_t* __restrict__ idx) {
-  __shared__ uint32_t own[kItemThreads], s_n;
+    const uint32_t* __restrict__ long_bricks, uint32_t* __restrict__ idx) {
+  __shared__ uint32_t own[kItemThreads], next[kBrickVox];   // next place; none: not long
   __shared__ RunLists lists;
-  const BrickItem it = longs[blockIdx.x];
-  uint32_t lo, n;
-  long_voxel(bg, it, offsets, lo, n);
-  if (threadIdx.x == 0) s_n = 0u;
-  run_lists(brick, bg.n, it.brick, 1u, lists);
+  constexpr uint32_t kNone = 0xFFFFFFFFu;
+  const uint32_t b = long_bricks[blockIdx.x];
+  uint32_t bc[3];
+  bg.brick(b, bc);
+  for (uint32_t i = threadIdx.x; i < kBrickVox; i += kItemThreads) {
+    const uint32_t x = 8 * bc[0] + (i & 7u), y = 8 * bc[1] + (i >> 3 & 7u), z = 8 * bc[2] + (i >> 6);
+    next[i] = kNone;
+    if (x < (uint32_t)bg.g[0] && y < (uint32_t)bg.g[1] && z < (uint32_t)bg.g[2]) {
+      const int64_t v = x + (int64_t)bg.g[0] * (y + (int64_t)bg.g[1] * z);
+      const uint32_t lo = offsets[v];
+      if (offsets[v + 1] - lo > kLongMin) next[i] = lo;
+    }
+  }
+  run_lists(brick, bg.n, b, 1u, lists);
   __syncthreads();
-  const uint32_t lane = threadIdx.x & 63u;
-  for_each_line<kItemThreads>(
-      runs, lists, vox, own + (threadIdx.x & ~63u), [&](uint32_t e, uint32_t bv) {
-        if ((bv & (kBrickVox - 1)) != it.v0) return;
-        // one atomic for the wave's lanes that came here
-        const unsigned long long m = __ballot(1);
-        const uint32_t first = (uint32_t)__builtin_ctzll(m);
-        uint32_t at = 0;
-        if (lane == first) at = atomicAdd(&s_n, (uint32_t)__popcll(m));
-        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-        idx[lo + at + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = e;
-      });
+  for_each_line<kItemThreads>(runs, lists, vox, own + (threadIdx.x & ~63u),
+                              [&](uint32_t e, uint32_t bv) {
+                                const uint32_t v = bv & (kBrickVox - 1);
+                                if (next[v] != kNone) idx[atomicAdd(next + v, 1u)] = e;
+                              });
 }
 
 __global__ __launch_bounds__(kBlock) void k_long_rank(
@@ -1270,10 +1291,13 @@ __global__ __launch_bounds__(kBlock) void k_long_rank(
       for (uint32_t q = threadIdx.x; q < kLongTile; q += kBlock)
         reinterpret_cast<uint32_t*>(tile)[q] = q0 + q < n ? idx[lo + q0 + q] : 0xFFFFFFFFu;
       __syncthreads();
-      for (uint32_t q = 0; q < kLongTile / 4; ++q) {
-        const uint4 t = tile[q];   // the same for all lanes
-        r += (t.x < e ? 1u : 0u) + (t.y < e ? 1u : 0u) + (t.z < e ? 1u : 0u) + (t.w < e ? 1u : 0u);
-      }
+      const uint32_t m = (uint32_t)min((uint64_t)kLongTile, n - q0);
+      for (uint32_t q = 0; q < (m + 3) / 4; q += 8)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const uint4 t = tile[q + j];   // the same for all lanes
+          r += (t.x < e ? 1u : 0u) + (t.y < e ? 1u : 0u) + (t.z < e ? 1u : 0u) + (t.w < e ? 1u : 0u);
+        }
     }
     if (in) {
       records[lo + r] = rec[e];
@@ -1743,26 +1767,30 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
   // 4. counts -> offsets (in place)
   DeviceBuf brick(drain), runs(drain), items(drain), part(drain), sums_b(drain);
   int64_t n_groups = 0;
-  // (and long voxels after the items)
-  const size_t item_max = 3 * (size_t)(n_slots / kFillCap) + 1;
-  const size_t long_max = (size_t)(n_slots / kItemCap) + 1;
+  // items (a long voxel may cut one in two), long voxels, bricks with some
+  const size_t long_max = (size_t)(n_slots / kLongMin) + 1;
+  const size_t item_max = 3 * (size_t)(n_slots / kFillCap) + long_max;
   uint32_t* n_items = nullptr;
+  BrickItem* longs = nullptr;
+  uint32_t* long_bricks = nullptr;
   uint32_t* cursor = nullptr;
   if (bricks) {
     // run counts (kReps copies, one past the last), run cursors, item counts
     n_groups = bg.n / kGroupBricks;
     const int64_t nc = (int64_t)kReps * bg.n;
-    const size_t words = 2 * (size_t)nc + 3;
+    const size_t words = 2 * (size_t)nc + 4;
     if ((rc = brick.alloc(sizeof(uint32_t) * words)) ||
         (rc = sums_b.alloc(sizeof(uint32_t) * scan_block_sums_len(nc))) ||
         (rc = runs.alloc(sizeof(uint64_t) * (n_slots ? n_slots : 1))) ||
-        (rc = items.alloc(sizeof(BrickItem) * (item_max + long_max))) ||
+        (rc = items.alloc(sizeof(BrickItem) * (item_max + long_max) + sizeof(uint32_t) * long_max)) ||
         (rc = part.alloc(sizeof(ListHeader) + sizeof(uint64_t) * n_groups)) ||
         (rc = occupancy_alloc(s)))
       return rc;
     uint32_t* bc = brick.as<uint32_t>();
     cursor = bc + nc + 1;
     n_items = cursor + nc;
+    longs = items.as<BrickItem>() + item_max;
+    long_bricks = reinterpret_cast<uint32_t*>(longs + long_max);
     if ((rc = fill_u32(bc, 0u, (int64_t)words, st))) return rc;
     if (n_slots > 0) {
       hipLaunchKernelGGL(k_runs<false>, dim3(blocks_for((int64_t)n_slots)), dim3(kBlock), 0, st,
@@ -1781,7 +1809,7 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
                        runs.as<unsigned long long>(), vox.as<uint32_t>(), bg, s->offsets,
                        reinterpret_cast<unsigned long long*>(s->occupancy),
                        reinterpret_cast<unsigned long long*>(part.as<ListHeader>() + 1), n_items,
-                       items.as<BrickItem>(), items.as<BrickItem>() + item_max);
+                       items.as<BrickItem>(), longs, long_bricks);
     LS_HIP(hipGetLastError());
   }
   if ((rc = exclusive_scan_u32(s->offsets, s->offsets, s->nvox, sums32.as<uint32_t>(), st)))
@@ -1825,11 +1853,10 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
                            vox.as<uint32_t>(), rec.as<uint64_t>(), eo, bg, s->offsets, n_items,
                            items.as<BrickItem>(), s->records, ends);
       if (lh.n_longs > 0) {
-        const BrickItem* longs = items.as<BrickItem>() + item_max;
         if ((rc = idx.alloc(sizeof(uint32_t) * (size_t)n_rec))) return rc;
-        hipLaunchKernelGGL(k_long_gather, dim3(lh.n_longs), dim3(kItemThreads), 0, st,
+        hipLaunchKernelGGL(k_long_gather, dim3(lh.n_long_bricks), dim3(kItemThreads), 0, st,
                            brick.as<uint32_t>(), runs.as<unsigned long long>(),
-                           vox.as<uint32_t>(), bg, s->offsets, longs, idx.as<uint32_t>());
+                           vox.as<uint32_t>(), bg, s->offsets, long_bricks, idx.as<uint32_t>());
         // the longest voxel's lines at once, unless the voxels fill the device
         const unsigned across =
             std::min(blocks_for(s->max_list), std::max(16u, 65536u / lh.n_longs));
