@@ -965,8 +965,7 @@ __device__ __attribute__((always_inline)) inline void voxels_opaque(
       cnt.tested++;
       hit = capsule(qr, dr, ddr, iddr, a, b, R.r2, si, so) && vt0r + (double)si >= 0.0;
     }
-    unsigned long long m =
-        __ballot(hit) & lane_range(max((int)P - (int)base, 0), min((int)(P + n) - (int)base, 64));
+    unsigned long long m = __ballot(hit) & chunk_lanes(P, n, base);
     while (__ballot(m != 0ull) != 0ull) {
       const int src = m ? __builtin_ctzll(m) : 0;
       const float ts = __shfl(si, src, 64);
@@ -1043,8 +1042,7 @@ __device__ __attribute__((always_inline)) inline void voxels_coop(
         hit = capsule(qr, dr, ddr, iddr, a, b, R.r2, si, so) && vt0r + (double)si >= 0.0 &&
               (firstr || HitBuf<float, kCoopSlots>::less(ltr, lir, si, k));
       }
-      unsigned long long m =
-          __ballot(hit) & lane_range(max((int)P - (int)base, 0), min((int)(P + np) - (int)base, 64));
+      unsigned long long m = __ballot(hit) & chunk_lanes(P, np, base);
       while (__ballot(m != 0ull) != 0ull) {
         const int src = m ? __builtin_ctzll(m) : 0;
         const float ts = __shfl(si, src, 64), os = __shfl(so, src, 64);
@@ -1499,7 +1497,7 @@ __device__ __attribute__((always_inline)) inline void nb_sweep(
       nl.qr[slot] = (uint8_t)r;
     }
     // this lane's lines of the chunk are contiguous, and so are their places
-    const int c0 = max((int)P - (int)base, 0), c1 = min((int)(P + total) - (int)base, 64);
+    const int c0 = chunk_lane(P, base), c1 = chunk_lane(P + total, base);
     if (c0 < c1) {
       const uint32_t before = (uint32_t)__popcll(am & lane_range(0, c0));
       if (P >= base) mb = qt + before;   // the lane's first lines

@@ -83,9 +83,7 @@ __global__ __launch_bounds__(kBlock) void k_merge_count(const uint32_t* __restri
       const bool gone = w < N && removed(mask, rec[lo0 + w]);
       const unsigned long long gm = __ballot(gone);
       if (gm == 0ull) continue;
-      // this voxel's lanes of the chunk
-      const int c0 = max((int)P - (int)base, 0), c1 = min((int)(P + n) - (int)base, 64);
-      if (c0 < c1) kept -= (uint32_t)__popcll(gm & lane_range(c0, c1));
+      kept -= (uint32_t)__popcll(gm & chunk_lanes(P, n, base));
     }
   }
   if (in) counts[v] = kept;
@@ -117,8 +115,7 @@ __global__ __launch_bounds__(kBlock) void k_merge_scatter(
     // kept records of the same voxel before this one in the chunk
     const int s0 = Po > base ? (int)(Po - base) : 0;
     if (keep) out[at + (uint32_t)__popcll(km & lane_range(s0, lane))] = r;
-    const int c0 = max((int)P - (int)base, 0), c1 = min((int)(P + n) - (int)base, 64);
-    if (c0 < c1) next += (uint32_t)__popcll(km & lane_range(c0, c1));
+    next += (uint32_t)__popcll(km & chunk_lanes(P, n, base));
   }
   if (in && add_off)
     for (uint32_t k = add_off[v], e = add_off[v + 1]; k < e; ++k) out[next++] = add_rec[k];

@@ -94,4 +94,15 @@ __device__ inline unsigned long long lane_range(int a, int b) {
   return hi & ~((1ull << a) - 1ull);
 }
 
+// Pair w's lane in the chunk [base, base + 64): 0 before it, 64 after it. (A wave's
+// pairs may number 2^31 and more.)
+__device__ inline int chunk_lane(uint32_t w, uint32_t base) {
+  return (int)min(__builtin_elementwise_sub_sat(w, base), 64u);
+}
+
+// The chunk's lanes that hold pairs [P, P + n).
+__device__ inline unsigned long long chunk_lanes(uint32_t P, uint32_t n, uint32_t base) {
+  return lane_range(chunk_lane(P, base), chunk_lane(P + n, base));
+}
+
 }  // namespace
