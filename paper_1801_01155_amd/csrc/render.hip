@@ -604,21 +604,19 @@ __device__ __attribute__((always_inline)) inline void composite(const RenderArgs
 }
 
 // Sorted register buffer of hits. Key (t, idx) lexicographic.
-template <typename TKey, int K>
+template <int K>
 struct HitBuf {
-  TKey t[K];
+  float t[K];
   float so[K];
   uint32_t idx[K];
-  uint32_t aux[K];
-  uint64_t rec[K];
   int n = 0;
   int dropped = 0;
 
-  __device__ inline static bool less(TKey ta, uint32_t ia, TKey tb, uint32_t ib) {
+  __device__ inline static bool less(float ta, uint32_t ia, float tb, uint32_t ib) {
     return ta < tb || (ta == tb && ia < ib);
   }
 
-  __device__ inline void insert(TKey tk, float sout, uint32_t id, uint32_t ax, uint64_t rc) {
+  __device__ inline void insert(float tk, float sout, uint32_t id) {
     if (n == K && !less(tk, id, t[K - 1], idx[K - 1])) {
       ++dropped;
       return;
@@ -630,20 +628,14 @@ struct HitBuf {
       bool occupied = i < n;
       bool sw = !occupied || less(tk, id, t[i], idx[i]);
       if (sw) {
-        TKey t2 = t[i];
-        float s2 = so[i];
-        uint32_t i2 = idx[i], a2 = aux[i];
-        uint64_t r2 = rec[i];
+        const float t2 = t[i], s2 = so[i];
+        const uint32_t i2 = idx[i];
         t[i] = tk;
         so[i] = sout;
         idx[i] = id;
-        aux[i] = ax;
-        rec[i] = rc;
         tk = t2;
         sout = s2;
         id = i2;
-        ax = a2;
-        rc = r2;
         if (!occupied) break;
       }
     }
@@ -657,8 +649,6 @@ struct HitBuf {
       t[i] = t[i + 1];
       so[i] = so[i + 1];
       idx[i] = idx[i + 1];
-      aux[i] = aux[i + 1];
-      rec[i] = rec[i + 1];
     }
     --n;
   }
@@ -1015,7 +1005,7 @@ __device__ __attribute__((always_inline)) inline void voxels_coop(
     const uint32_t np = need ? n : 0u;
     uint32_t N;
     const uint32_t P = wave_excl_scan(np, N);
-    HitBuf<float, kCoopSlots> buf;
+    HitBuf<kCoopSlots> buf;
     for (uint32_t base = 0; base < N; base += 64) {
       const uint32_t w = base + (uint32_t)lane;
       const int r = chunk_owner(own, P, np, base);
@@ -1040,7 +1030,7 @@ __device__ __attribute__((always_inline)) inline void voxels_coop(
         cnt.tested++;
         // t >= 0 and the pass filter are applied here, so only kept hits are pulled
         hit = capsule(qr, dr, ddr, iddr, a, b, R.r2, si, so) && vt0r + (double)si >= 0.0 &&
-              (firstr || HitBuf<float, kCoopSlots>::less(ltr, lir, si, k));
+              (firstr || HitBuf<kCoopSlots>::less(ltr, lir, si, k));
       }
       unsigned long long m = __ballot(hit) & chunk_lanes(P, np, base);
       while (__ballot(m != 0ull) != 0ull) {
@@ -1049,7 +1039,7 @@ __device__ __attribute__((always_inline)) inline void voxels_coop(
         const uint32_t ks = __shfl(k, src, 64);
         if (m) {
           if (first) cnt.hits++;
-          buf.insert(ts, os, ks, 0u, 0ull);   // the record is reloaded when composited
+          buf.insert(ts, os, ks);
           m &= m - 1ull;
         }
       }
