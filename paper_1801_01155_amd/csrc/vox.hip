@@ -827,6 +827,9 @@ struct BrickGrid {
   int32_t m[3];          // macro-cell grid (4^3 voxels)
   uint32_t nk[3];        // blocks of 4 x 4 x 2 bricks
   uint32_t n;            // bricks, those of partial blocks included
+  // room for items and for the long voxels after them (pointers of their own made
+  // every workgroup of k_brick_count wait for its arguments: 548 -> 580 us at 512^3)
+  uint32_t item_max, long_max;
   // coordinates of brick b
   __device__ inline void brick(uint32_t b, uint32_t c[3]) const {
     const uint32_t k = b >> 5;
@@ -955,8 +958,7 @@ __device__ inline void for_each_line(const unsigned long long* __restrict__ runs
 __global__ __launch_bounds__(kCountThreads) void k_brick_count(
     const uint32_t* __restrict__ brick, const unsigned long long* __restrict__ runs,
     const uint32_t* __restrict__ vox, BrickGrid bg, uint32_t* counts, unsigned long long* occ,
-    unsigned long long* part, uint32_t* n_items, BrickItem* items, BrickItem* longs,
-    uint32_t* long_bricks) {
+    unsigned long long* part, uint32_t* n_items, BrickItem* items) {
   __shared__ uint32_t hist[kGroupBricks * kBrickVox];
   __shared__ uint32_t s_ne, s_mx, own[kCountThreads], s_lines[kGroupBricks];
   __shared__ RunLists lists;
@@ -1024,26 +1026,37 @@ __global__ __launch_bounds__(kCountThreads) void k_brick_count(
         v0 = v;
         sum = 0;
       };
-      for (uint32_t v8 = 0; v8 < kBrickVox; v8 += 8) {   // one lane's chain: 8 loads at once
-        uint32_t c[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) c[j] = h[v8 + j];
+      // one lane's chain, at the end of the kernel: eight voxels at a time (one by one,
+      // 100k x 200 curves in 256^3 94 us for the kernel, so 69)
+      for (uint32_t v8 = 0; v8 < kBrickVox; v8 += 8) {
+        uint32_t all = 0, most = 0;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-          if (c[j] <= kLongMin) {
-            if (sum + c[j] > kItemCap) cut(v8 + j);
-            sum += c[j];
-          } else {
-            cut(v8 + j);
-            longs[atomicAdd(n_items + 1, 1u)] =
-                BrickItem{b, (uint16_t)(v8 + j), (uint16_t)(v8 + j + 1)};
+          all += h[v8 + j];
+          most = max(most, h[v8 + j]);
+        }
+        if (most <= kLongMin && sum + all <= kItemCap) {
+          sum += all;
+          continue;
+        }
+#pragma unroll 1
+        for (uint32_t v = v8; v < v8 + 8; ++v) {
+          const uint32_t c = h[v];
+          if (c > kLongMin || sum + c > kItemCap) cut(v);
+          if (c > kLongMin) {
+            items[bg.item_max + atomicAdd(n_items + 1, 1u)] =
+                BrickItem{b, (uint16_t)v, (uint16_t)(v + 1)};
             ++n_long;
-            v0 = v8 + j + 1;
+            v0 = v + 1;
+          } else {
+            sum += c;
           }
         }
       }
       cut(kBrickVox);
-      if (n_long) long_bricks[atomicAdd(n_items + 2, 1u)] = b;
+      if (n_long)
+        reinterpret_cast<uint32_t*>(items + bg.item_max + bg.long_max)[atomicAdd(n_items + 2, 1u)] =
+            b;
     }
   }
   if (threadIdx.x == 0)
@@ -1768,8 +1781,8 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
   DeviceBuf brick(drain), runs(drain), items(drain), part(drain), sums_b(drain);
   int64_t n_groups = 0;
   // items (a long voxel may cut one in two), long voxels, bricks with some
-  const size_t long_max = (size_t)(n_slots / kLongMin) + 1;
-  const size_t item_max = 3 * (size_t)(n_slots / kFillCap) + long_max;
+  bg.long_max = (uint32_t)(n_slots / kLongMin) + 1;
+  bg.item_max = 3 * (uint32_t)(n_slots / kFillCap) + bg.long_max;
   uint32_t* n_items = nullptr;
   BrickItem* longs = nullptr;
   uint32_t* long_bricks = nullptr;
@@ -1782,15 +1795,16 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
     if ((rc = brick.alloc(sizeof(uint32_t) * words)) ||
         (rc = sums_b.alloc(sizeof(uint32_t) * scan_block_sums_len(nc))) ||
         (rc = runs.alloc(sizeof(uint64_t) * (n_slots ? n_slots : 1))) ||
-        (rc = items.alloc(sizeof(BrickItem) * (item_max + long_max) + sizeof(uint32_t) * long_max)) ||
+        (rc = items.alloc(sizeof(BrickItem) * ((size_t)bg.item_max + bg.long_max) +
+                          sizeof(uint32_t) * bg.long_max)) ||
         (rc = part.alloc(sizeof(ListHeader) + sizeof(uint64_t) * n_groups)) ||
         (rc = occupancy_alloc(s)))
       return rc;
     uint32_t* bc = brick.as<uint32_t>();
     cursor = bc + nc + 1;
     n_items = cursor + nc;
-    longs = items.as<BrickItem>() + item_max;
-    long_bricks = reinterpret_cast<uint32_t*>(longs + long_max);
+    longs = items.as<BrickItem>() + bg.item_max;
+    long_bricks = reinterpret_cast<uint32_t*>(longs + bg.long_max);
     if ((rc = fill_u32(bc, 0u, (int64_t)words, st))) return rc;
     if (n_slots > 0) {
       hipLaunchKernelGGL(k_runs<false>, dim3(blocks_for((int64_t)n_slots)), dim3(kBlock), 0, st,
@@ -1809,7 +1823,7 @@ int vox_build(ls_lineset* s, const float* xyz, const int32_t* lat, const int64_t
                        runs.as<unsigned long long>(), vox.as<uint32_t>(), bg, s->offsets,
                        reinterpret_cast<unsigned long long*>(s->occupancy),
                        reinterpret_cast<unsigned long long*>(part.as<ListHeader>() + 1), n_items,
-                       items.as<BrickItem>(), longs, long_bricks);
+                       items.as<BrickItem>());
     LS_HIP(hipGetLastError());
   }
   if ((rc = exclusive_scan_u32(s->offsets, s->offsets, s->nvox, sums32.as<uint32_t>(), st)))
