@@ -36,15 +36,15 @@ COPY_CAL_BYTES = 2 << 30
 # the kernel source it was measured on only: bench reports it when
 # csrc/render.hip still has this sha256, else null.
 RENDER_TRAFFIC = {
-    "render_hip_sha256": "a971afa7bfda6e39f8a53f048c35227138126b3e507b9ff2dd6964cebeb0073d",
-    "bytes_per_launch": 122657154,
+    "render_hip_sha256": "6fcc58baed5e4f75dcb41df1a46595621b406bd9f82efee1f9987bbf32ddc4d7",
+    "bytes_per_launch": 123784620,
 }
 # Counters of the same launch and source, from one rocprofv3 --pmc run
 # (SQ_WAVES SQ_WAVE_CYCLES SQ_BUSY_CYCLES SQ_WAIT_ANY SQ_ACTIVE_INST_VALU
 # SQ_THREAD_CYCLES_VALU TCC_HIT_sum TCC_MISS_sum): L2 hit = hits / (hits +
 # misses); VALU lane use = thread-cycles / (64 x wave instructions); waits =
 # SQ_WAIT_ANY / SQ_WAVE_CYCLES.
-RENDER_COUNTERS = {"l2_hit": 0.829, "valu_lane_use": 0.352, "wait_frac": 0.400}
+RENDER_COUNTERS = {"l2_hit": 0.829, "valu_lane_use": 0.352, "wait_frac": 0.392}
 # fp32 operations of one ray-capsule test (two sphere quadratics, the
 # projected cylinder quadratic and its slab clip), counted from the kernel
 # source; the VALU figure of the roofline is tests x this / launch time.

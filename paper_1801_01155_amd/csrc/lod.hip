@@ -115,7 +115,7 @@ struct LodRows {
 // Levels 0 and 1 together: a block takes 64 x 2 x 2 voxels, a wave per row along
 // x, and averages its 32 level-1 cells from LDS (children in k_mip's order, so
 // the same bits), instead of reading the three fields of level 0 again. 256^3,
-// 9.5M records: 171 us for both as two kernels, 147 so; its traffic takes 75, what
+// 9.5M records: 171 us for both as two kernels, 121 so; its traffic takes 75, what
 // is left is the latency of a block's few serial stages.
 // Blocks go to the XCDs, and within one to its shader engines, in turn along x
 // first. With two or four blocks to a row each XCD would see the same columns of

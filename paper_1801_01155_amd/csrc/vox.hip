@@ -1446,7 +1446,7 @@ inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBl
 // 512^3, 140.6M lines (1M x 100): 14.63 -> 8.23 ms, of it the emission 4.66 ->
 // 2.77 ms without the rank atomics, and scatter + rank + occupancy + histogram
 // copy 7.96 -> 3.45 ms as runs (0.50 + 0.75), counts 0.55, fills 0.51 + 1.16
-// (with counting, emission and scans as they are now 870 us and 7.35 ms).
+// (with counting, emission and scans as they are now 860 us and 7.35 ms).
 // Run atomics are bound by requests per 128-byte line: one copy of the counters
 // in plain brick order took 1.0 + 1.2 ms at 512^3 and 0.13 + 0.15 ms at 256^3,
 // 4 x 4 x 2 blocks and 32 copies take 0.50 + 0.75 and 0.04 + 0.04.
